@@ -897,7 +897,7 @@ enova_status enova_detect_ref_stats(enova_detector det, const void *x, const int
     if (!x || !soff || !out_mean || !out_std)
         return fail(ENOVA_EINVAL, "NULL argument");
     DeviceGuard dg(det->device);
-    hipError_t e = launch_ref_stats(det->g, x, soff, n, out_mean, out_std, stream);
+    hipError_t e = launch_ref_stats(det->g, x, soff, n, out_mean, out_std, nullptr, stream);
     if (e != hipSuccess)
         return hip_fail(e, "reference statistics kernel");
     return ENOVA_OK;
@@ -906,16 +906,26 @@ enova_status enova_detect_ref_stats(enova_detector det, const void *x, const int
 namespace {
 
 // The scoring path's workspace: reference statistics [2][n][M] floats (when the caller gives
-// none), the matrix-core kernel's first tile of each stream [n+1] and stream of each block [grid].
+// none) and their chunk sums, the matrix-core kernel's first tile of each stream [n+1] and stream
+// of each block [grid].
 struct ScoreWork {
     float *stats = nullptr;
+    double *part = nullptr;
     int64_t *tiles = nullptr;
     int *tile_map = nullptr;
 };
 
-// Bytes of the fixed-scratch layout of that workspace, each part on a 256-byte boundary.
+// Floats of the statistics and of their chunk sums behind them (on a 16-byte boundary).
+size_t stats_floats(int32_t n, int M, size_t *o_part)
+{
+    *o_part = (2 * static_cast<size_t>(n) * M + 3) / 4 * 4;
+    return *o_part + stat_part_bytes(n, M) / sizeof(float);
+}
+
+// Bytes of the fixed-scratch layout of that workspace, each part on a 256-byte boundary. The chunk
+// sums come last and only where they still fit the scratch (*o_part = 0: one block per stream).
 size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, bool stats, size_t *o_tiles,
-                     size_t *o_map)
+                     size_t *o_map, size_t *o_part)
 {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     size_t o = stats ? up(2 * static_cast<size_t>(n) * g.M * sizeof(float)) : 0;
@@ -925,6 +935,12 @@ size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, bool 
     *o_map = o;
     if (kind == 2)
         o += up(static_cast<size_t>(grid > 0 ? grid : 1) * sizeof(int));
+    *o_part = 0;
+    const size_t part = stats ? stat_part_bytes(n, g.M) : 0;
+    if (part > 0 && o > 0 && o + part <= kScratchBytes) {
+        *o_part = o;
+        o += part;
+    }
     return o;
 }
 
@@ -954,8 +970,8 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         return fail(ENOVA_EUNSUPPORTED, "too many windows");
     ScoreWork wk;
     if (noalloc) {
-        size_t o_tiles = 0, o_map = 0;
-        const size_t need = noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map);
+        size_t o_tiles = 0, o_map = 0, o_part = 0;
+        const size_t need = noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part);
         if (need > kScratchBytes)
             return fail(ENOVA_ESHAPE,
                         "the allocation-free call needs %zu bytes of device scratch for %d streams and %lld "
@@ -967,6 +983,7 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         wk.stats = reinterpret_cast<float *>(base);
         wk.tiles = reinterpret_cast<int64_t *>(base + o_tiles);
         wk.tile_map = reinterpret_cast<int *>(base + o_map);
+        wk.part = o_part ? reinterpret_cast<double *>(base + o_part) : nullptr;
     }
     DeviceGuard dg(det->device);
     if (!dg.ok)
@@ -980,8 +997,9 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     }
     if (!noalloc) {
         enova_status st = ENOVA_OK;
+        size_t o_part = 0;
         if (!ref_mean)
-            st = ensure(&det->stats, &det->stats_cap, 2 * static_cast<size_t>(n) * g.M);
+            st = ensure(&det->stats, &det->stats_cap, stats_floats(n, g.M, &o_part));
         if (st == ENOVA_OK && det->kind == 2) {
             st = ensure(&det->tiles, &det->tiles_cap, static_cast<size_t>(n) + 1);
             if (st == ENOVA_OK)
@@ -990,21 +1008,31 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         if (st != ENOVA_OK)
             return st;
         wk.stats = det->stats;
+        if (!ref_mean && stat_part_bytes(n, g.M) > 0)
+            wk.part = reinterpret_cast<double *>(det->stats + o_part);
         wk.tiles = det->tiles;
         wk.tile_map = det->tile_map;
     }
-    if (!ref_mean) {
-        ref_mean = wk.stats;
-        ref_std = wk.stats + static_cast<size_t>(n) * g.M;
-        if (timing)
-            (void)hipEventRecord(det->ev[0], stream);
-        e = launch_ref_stats(g, x, soff, n, wk.stats, wk.stats + static_cast<size_t>(n) * g.M, stream);
+    const bool own = !ref_mean;
+    float *own_mean = own ? wk.stats : nullptr, *own_std = own ? wk.stats + static_cast<size_t>(n) * g.M : nullptr;
+    if (own) {
+        ref_mean = own_mean;
+        ref_std = own_std;
+    }
+    if (timing && own)
+        (void)hipEventRecord(det->ev[0], stream);
+    if (det->kind == 2) {
+        e = launch_prep_scan(g, x, soff, woff, n, g.Nb, wk.tiles, own_mean, own_std, wk.part, stream);
+        if (e != hipSuccess)
+            return hip_fail(e, "tile scan and reference statistics kernels");
+    } else if (own) {
+        e = launch_ref_stats(g, x, soff, n, own_mean, own_std, wk.part, stream);
         if (e != hipSuccess)
             return hip_fail(e, "reference statistics kernel");
-        if (timing)
-            (void)hipEventRecord(det->ev[1], stream);
-        det->ran_stats = timing;
     }
+    if (timing && own)
+        (void)hipEventRecord(det->ev[1], stream);
+    det->ran_stats = timing && own;
     ScoreParams p{};
     p.x = x;
     p.soff = soff;
@@ -1036,11 +1064,8 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     p.md = out_md;
     p.flags = out_flags;
     if (det->kind == 2) {
-        e = launch_stream_scan(g, soff, woff, n, 0, g.Nb, wk.tiles, stream);
-        if (e != hipSuccess)
-            return hip_fail(e, "tile scan kernel");
         p.tile_off = wk.tiles;
-        e = launch_tile_map(wk.tiles, n, grid, wk.tile_map, stream);
+        e = launch_prep_map(g, x, soff, wk.tiles, n, grid, wk.tile_map, own_mean, own_std, wk.part, stream);
         if (e != hipSuccess)
             return hip_fail(e, "tile map kernel");
         p.tile_stream = wk.tile_map;
@@ -1119,9 +1144,10 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         if (grid > 0x7fffffffLL)
             return fail(ENOVA_EUNSUPPORTED, "too many tiles (%lld)", static_cast<long long>(grid));
         const bool stats = norm == ENOVA_NORM_REFERENCE && !ref_mean;
-        // workspace: reference statistics [2][n][M] floats, first tile of each stream [n+1]
-        // int64, stream of each block [grid] ints
-        const size_t n_st = stats ? (2 * static_cast<size_t>(n) * M + 3) / 4 * 4 : 0;
+        // workspace: reference statistics [2][n][M] floats and their chunk sums, first tile of each
+        // stream [n+1] int64, stream of each block [grid] ints
+        size_t o_part = 0;
+        const size_t n_st = stats ? stats_floats(n, M, &o_part) : 0;
         const size_t n_tiles = 2 * (static_cast<size_t>(n) + 1);
         enova_status st = ensure(&det->ext_ws, &det->ext_ws_cap, n_st + n_tiles + static_cast<size_t>(grid) + 4);
         if (st != ENOVA_OK)
@@ -1130,16 +1156,17 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         int *tmap = reinterpret_cast<int *>(tiles + n + 1);
         if (det->timing)
             (void)hipEventRecord(det->ext_ev[0], stream);
+        float *own_mean = stats ? det->ext_ws : nullptr;
+        float *own_std = stats ? det->ext_ws + static_cast<size_t>(n) * M : nullptr;
+        double *part = stats && stat_part_bytes(n, M) > 0 ? reinterpret_cast<double *>(det->ext_ws + o_part) : nullptr;
         if (stats) {
-            ref_mean = det->ext_ws;
-            ref_std = det->ext_ws + static_cast<size_t>(n) * M;
-            if ((e = launch_ref_stats(g, x, soff, n, det->ext_ws, det->ext_ws + static_cast<size_t>(n) * M,
-                                      stream)) != hipSuccess)
-                return hip_fail(e, "reference statistics kernel");
+            ref_mean = own_mean;
+            ref_std = own_std;
         }
-        if ((e = launch_stream_scan(g, soff, woff, n, 0, kExtFusedNb, tiles, stream)) != hipSuccess)
-            return hip_fail(e, "tile scan kernel");
-        if ((e = launch_tile_map(tiles, n, grid, tmap, stream)) != hipSuccess)
+        if ((e = launch_prep_scan(g, x, soff, woff, n, kExtFusedNb, tiles, own_mean, own_std, part, stream)) !=
+            hipSuccess)
+            return hip_fail(e, "tile scan and reference statistics kernels");
+        if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
         ExtFusedParams fp{};
         fp.x = static_cast<const float *>(x);
@@ -1192,13 +1219,15 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
     if (det->timing)
         (void)hipEventRecord(det->ext_ev[0], stream);
     if (norm == ENOVA_NORM_REFERENCE && !ref_mean) {
-        st = ensure(&det->stats, &det->stats_cap, 2 * static_cast<size_t>(n) * M);
+        size_t o_part = 0;
+        st = ensure(&det->stats, &det->stats_cap, stats_floats(n, M, &o_part));
         if (st != ENOVA_OK)
             return st;
         ref_mean = det->stats;
         ref_std = det->stats + static_cast<size_t>(n) * M;
-        if ((e = launch_ref_stats(g, x, soff, n, det->stats, det->stats + static_cast<size_t>(n) * M, stream)) !=
-            hipSuccess)
+        double *part = stat_part_bytes(n, M) > 0 ? reinterpret_cast<double *>(det->stats + o_part) : nullptr;
+        if ((e = launch_ref_stats(g, x, soff, n, det->stats, det->stats + static_cast<size_t>(n) * M, part,
+                                  stream)) != hipSuccess)
             return hip_fail(e, "reference statistics kernel");
     }
     GemmEpilogue plain{};

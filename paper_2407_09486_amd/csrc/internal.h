@@ -138,8 +138,17 @@ struct ScoreParams {
 };
 
 // Launchers (return the launch error).
+// part: stat_part_bytes(n, M) bytes for chunk sums (then about 2048 blocks share the streams), or
+// NULL (one block per stream); the statistics are bit for bit the same.
+size_t stat_part_bytes(int n, int M);
 hipError_t launch_ref_stats(const Geometry &g, const void *x, const int64_t *soff, int n,
-                            float *mean, float *std, hipStream_t st);
+                            float *mean, float *std, double *part, hipStream_t st);
+// The two launches that head a scoring pass: the tiles' scan (launch_stream_scan, mode 0) with the
+// reference statistics unless mean is NULL, then the tile map with the statistics' last step.
+hipError_t launch_prep_scan(const Geometry &g, const void *x, const int64_t *soff, const int64_t *woff, int n,
+                            int div, int64_t *tile_off, float *mean, float *std, double *part, hipStream_t st);
+hipError_t launch_prep_map(const Geometry &g, const void *x, const int64_t *soff, const int64_t *tile_off, int n,
+                           int64_t grid, int *map, float *mean, float *std, const double *part, hipStream_t st);
 // out[s] = sum_{r<s} ceil(count(s)/div) for count(s) = (mode 0) windows of stream s,
 // (mode 1) calibration windows of stream s. out has n+1 entries.
 hipError_t launch_stream_scan(const Geometry &g, const int64_t *soff, const int64_t *woff, int n,
