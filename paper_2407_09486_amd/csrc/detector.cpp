@@ -74,6 +74,10 @@ struct enova_detector_s {
     void *ring_w = nullptr;       // ring kernel: W1, heads and decoder fragments (one allocation)
     const uint4 *w1r = nullptr, *whr = nullptr;
     const uint2 *wdr = nullptr;
+    SplitGeometry sg;             // split kernel (fp32 detectors): its tiles and fragments (one allocation)
+    void *split_w = nullptr;
+    const uint4 *w1x = nullptr, *whx = nullptr, *wdx = nullptr;
+    const float *w1scale = nullptr;
     void *stream_w = nullptr;     // streaming kernel: W1, heads and decoder fragments (one allocation)
     const uint4 *w1s = nullptr;
     const float *whs = nullptr, *wds = nullptr;
@@ -238,6 +242,38 @@ enova_status ensure(T **buf, size_t *cap, size_t need)
     return ENOVA_OK;
 }
 
+// The f16 nearest to f (ties to even; |f| below 65520) and its value.
+uint16_t float_to_f16(float f, float *value)
+{
+    uint32_t u;
+    std::memcpy(&u, &f, sizeof(u));
+    const uint32_t sign = u & 0x80000000u, a = u ^ sign;
+    if (a < 0x38800000u) {                       // below 2^-14: a multiple of 2^-24
+        volatile float t = f + 0.75f;            // 0.75 has 2^-24 as its last place
+        *value = t - 0.75f;
+        return static_cast<uint16_t>((sign >> 16) | static_cast<uint32_t>(std::fabs(*value) * 0x1p24f));
+    }
+    const uint32_t r = (a + 0xfffu + ((a >> 13) & 1u)) & ~0x1fffu;
+    const uint32_t v = r | sign;
+    std::memcpy(value, &v, sizeof(v));
+    return static_cast<uint16_t>((sign >> 16) | ((r - 0x38000000u) >> 13));
+}
+
+// fn(src, kappa, e) for every weight src = t * M + m of a W1 row in the chunk order of super-rows of
+// cpr chunks of epc elements (mp elements a step): element e of chunk kappa.
+template <typename F>
+void for_row(const Geometry &g, int mp, int cpr, int epc, F fn)
+{
+    const int sh = epc == 8 ? 3 : 2;
+    for (int t = 0; t < g.W; ++t) {
+        const int q = t / g.S, base = (t - q * g.S) * mp;
+        for (int m = 0; m < g.M; ++m) {
+            const int el = base + m;
+            fn(t * g.M + m, q * cpr + (el >> sh), el & (epc - 1));
+        }
+    }
+}
+
 // Fragments of the ring kernel (bf16 detectors with 193..256 hidden units), one allocation:
 //  W1      step i = q * KS + sp (KS = P / 4), hidden block hb (16 rows), lane l: the 8 bf16 of
 //          W1[16 hb + l % 16] at the elements of chunk 4 sp + l / 16 of super-row q (zero past the
@@ -340,38 +376,17 @@ enova_status pack_stream(enova_detector d, const enova_detect_weights *w)
     const size_t n_wh = static_cast<size_t>(NHB) * 4 * 2 * 64;   // floats
     const size_t n_wd = static_cast<size_t>(NHB) * 4 * 64;       // floats
     std::vector<uint32_t> buf(n_w1 * 4 + n_wh + n_wd, 0u);
-    for (int j = 0; j < steps; ++j)
-        for (int hb = 0; hb < NHB; ++hb)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int h = 16 * hb + (lane & 15);
-                const int kappa = 4 * j + (lane >> 4);
-                if (h >= H || kappa >= g.KC)
-                    continue;
-                const int q = kappa / g.CPR;
-                const int c = kappa - q * g.CPR;
-                uint16_t bits[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                float vals[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                for (int e = 0; e < g.epc; ++e) {
-                    const int jj = c * g.epc + e;
-                    const int tt = jj / g.Mp;
-                    const int m = jj - tt * g.Mp;
-                    const int t = q * g.S + tt;
-                    if (q < g.Q && t < g.W && m < g.M) {
-                        const int64_t at = static_cast<int64_t>(h) * D + static_cast<int64_t>(t) * g.M + m;
-                        if (bf)
-                            bits[e] = static_cast<const uint16_t *>(w->w1)[at];
-                        else
-                            vals[e] = static_cast<const float *>(w->w1)[at];
-                    }
-                }
-                uint32_t *dst = &buf[((static_cast<size_t>(j) * NHB + hb) * 64 + lane) * 4];
-                if (bf) {
-                    for (int e = 0; e < 4; ++e)
-                        dst[e] = static_cast<uint32_t>(bits[2 * e]) | (static_cast<uint32_t>(bits[2 * e + 1]) << 16);
-                } else {
-                    std::memcpy(dst, vals, 16);
-                }
-            }
+    for (int h = 0; h < H; ++h) {
+        const int64_t row = static_cast<int64_t>(h) * D;
+        uint32_t *dst = buf.data() + (static_cast<size_t>(h >> 4) * 64 + (h & 15)) * 4;
+        for_row(g, g.Mp, g.CPR, g.epc, [&](int j, int kappa, int e) {
+            uint32_t *at = dst + (static_cast<size_t>(kappa >> 2) * NHB * 64 + (kappa & 3) * 16) * 4;
+            if (bf)
+                reinterpret_cast<uint16_t *>(at)[e] = static_cast<const uint16_t *>(w->w1)[row + j];
+            else
+                std::memcpy(at + e, static_cast<const float *>(w->w1) + row + j, 4);
+        });
+    }
     float *wh = reinterpret_cast<float *>(buf.data() + n_w1 * 4);
     float *wd = wh + n_wh;
     for (int hb = 0; hb < NHB; ++hb)
@@ -430,12 +445,98 @@ enova_status pack_ext_fused(enova_detector d, const enova_detect_weights *w)
     return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the fused variant kernel");
 }
 
+// Weights the split kernel can take: all finite, and none so large that a product of three layers
+// could leave the fp32 range.
+bool split_weights_ok(const Geometry &g, const enova_detect_weights *w)
+{
+    const size_t H = g.H, L = g.L, D = g.D;
+    auto ok = [](const void *p, size_t n) {
+        const float *f = static_cast<const float *>(p);
+        bool good = true;
+        for (size_t i = 0; i < n; ++i)
+            good &= std::fabs(f[i]) < 0x1p20f;   // false for NaN
+        return good;
+    };
+    return ok(w->w1, H * D) && ok(w->b1, H) && ok(w->wmu, L * H) && ok(w->bmu, L) && ok(w->wlv, L * H) &&
+           ok(w->blv, L) && ok(w->wd1, H * L) && ok(w->bd1, H);
+}
+
+// Fragments of the split kernel, one allocation:
+//  W1      step i, hidden block hb, part (hi, lo), lane l: the 8 f16 of W1[32 hb + l % 32] at chunk
+//          2i + l / 32 (8 elements; zero past the window, the hidden width or the row), each row
+//          scaled by 2^e with its largest |w| in [2^13, 2^14); kSplitPrefetch zero steps follow.
+//  heads   [hb][m][part][lane] 8 bf16 and decoder [hb][part][lane] 8 bf16: the slots of the bf16
+//          detectors' fragments (reduction slot t of lane half g is hidden row crow(8m + t, g),
+//          latent crow(t, g)), three parts of each weight.
+//  scale   2^-e / kSplitScale of each hidden row.
+enova_status pack_split(enova_detector d, const enova_detect_weights *w)
+{
+    const Geometry &g = d->g;
+    const SplitGeometry &sg = d->sg;
+    const int H = g.H, L = g.L, HB = g.HB;
+    const float *w1 = static_cast<const float *>(w->w1);
+    const size_t n_w1 = static_cast<size_t>(sg.nsteps + kSplitPrefetch) * HB * 2 * 64;   // 16-byte fragments
+    const size_t n_wh = static_cast<size_t>(HB) * 2 * 3 * 64, n_wd = static_cast<size_t>(HB) * 3 * 64;
+    std::vector<uint16_t> buf((n_w1 + n_wh + n_wd) * 8 + static_cast<size_t>(g.Hp) * 2, 0);
+    uint16_t *w1x = buf.data(), *whx = w1x + n_w1 * 8, *wdx = whx + n_wh * 8;
+    float *scale = reinterpret_cast<float *>(wdx + n_wd * 8);
+    for (int h = 0; h < H; ++h) {
+        const float *row = w1 + static_cast<size_t>(h) * g.D;
+        float big = 0.0f;
+        for (int j = 0; j < g.D; ++j)
+            big = std::max(big, std::fabs(row[j]));
+        const int e = big > 0.0f ? std::min(13 - std::ilogb(big), 100) : 0;
+        const float up = std::ldexp(1.0f, e);
+        scale[h] = std::ldexp(1.0f, -e - 4);
+        uint16_t *dst = w1x + (static_cast<size_t>(h >> 5) * 2 * 64 + (h & 31)) * 8;
+        for_row(g, sg.Mp, sg.CPR, 8, [&](int j, int kappa, int e) {
+            const float v = row[j] * up;
+            uint16_t *at = dst + (static_cast<size_t>(kappa >> 1) * HB * 2 * 64 + (kappa & 1) * 32) * 8 + e;
+            float hi, lo;
+            at[0] = float_to_f16(v, &hi);
+            at[64 * 8] = float_to_f16(v - hi, &lo);
+        });
+    }
+    auto parts = [](float v, uint16_t *dst, size_t stride) {
+        for (int q = 0; q < 3; ++q) {
+            const uint16_t b = float_to_bf16_bits(v);
+            dst[q * stride] = b;
+            v -= bf16_bits_to_float(b);
+        }
+    };
+    for (int hb = 0; hb < HB; ++hb)
+        for (int lane = 0; lane < 64; ++lane)
+            for (int t = 0; t < 8; ++t) {
+                for (int m = 0; m < 2; ++m) {
+                    const int row = lane & 31, h = hb * 32 + crow(8 * m + t, lane >> 5);
+                    float v = 0.0f;
+                    if (h < H && (row & 15) < L)
+                        v = row < 16 ? w->wmu[row * H + h] : w->wlv[(row - 16) * H + h];
+                    parts(v, whx + (((static_cast<size_t>(hb) * 2 + m) * 3) * 64 + lane) * 8 + t, 64 * 8);
+                }
+                const int h = hb * 32 + (lane & 31), l = crow(t, lane >> 5);
+                parts(h < H && l < L ? w->wd1[h * L + l] : 0.0f,
+                      wdx + ((static_cast<size_t>(hb) * 3) * 64 + lane) * 8 + t, 64 * 8);
+            }
+    enova_status st = dev_upload(&d->split_w, buf.data(), buf.size() * sizeof(uint16_t));
+    if (st != ENOVA_OK)
+        return st;
+    d->w1x = static_cast<const uint4 *>(d->split_w);
+    d->whx = d->w1x + n_w1;
+    d->wdx = d->whx + n_wh;
+    d->w1scale = reinterpret_cast<const float *>(d->wdx + n_wd);
+    hipError_t e = prepare_score_split(g, d->sg);
+    if (e == hipSuccess)
+        e = prepare_score_list(g);
+    return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the split scoring kernel");
+}
+
 void free_detector(enova_detector d)
 {
     if (!d)
         return;
     void *ptrs[] = {d->w1p, d->w1t, d->small, d->stats, d->tiles, d->tile_map, d->cal, d->hist,
-                    d->peaks, d->blk, d->gx, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w};
+                    d->peaks, d->blk, d->gx, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -611,12 +712,6 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
 
     const int H = g.H, L = g.L, D = g.D, Hp = g.Hp;
     const bool bf = g.dtype == ENOVA_BF16;
-    auto w1v = [&](int h, int j) -> float {
-        if (bf)
-            return bf16_bits_to_float(static_cast<const uint16_t *>(w->w1)[static_cast<int64_t>(h) * D + j]);
-        return static_cast<const float *>(w->w1)[static_cast<int64_t>(h) * D + j];
-    };
-
     // small arrays: b1[Hp] bd1[Hp] u[Hp] bh[32] bmu[L] blv[L] wmu[L*H] wlv[L*H] wd1[H*L]
     //               whp[HB*16*64] wd1p[HB*8*64]
     const size_t n_whp = d->kind == 2 ? static_cast<size_t>(g.HB) * 16 * 64 : 0;
@@ -642,13 +737,14 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
     const size_t o_wd1 = take(static_cast<size_t>(H) * L);
     std::vector<float> small(o, 0.0f);
 
+    std::vector<double> cs(H, 0.0);
+    for (int j = 0; j < D; ++j)
+        for (int h = 0; h < H; ++h)
+            cs[h] += static_cast<double>(w->wd2[static_cast<int64_t>(j) * H + h]);
     for (int h = 0; h < H; ++h) {
         small[o_b1 + h] = w->b1[h];
         small[o_bd1 + h] = w->bd1[h];
-        double cs = 0.0;
-        for (int j = 0; j < D; ++j)
-            cs += static_cast<double>(w->wd2[static_cast<int64_t>(j) * H + h]);
-        small[o_u + h] = static_cast<float>(cs);
+        small[o_u + h] = static_cast<float>(cs[h]);
     }
     double sb = 0.0;
     for (int j = 0; j < D; ++j)
@@ -757,9 +853,13 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
                      p_bml = takd(2 * static_cast<size_t>(L)), p_wd1 = takd(static_cast<size_t>(H) * L),
                      p_wd2 = takd(static_cast<size_t>(D) * H), p_bd2 = takd(D);
         std::vector<float> dn(od, 0.0f);
-        for (int h = 0; h < H; ++h)
-            for (int j = 0; j < D; ++j)
-                dn[p_w1 + static_cast<size_t>(h) * D + j] = w1v(h, j);
+        if (bf) {
+            const uint16_t *src = static_cast<const uint16_t *>(w->w1);
+            for (size_t i = 0; i < static_cast<size_t>(H) * D; ++i)
+                dn[p_w1 + i] = bf16_bits_to_float(src[i]);
+        } else {
+            std::memcpy(&dn[p_w1], w->w1, sizeof(float) * static_cast<size_t>(H) * D);
+        }
         std::memcpy(&dn[p_wml], w->wmu, sizeof(float) * L * H);
         std::memcpy(&dn[p_wml + static_cast<size_t>(L) * H], w->wlv, sizeof(float) * L * H);
         std::memcpy(&dn[p_bml], w->bmu, sizeof(float) * L);
@@ -797,37 +897,17 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
         const int steps = g.KC / 2;
         const size_t frag = static_cast<size_t>(steps + kPrefetchSteps) * g.HB * 64;
         std::vector<uint32_t> pk(frag * 4, 0u);
-        for (int i = 0; i < steps; ++i)
-            for (int hb = 0; hb < g.HB; ++hb)
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int h = hb * 32 + (lane & 31);
-                    const int kappa = 2 * i + (lane >> 5);
-                    const int q = kappa / g.CPR;
-                    const int c = kappa - q * g.CPR;
-                    float vals[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                    uint16_t bits[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                    for (int e = 0; e < g.epc; ++e) {
-                        const int jj = c * g.epc + e;
-                        const int tt = jj / g.Mp;
-                        const int m = jj - tt * g.Mp;
-                        const int t = q * g.S + tt;
-                        if (h < H && t < g.W && m < g.M && q < g.Q) {
-                            const int64_t j = static_cast<int64_t>(t) * g.M + m;
-                            if (bf)
-                                bits[e] = static_cast<const uint16_t *>(w->w1)[static_cast<int64_t>(h) * D + j];
-                            else
-                                vals[e] = w1v(h, static_cast<int>(j));
-                        }
-                    }
-                    uint32_t *dst = &pk[((static_cast<size_t>(i) * g.HB + hb) * 64 + lane) * 4];
-                    if (bf) {
-                        for (int e = 0; e < 4; ++e)
-                            dst[e] = static_cast<uint32_t>(bits[2 * e]) |
-                                     (static_cast<uint32_t>(bits[2 * e + 1]) << 16);
-                    } else {
-                        std::memcpy(dst, vals, 16);
-                    }
-                }
+        for (int h = 0; h < H; ++h) {
+            const int64_t row = static_cast<int64_t>(h) * D;
+            uint32_t *dst = pk.data() + (static_cast<size_t>(h >> 5) * 64 + (h & 31)) * 4;
+            for_row(g, g.Mp, g.CPR, g.epc, [&](int j, int kappa, int e) {
+                uint32_t *at = dst + (static_cast<size_t>(kappa >> 1) * g.HB * 64 + (kappa & 1) * 32) * 4;
+                if (bf)
+                    reinterpret_cast<uint16_t *>(at)[e] = static_cast<const uint16_t *>(w->w1)[row + j];
+                else
+                    std::memcpy(at + e, static_cast<const float *>(w->w1) + row + j, 4);
+            });
+        }
         st = dev_upload(&d->w1p, pk.data(), pk.size() * sizeof(uint32_t));
         if (st == ENOVA_OK) {
             hipError_t e = prepare_score_mfma(g);
@@ -836,6 +916,12 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
         }
         if (st == ENOVA_OK && g.ring)
             st = pack_ring(d, w);
+        if (st == ENOVA_OK) {
+            d->sg = plan_split(g);
+            d->sg.ok = d->sg.ok && score_list_lds(g) <= kLdsLimit && split_weights_ok(g, w);
+            if (d->sg.ok)
+                st = pack_split(d, w);
+        }
         if (st == ENOVA_OK && stream_score_supported(g))
             st = pack_stream(d, w);
         if (st == ENOVA_OK && ext_fused_supported(g))
@@ -963,15 +1049,25 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         return fail(ENOVA_EINVAL, "NULL argument");
     const bool want_flags = out_flags != nullptr && !std::isnan(threshold);
     const Geometry &g = det->g;
-    const int64_t grid = det->kind == 2 ? (n_windows + g.Nb - 1) / g.Nb + n : 0;
+    // windows per tile: the split kernel's where it applies, unless its smaller tiles need more
+    // blocks or workspace than a call may have
+    bool split = det->kind == 2 && det->sg.ok;
+    int nb = split ? det->sg.nb(n_windows, n) : g.Nb;
+    int64_t grid = det->kind == 2 ? (n_windows + nb - 1) / nb + n : 0;
+    size_t o_tiles = 0, o_map = 0, o_part = 0;
+    size_t need = noalloc ? noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part) : 0;
+    if (split && (grid > 0x7fffffffLL || need > kScratchBytes)) {
+        split = false;
+        nb = g.Nb;
+        grid = (n_windows + nb - 1) / nb + n;
+        need = noalloc ? noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part) : 0;
+    }
     if (grid > 0x7fffffffLL)
         return fail(ENOVA_EUNSUPPORTED, "too many tiles (%lld)", static_cast<long long>(grid));
     if (det->kind != 2 && (n_windows + 15) / 16 > 0x7fffffffLL)
         return fail(ENOVA_EUNSUPPORTED, "too many windows");
     ScoreWork wk;
     if (noalloc) {
-        size_t o_tiles = 0, o_map = 0, o_part = 0;
-        const size_t need = noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part);
         if (need > kScratchBytes)
             return fail(ENOVA_ESHAPE,
                         "the allocation-free call needs %zu bytes of device scratch for %d streams and %lld "
@@ -1022,7 +1118,7 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     if (timing && own)
         (void)hipEventRecord(det->ev[0], stream);
     if (det->kind == 2) {
-        e = launch_prep_scan(g, x, soff, woff, n, g.Nb, wk.tiles, own_mean, own_std, wk.part, stream);
+        e = launch_prep_scan(g, x, soff, woff, n, nb, wk.tiles, own_mean, own_std, wk.part, stream);
         if (e != hipSuccess)
             return hip_fail(e, "tile scan and reference statistics kernels");
     } else if (own) {
@@ -1057,6 +1153,10 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     p.w1r = det->w1r;
     p.whr = det->whr;
     p.wdr = det->wdr;
+    p.w1x = det->w1x;
+    p.whx = det->whx;
+    p.wdx = det->wdx;
+    p.w1scale = det->w1scale;
     p.sum_bd2 = det->sum_bd2;
     p.threshold = threshold;
     p.write_flags = want_flags ? 1 : 0;
@@ -1071,7 +1171,13 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         p.tile_stream = wk.tile_map;
         if (timing)
             (void)hipEventRecord(det->ev[2], stream);
-        e = g.ring ? launch_score_ring(g, p, grid, stream) : launch_score_mfma(g, p, grid, stream);
+        if (split) {
+            e = launch_score_split(g, det->sg, p, nb, grid, stream);
+            if (e == hipSuccess)
+                e = launch_score_list(g, p, nb, grid, stream);
+        } else {
+            e = g.ring ? launch_score_ring(g, p, grid, stream) : launch_score_mfma(g, p, grid, stream);
+        }
     } else {
         if (timing)
             (void)hipEventRecord(det->ev[2], stream);

@@ -106,7 +106,8 @@ struct ScoreParams {
     const int64_t *soff;
     const int64_t *woff;
     const int64_t *tile_off;     // matrix-core kernel only: first tile of each stream
-    const int *tile_stream;      // matrix-core kernel only: stream of each block (-1: none)
+    int *tile_stream;            // matrix-core kernel only: stream of each block (-1: none; the split
+                                 // kernel marks tiles it leaves windows of to the fp32 kernel)
     int n_streams;
     int64_t n_windows;
     const float *mean;
@@ -129,6 +130,13 @@ struct ScoreParams {
     const uint4 *w1r;
     const uint4 *whr;
     const uint2 *wdr;
+    // split kernel: W1 as f16 hi/lo 32x32x16 A fragments [steps + 2][HB][hi, lo][64 lanes], the heads
+    // [HB][2][3][64] and the decoder hidden layer [HB][3][64] as bf16 parts, and each hidden row's
+    // accumulator scale [Hp]
+    const uint4 *w1x;
+    const uint4 *whx;
+    const uint4 *wdx;
+    const float *w1scale;
     float sum_bd2;
     float threshold;
     int write_flags;
@@ -137,7 +145,33 @@ struct ScoreParams {
     uint8_t *flags;
 };
 
+// Geometry of the split-precision kernel (k_score_split.hip; fp32 detectors): super-rows of 8-element
+// chunks, each as an f16 hi and lo chunk in LDS; a large and a small tile of windows.
+struct SplitGeometry {
+    bool ok = false;
+    int Mp = 0, Q = 0, CPR = 0, P = 0, nsteps = 0, spare = 0;
+    int nb_small = 0, nb_large = 0;
+    size_t lds_small = 0, lds_large = 0;
+    int nb(int64_t n_windows, int n_streams) const
+    {
+        // the large tile once it gives two blocks to every compute unit and the streams fill it
+        // at least by half (the padding of a stream's last tile is computed)
+        const bool large = n_windows >= 512LL * nb_large && n_windows >= static_cast<int64_t>(n_streams) * (nb_large / 2);
+        return large ? nb_large : nb_small;
+    }
+};
+constexpr int kSplitPrefetch = 2;   // zero steps after the last one in w1x
+
 // Launchers (return the launch error).
+SplitGeometry plan_split(const Geometry &g);
+hipError_t prepare_score_split(const Geometry &g, const SplitGeometry &sg);
+hipError_t launch_score_split(const Geometry &g, const SplitGeometry &sg, const ScoreParams &p, int nb, int64_t grid,
+                              hipStream_t st);
+// The fp32 kernel over the tiles (of nb windows) that the split kernel marked, writing only their
+// windows outside the split's range; score_list_lds is its dynamic LDS.
+size_t score_list_lds(const Geometry &g);
+hipError_t prepare_score_list(const Geometry &g);
+hipError_t launch_score_list(const Geometry &g, const ScoreParams &p, int nb, int64_t grid, hipStream_t st);
 // part: stat_part_bytes(n, M) bytes for chunk sums (then about 2048 blocks share the streams), or
 // NULL (one block per stream); the statistics are bit for bit the same.
 size_t stat_part_bytes(int n, int M);

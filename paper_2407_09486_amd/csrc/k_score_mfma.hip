@@ -18,16 +18,35 @@
 
 #include "internal.h"
 #include "mfma_common.h"
+#include "split.h"
 
 namespace enova {
 
 namespace {
+
+// Largest scaled |v| of a row's elements, as k_score_split forms it.
+template <int N>
+__device__ __forceinline__ void row_max(unsigned *rm, const float (&x)[N], const float *mu, const float *ri)
+{
+    float big = 0.0f;
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const float a = fabsf((x[e] - mu[e]) * (ri[e] * kSplitScale));
+        const bool out = !(a <= kSplitMax);
+        bad |= out;
+        big = fmaxf(big, out ? 0.0f : a);
+    }
+    atomicMax(rm, bad ? 0x7f800000u : __float_as_uint(big));
+}
 
 struct MfmaShape {
     int M, S, W, Mp, Q, CPR, CPRP, KC;
     int spare;       // staged super-rows after a tile's last window's Q - 1
     int tail_rows;   // steps of the window's last super-row that belong to the window
     float inv_d;
+    int64_t list_grid;   // list mode: entries of the tile map, and windows of a marked tile
+    int list_nb;
 };
 
 // Wave layout: the NW waves form WH groups along the hidden rows and NW/WH groups along the
@@ -36,9 +55,10 @@ struct MfmaShape {
 // through LDS.
 // CL: the epilogue weights are copied into LDS with each tile (else read from L2, leaving the
 // LDS to a larger segment).
-template <int DT, int HB, int NBW, int WH, int NW, int ACT, bool CL>
-__global__ __launch_bounds__(NW * 64, (NW == 4 && ACT == ENOVA_RELU && WH == 1) ? 2 : 1)
-void k_score_mfma(ScoreParams p, MfmaShape g)
+// LIST: the tile is one that k_score_split marked; only its windows outside the split's range are
+// written (see split.h).
+template <int DT, int HB, int NBW, int WH, int NW, int ACT, bool CL, bool LIST>
+__device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const MfmaShape &g, int s, int64_t k0, int nv)
 {
     constexpr int NT = NW * 64;                   // threads of the block
     constexpr int WN = NW / WH;                   // window groups
@@ -54,14 +74,6 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
     const int wh = wave % WH;                     // hidden-row group of this wave
     const int wn = wave / WH;                     // window group of this wave
 
-    // ---- tile -> (stream, first window)
-    const int64_t b = blockIdx.x;
-    const int s = p.tile_stream[b];
-    if (s < 0)
-        return;
-    const int64_t k0 = (b - p.tile_off[s]) * NB;
-    const int64_t ns = p.woff[s + 1] - p.woff[s];
-    const int nv = static_cast<int>(ns - k0 < NB ? ns - k0 : NB);
     const int64_t srow = p.soff[s];
     const int64_t T = p.soff[s + 1] - srow;
 
@@ -97,6 +109,11 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
     float *s_bd1 = s_b1 + HP;
     float *s_u = s_bd1 + HP;
     float *s_bh = s_u + HP;
+    // list mode: the largest scaled |v| of each staged row
+    unsigned *rm = reinterpret_cast<unsigned *>(CL ? ps + rows_alloc : s_bh + 32);
+    if constexpr (LIST)
+        for (int r = tid; r < nrows; r += NT)
+            rm[r] = 0u;
 
     if constexpr (CL) {
         // the host lays the epilogue weights out contiguously in this LDS order; copy them with
@@ -200,6 +217,8 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
                     v[6] = bf16_lo(raw[u].w);
                     v[7] = bf16_hi(raw[u].w);
                 }
+                if constexpr (LIST)
+                    row_max(rm + r, v, mu, ri);
 #pragma unroll
                 for (int e = 0; e < EPC; ++e)
                     v[e] = (v[e] - mu[e]) * ri[e];
@@ -210,8 +229,12 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
                 for (int e = 0; e < EPC; ++e) {
                     const int off = coff[c * EPC + e];
                     float val = 0.0f;
-                    if (off >= 0 && rel + off < eavail)
-                        val = (load_x<DT>(p.x, ebase + rel + off) - mu[e]) * ri[e];
+                    if (off >= 0 && rel + off < eavail) {
+                        const float raw1[1] = {load_x<DT>(p.x, ebase + rel + off)};
+                        if constexpr (LIST)
+                            row_max(rm + r, raw1, mu + e, ri + e);
+                        val = (raw1[0] - mu[e]) * ri[e];
+                    }
                     v[e] = val;
                 }
             }
@@ -425,7 +448,14 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
         if (((Q - 1) & 1) == half)
             vsum += ps[row0 + Q - 1];
         vsum += __shfl_xor(vsum, 32);
-        if (storer && half == 0 && n < nv) {
+        bool mine = true;
+        if constexpr (LIST) {
+            unsigned wm = 0u;
+            for (int qq = 0; qq < Q; ++qq)
+                wm = max(wm, rm[row0 + qq]);
+            mine = split_outside(wm);
+        }
+        if (storer && half == 0 && n < nv && mine) {
             const int64_t w = p.woff[s] + k0 + n;
             p.scores[w] = sc;
             if (p.md)
@@ -436,7 +466,63 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
     });
 }
 
+template <int DT, int HB, int NBW, int WH, int NW, int ACT, bool CL>
+__global__ __launch_bounds__(NW * 64, (NW == 4 && ACT == ENOVA_RELU && WH == 1) ? 2 : 1)
+void k_score_mfma(ScoreParams p, MfmaShape g)
+{
+    constexpr int NB = NW / WH * NBW * 32;
+    const int64_t b = blockIdx.x;
+    const int s = p.tile_stream[b];
+    if (s < 0)
+        return;
+    const int64_t k0 = (b - p.tile_off[s]) * NB;
+    const int64_t ns = p.woff[s + 1] - p.woff[s];
+    const int nv = static_cast<int>(ns - k0 < NB ? ns - k0 : NB);
+    score_mfma_tile<DT, HB, NBW, WH, NW, ACT, CL, false>(p, g, s, k0, nv);
+}
+
+// The tiles that k_score_split marked (of list_nb <= NB windows each). A block looks through the
+// entries blockIdx.x, blockIdx.x + gridDim.x, ... of the tile map, 256 at a time, so neighbouring
+// marked tiles go to different blocks; without a mark the kernel costs its launch and one load.
+template <int HB, int NBW, int ACT>
+__global__ __launch_bounds__(256, 1) void k_score_mfma_list(ScoreParams p, MfmaShape g)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t step = gridDim.x;
+    for (int64_t first = blockIdx.x; first < g.list_grid; first += 256 * step) {
+        uint64_t mask[4];   // the same in every wave
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = first + (q * 64 + lane) * step;
+            mask[q] = __ballot(i < g.list_grid && split_marked(p.tile_stream[i]) >= 0);
+        }
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q)
+            for (uint64_t m = mask[q]; m; m &= m - 1) {
+                const int64_t b = first + (q * 64 + __builtin_ctzll(m)) * step;
+                const int s = split_marked(p.tile_stream[b]);
+                const int64_t k0 = (b - p.tile_off[s]) * g.list_nb;
+                const int64_t ns = p.woff[s + 1] - p.woff[s];
+                const int nv = static_cast<int>(ns - k0 < g.list_nb ? ns - k0 : g.list_nb);
+                score_mfma_tile<ENOVA_F32, HB, NBW, 1, 4, ACT, true, true>(p, g, s, k0, nv);
+                __syncthreads();   // the tile's LDS is written again
+            }
+    }
+}
+
 using ScoreKernel = void (*)(ScoreParams, MfmaShape);
+
+template <int ACT>
+ScoreKernel pick_list(int hb)
+{
+    switch (hb) {
+    case 1: return k_score_mfma_list<1, 4, ACT>;
+    case 2: return k_score_mfma_list<2, 4, ACT>;
+    case 4: return k_score_mfma_list<4, 2, ACT>;
+    case 8: return k_score_mfma_list<8, 1, ACT>;
+    default: return nullptr;
+    }
+}
 
 template <int DT, int ACT>
 ScoreKernel pick_layout(int hbw, int nbw, int wh, int nw, bool cl)
@@ -474,6 +560,57 @@ ScoreKernel pick(const Geometry &g)
 
 }  // namespace
 
+static MfmaShape shape_of(const Geometry &g)
+{
+    MfmaShape sh{};
+    sh.M = g.M;
+    sh.S = g.S;
+    sh.W = g.W;
+    sh.Mp = g.Mp;
+    sh.Q = g.Q;
+    sh.CPR = g.CPR;
+    sh.CPRP = g.CPRP;
+    sh.KC = g.KC;
+    sh.spare = g.spare;
+    sh.tail_rows = g.W - (g.Q - 1) * g.S;
+    sh.inv_d = 1.0f / static_cast<float>(g.D);
+    return sh;
+}
+
+static ScoreKernel pick_list(const Geometry &g)
+{
+    return g.act == ENOVA_RELU ? pick_list<ENOVA_RELU>(g.HB) : pick_list<ENOVA_TANH>(g.HB);
+}
+
+size_t score_list_lds(const Geometry &g)
+{
+    return g.lds_bytes + sizeof(unsigned) * static_cast<size_t>(g.Nb + g.Q - 1 + g.spare);
+}
+
+hipError_t prepare_score_list(const Geometry &g)
+{
+    ScoreKernel k = pick_list(g);
+    if (!k)
+        return hipErrorInvalidValue;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(score_list_lds(g)));
+}
+
+hipError_t launch_score_list(const Geometry &g, const ScoreParams &p, int nb, int64_t grid, hipStream_t st)
+{
+    if (grid <= 0)
+        return hipSuccess;
+    ScoreKernel k = pick_list(g);
+    if (!k || nb > g.Nb)
+        return hipErrorInvalidValue;
+    MfmaShape sh = shape_of(g);
+    sh.list_grid = grid;
+    sh.list_nb = nb;
+    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid < 512 ? grid : 512)), dim3(256), score_list_lds(g), st, p,
+                       sh);
+    return hipGetLastError();
+}
+
 // Allow the chosen instantiation the full 160 KiB of LDS.
 hipError_t prepare_score_mfma(const Geometry &g)
 {
@@ -491,18 +628,7 @@ hipError_t launch_score_mfma(const Geometry &g, const ScoreParams &p, int64_t gr
     ScoreKernel k = pick(g);
     if (!k)
         return hipErrorInvalidValue;
-    MfmaShape sh;
-    sh.M = g.M;
-    sh.S = g.S;
-    sh.W = g.W;
-    sh.Mp = g.Mp;
-    sh.Q = g.Q;
-    sh.CPR = g.CPR;
-    sh.CPRP = g.CPRP;
-    sh.KC = g.KC;
-    sh.spare = g.spare;
-    sh.tail_rows = g.W - (g.Q - 1) * g.S;
-    sh.inv_d = 1.0f / static_cast<float>(g.D);
+    const MfmaShape sh = shape_of(g);
     hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(64 * g.NW), g.lds_bytes, st, p, sh);
     return hipGetLastError();
 }

@@ -1,0 +1,112 @@
+"""The split-precision scoring kernel (fp32 detectors): tile edges, both tile sizes, odd geometries and
+the range its 16-bit parts hold, against the fp64 oracle, and the windows outside that range against the
+vector kernel. Two fp32 sums of D products in different order differ by about sqrt(D) 2^-24 of the
+score's scale; the tests allow 2e-6 (D <= 1024)."""
+import numpy as np
+import pytest
+
+import oracle
+from harness import check_md, check_scores, detector, gpu_score, log, oracle_score
+from paper_2407_09486_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(M, W, S, H, L=16, act="relu", n=1):
+    return wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, latent=L, act=act, n_streams=n)
+
+
+def _check(cfg, w, weights, what):
+    det = detector(cfg, weights)
+    sc, md, _, _ = gpu_score(det, w, pad=32)
+    o_sc, o_md, info = oracle_score(cfg, w, weights)
+    scale = float(np.sqrt(np.mean(o_sc ** 2)))
+    assert np.linalg.norm(sc - o_sc) <= 2e-6 * np.linalg.norm(o_sc), what
+    assert np.max(np.abs(sc - o_sc)) <= 2e-5 * scale + 2e-5 * np.max(np.abs(o_sc)), what
+    check_scores(sc, o_sc, "f32", what)
+    check_md(md, o_md, info["md_scale"], "f32", what)
+    det.close()
+
+
+# chunk counts of a super-row of 1 (two rows a step), 2, 3 (odd), padded metrics, strides, S > W;
+# windows around the tiles' 64, 128, 256 and 512; hidden layers of one to eight 32-row blocks
+@pytest.mark.parametrize("M,W,S,H,act", [(8, 6, 1, 32, "relu"), (7, 9, 1, 64, "tanh"), (16, 5, 1, 100, "relu"),
+                                         (3, 4, 8, 33, "relu"), (24, 3, 1, 200, "tanh"), (4, 11, 2, 256, "relu"),
+                                         (5, 16, 3, 128, "tanh"), (32, 2, 5, 8, "relu")])
+def test_tile_edges(M, W, S, H, act):
+    counts = [1, 31, 33, 64, 65, 128, 129, 257, 512, 513]
+    lengths = [W + (k - 1) * S for k in counts] + [W - 1, 0, W + 300 * S + S - 1]
+    cfg = _cfg(M, W, S, H, act=act, n=len(lengths))
+    log(f"[split] edges M={M} W={W} S={S} H={H} {act}")
+    rng = np.random.default_rng(5)
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    w = wl.from_arrays(cfg, rng.standard_normal((int(offs[-1]), M)) * 3 + 1, offs)
+    _check(cfg, w, wl.make_weights(cfg, bias_scale=0.1), f"{M} {W} {S} {H}")
+
+
+@pytest.mark.parametrize("H", [32, 64, 128, 256])
+def test_large_tiles(H):
+    """Enough windows for the large tile of each hidden width."""
+    cfg = _cfg(2, 4, 1, H, n=2)
+    n = {32: 262200, 64: 262200, 128: 131200, 256: 65700}[H]
+    log(f"[split] large tiles H={H}, {n} windows")
+    rng = np.random.default_rng(H)
+    offs = np.array([0, n // 2 + 17, n + 40], np.int64)
+    w = wl.from_arrays(cfg, rng.standard_normal((n + 40, 2)), offs)
+    _check(cfg, w, wl.make_weights(cfg, bias_scale=0.1), f"large {H}")
+
+
+@pytest.mark.parametrize("H", [32, 128, 256])
+def test_windows_outside_the_range(H):
+    """Spikes beyond the f16 range, infinities, NaN and nearly constant stretches: the windows that hold
+    them agree with the vector kernel, and every window is bitwise what its stream gives alone."""
+    cfg = _cfg(7, 20, 1, H, n=3)
+    rng = np.random.default_rng(9)
+    lengths = [900, 2500, 700]
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    x = rng.standard_normal((int(offs[-1]), 7)).astype(np.float32)
+    x[offs[0] + 600, 2] = 1e6
+    x[offs[0] + 800, 0] = -3e38
+    x[offs[1] + 1400:offs[1] + 1460] = x[offs[1]:offs[1] + 1250].mean(0) + 1e-4     # nearly constant
+    x[offs[1] + 1700, 3] = np.inf
+    x[offs[1] + 1900, 6] = np.nan
+    x[offs[1] + 2100, 1] = 4001.0                                                  # about the limit
+    x[offs[2]:] = 5.0                                                              # constant: scores of v = 0
+    w = wl.from_arrays(cfg, x, offs)
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    log(f"[split] range H={H}")
+    det, ref = detector(cfg, weights), detector(cfg, weights, "valu")
+    (sc, md, _, woff), (rsc, rmd, _, _) = gpu_score(det, w, pad=16), gpu_score(ref, w)
+    fin = np.isfinite(rsc) & (np.abs(rsc) < 1e30)
+    assert np.array_equal(np.isnan(sc), np.isnan(rsc)) and np.array_equal(np.isinf(sc), np.isinf(rsc))
+    np.testing.assert_allclose(sc[fin], rsc[fin], rtol=1e-5, atol=1e-6)
+    ok = np.isfinite(rmd) & (np.abs(rmd) < 1e30)
+    np.testing.assert_allclose(md[ok], rmd[ok], rtol=1e-5, atol=2e-6)
+    for i in range(3):
+        one = wl.from_arrays(cfg, x[offs[i]:offs[i + 1]], np.array([0, lengths[i]]))
+        a, b, _, _ = gpu_score(det, one)
+        assert np.array_equal(a, sc[woff[i]:woff[i + 1]], equal_nan=True)
+        assert np.array_equal(b, md[woff[i]:woff[i + 1]], equal_nan=True)
+    det.close()
+    ref.close()
+
+
+def test_weight_scales():
+    """Hidden rows of very different scale keep their precision (each row has its own power of two); rows
+    of zeros; a weight outside the supported range falls back to the fp32 kernel."""
+    cfg = _cfg(8, 16, 1, 64, n=1)
+    rng = np.random.default_rng(2)
+    w = wl.from_arrays(cfg, rng.standard_normal((1500, 8)), np.array([0, 1500]))
+    weights = wl.make_weights(cfg, bias_scale=0.05)
+    scale = np.exp2(rng.integers(-30, 6, 64)).astype(np.float32)
+    scale[:3] = 0.0
+    weights.w1[:] *= scale[:, None]
+    weights.wmu[:] /= np.maximum(scale, 2.0 ** -10)[None, :]
+    log("[split] weight scales")
+    _check(cfg, w, weights, "row scales")
+    weights.w1[5, 7] = 2e6
+    det, ref = detector(cfg, weights), detector(cfg, weights, "valu")
+    sc, rsc = gpu_score(det, w)[0], gpu_score(ref, w)[0]
+    np.testing.assert_allclose(sc, rsc, rtol=1e-5)
+    det.close()
+    ref.close()
