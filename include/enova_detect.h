@@ -303,9 +303,9 @@ enova_status enova_train_init(const enova_train_config *config, const enova_dete
  *   eps       device [B][L] float: the reparameterisation noise
  *   out_info  device [4] float or NULL: J, mean log p, mean KL of the normal windows, beta(k)
  * Asynchronous on `stream`. The step's launches are captured once into a HIP graph (on a stream
- * of the trainer's own) and the graph is replayed while V, labels, eps, out_info and the batch
- * size stay the same (the contents may change between steps); any other arguments capture it
- * again, which first waits for the device. Steps taken with timing on, or with graph replay
+ * of the trainer's own), and the graph is replayed for every batch of the same size and alignment
+ * of V (whether on a 16-byte boundary), whatever its buffers; the last four such graphs are kept,
+ * and capturing another first waits for the device. Steps taken with timing on, or with graph replay
  * off, launch their kernels one by one on `stream`; a caller that captures the step into a
  * graph of its own turns replay off. Errors: EINVAL, ENOMEM, EHIP.
  */

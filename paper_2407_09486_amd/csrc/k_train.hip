@@ -134,6 +134,7 @@ struct EpiParams {
     const float *pre;    // kEpiDact; kEpiRowReduce: the minuend, leading dimension ldv
     float *sq;           // kEpiRowReduce: sums of squares
     int ldv, groups;     // kEpiRowReduce
+    const float *const *aind, *const *bind;   // GemmEpilogue
 };
 
 template <int ACT>
@@ -218,6 +219,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm(const float *__restrict__ A, in
     static_assert(MA >= 1 && MB >= 1 && WM * WN == 4, "tile shape");
     __shared__ __align__(16) float As[2][stage_floats(TM, AK)];
     __shared__ __align__(16) float Bs[2][stage_floats(TN, BK)];
+    if (ep.aind)
+        A = *ep.aind;
+    if (ep.bind)
+        B = *ep.bind;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -491,6 +496,10 @@ __global__ __launch_bounds__(64 * kRsWaves) void k_gemm_rs(const float *__restri
     const int iters = kc / (kRsStep * WK);
     C += static_cast<int64_t>(blockIdx.z) * m * ldc;
 
+    if (ep.aind)
+        A = *ep.aind;
+    if (ep.bind)
+        B = *ep.bind;
     // per-lane bases of iteration 0 and the stride between iterations
     const float *ab = AK ? A + static_cast<int64_t>(i0 + p) * lda + kw + 4 * g
                          : A + static_cast<int64_t>(kw + 4 * g) * lda + i0 + 4 * p;
@@ -649,9 +658,10 @@ __global__ __launch_bounds__(256) void k_sum_splits(const float *__restrict__ P,
 // One thread per window. ml holds [mu | lv] per window (2L floats, biases [bmu | blv] added in
 // place); sd = e^(lv/2), z = mu + sd eps and the KL of q(z|m) from N(0, I).
 __global__ __launch_bounds__(64) void k_latent(float *__restrict__ ml, const float *__restrict__ bml,
-                                               const float *__restrict__ eps, float *__restrict__ sd,
+                                               const StepArgs *__restrict__ sa, float *__restrict__ sd,
                                                float *__restrict__ z, float *__restrict__ kl, int rows, int L)
 {
+    const float *__restrict__ eps = sa->eps;
     const int i = blockIdx.x * 64 + threadIdx.x;
     if (i >= rows)
         return;
@@ -674,9 +684,10 @@ __global__ __launch_bounds__(64) void k_latent(float *__restrict__ ml, const flo
 // The same with one thread per (window, latent index) when L is a power of two <= 64: coalesced
 // accesses, and the window's KL summed over its L lanes by a butterfly.
 __global__ __launch_bounds__(256) void k_latent_lanes(float *__restrict__ ml, const float *__restrict__ bml,
-                                                      const float *__restrict__ eps, float *__restrict__ sd,
+                                                      const StepArgs *__restrict__ sa, float *__restrict__ sd,
                                                       float *__restrict__ z, float *__restrict__ kl, int rows, int L)
 {
+    const float *__restrict__ eps = sa->eps;
     const int64_t t = blockIdx.x * 256LL + threadIdx.x;
     const int64_t i = t / L;
     const int l = static_cast<int>(t - i * L);
@@ -704,10 +715,11 @@ __global__ __launch_bounds__(256) void k_latent_lanes(float *__restrict__ ml, co
 // wave, and no LDS or barrier is involved. Same outputs as k_recon.
 template <int Q>
 __global__ __launch_bounds__(256) void k_recon_wave(float *__restrict__ out, const float *__restrict__ bd2,
-                                                    const float *__restrict__ V, const float *__restrict__ labels,
+                                                    const StepArgs *__restrict__ sa,
                                                     float *__restrict__ logp, int rows, int D, float inv_b,
                                                     float margin)
 {
+    const float *__restrict__ V = sa->V, *__restrict__ labels = sa->labels;
     const int lane = threadIdx.x & 63;
     const int64_t row = blockIdx.x * 4LL + (threadIdx.x >> 6);
     if (row >= rows)
@@ -752,9 +764,10 @@ __global__ __launch_bounds__(256) void k_recon_wave(float *__restrict__ out, con
 // differences stay in registers between the reduction and the write; PER = 0 recomputes them.
 template <int PER>
 __global__ __launch_bounds__(256) void k_recon(float *__restrict__ out, const float *__restrict__ bd2,
-                                               const float *__restrict__ V, const float *__restrict__ labels,
+                                               const StepArgs *__restrict__ sa,
                                                float *__restrict__ logp, int D, float inv_b, float margin)
 {
+    const float *__restrict__ V = sa->V, *__restrict__ labels = sa->labels;
     __shared__ float red[256];
     const int64_t row = blockIdx.x;
     const float l = labels[row];
@@ -805,13 +818,15 @@ __global__ __launch_bounds__(256) void k_recon(float *__restrict__ out, const fl
 // It also advances the Adam step count k (held on the device, so a step's launches carry no
 // per-step host value) and writes the bias corrections 1/(1 - b1^k), 1/(1 - b2^k) to corr.
 __global__ __launch_bounds__(1024) void k_beta(const float *__restrict__ kl, const float *__restrict__ logp,
-                                              const float *__restrict__ labels, int rows, float kl_set,
+                                              const StepArgs *__restrict__ sa, int rows, float kl_set,
                                               float kp, float ki, float beta_min, float beta_max,
                                               float margin, float half_d_log2pi,
                                               float *__restrict__ st, float *__restrict__ beta_out,
-                                              float *__restrict__ info, float b1, float b2,
+                                              float b1, float b2,
                                               long long *__restrict__ step, float *__restrict__ corr)
 {
+    const float *__restrict__ labels = sa->labels;
+    float *__restrict__ info = sa->info;
     // per thread (fixed stride), per wave (butterfly), then the 16 wave sums in wave order
     __shared__ double r[5][16];
     double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // KL of normal windows, their count, log p, J terms, KL terms
@@ -893,9 +908,10 @@ __global__ __launch_bounds__(1024) void k_beta(const float *__restrict__ kl, con
 // c = (1 + l)/2 beta / B, written as [g_mu | g_lv] per window (the layout of ml).
 __global__ __launch_bounds__(256) void k_latent_grad(const float *__restrict__ gz, float *__restrict__ gml,
                                                      const float *__restrict__ ml, const float *__restrict__ sd,
-                                                     const float *__restrict__ eps, const float *__restrict__ labels,
+                                                     const StepArgs *__restrict__ sa,
                                                      const float *__restrict__ beta, int rows, int L, float inv_b)
 {
+    const float *__restrict__ eps = sa->eps, *__restrict__ labels = sa->labels;
     const int64_t total = static_cast<int64_t>(rows) * L;
     const float b = beta[0];
     for (int64_t e = blockIdx.x * 256LL + threadIdx.x; e < total; e += static_cast<int64_t>(gridDim.x) * 256) {
@@ -1119,7 +1135,8 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
     if (epi.kind == kEpiRowReduce &&
         (epi.groups < 1 || epi.groups > 32 || (epi.groups & (epi.groups - 1)) != 0 || !epi.sq || !epi.out2))
         return hipErrorInvalidValue;
-    const EpiParams epp{epi.bias, epi.out2, epi.pre, epi.sq, epi.ldv, epi.groups};
+    const EpiParams epp{epi.bias, epi.out2, epi.pre, epi.sq, epi.ldv, epi.groups, epi.aind, epi.bind};
+    const EpiParams ind{nullptr, nullptr, nullptr, nullptr, 0, 0, epi.aind, epi.bind};   // of split slices
     {
         // whole tiles with aligned operands: the register-streamed kernel
         const bool epi_rs = epi.kind == kEpiStore || epi.kind == kEpiBiasAct || epi.kind == kEpiDact;
@@ -1140,7 +1157,7 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
             }
             float *part_rows = rowsum ? work + static_cast<int64_t>(rp.used) * m * n : nullptr;
             rs_layouts<kEpiStore, ENOVA_RELU>(rp.kind, a_k, b_k, rgrid, st, A, lda, B, ldb, work,
-                                              static_cast<int64_t>(n), part_rows, EpiParams{}, m, rp.kc);
+                                              static_cast<int64_t>(n), part_rows, ind, m, rp.kc);
             if ((e = hipGetLastError()) != hipSuccess)
                 return e;
             if (ev1 && (e = hipEventRecord(ev1, st)) != hipSuccess)
@@ -1173,7 +1190,7 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
     // partial tiles, then one pass that sums them in slice order and applies the epilogue
     float *part_rows = rowsum ? work + static_cast<int64_t>(used) * m * n : nullptr;
     gemm_layouts<kEpiStore, ENOVA_RELU>(a_k, b_k, grid, st, A, lda, va, B, ldb, vb, work, static_cast<int64_t>(n),
-                                        part_rows, EpiParams{}, m, n, k, kc);
+                                        part_rows, ind, m, n, k, kc);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (ev1 && (e = hipEventRecord(ev1, st)) != hipSuccess)
@@ -1188,70 +1205,80 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
     return hipGetLastError();
 }
 
-hipError_t launch_latent(float *ml, const float *bml, const float *eps, float *sd, float *z, float *kl, int rows,
+namespace {
+__global__ void k_step_args(StepArgs *dst, StepArgs args) { *dst = args; }
+}  // namespace
+
+hipError_t launch_step_args(StepArgs *dst, const StepArgs &args, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_step_args, dim3(1), dim3(1), 0, st, dst, args);
+    return hipGetLastError();
+}
+
+hipError_t launch_latent(float *ml, const float *bml, const StepArgs *sa, float *sd, float *z, float *kl, int rows,
                          int L, hipStream_t st)
 {
     if (L <= 64 && (L & (L - 1)) == 0) {
         const int64_t threads = static_cast<int64_t>(rows) * L;
         hipLaunchKernelGGL(k_latent_lanes, dim3(static_cast<unsigned>((threads + 255) / 256)), dim3(256), 0, st, ml, bml,
-                           eps, sd, z, kl, rows, L);
+                           sa, sd, z, kl, rows, L);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_latent, dim3(static_cast<unsigned>((rows + 63) / 64)), dim3(64), 0, st, ml, bml, eps, sd, z,
+    hipLaunchKernelGGL(k_latent, dim3(static_cast<unsigned>((rows + 63) / 64)), dim3(64), 0, st, ml, bml, sa, sd, z,
                        kl, rows, L);
     return hipGetLastError();
 }
 
-hipError_t launch_recon(float *out, const float *bd2, const float *V, const float *labels, float *logp,
+hipError_t launch_recon(float *out, const float *bd2, const StepArgs *sa, bool aligned, float *logp,
                         int rows, int D, float margin, hipStream_t st)
 {
     const float inv_b = 1.0f / static_cast<float>(rows);
     const bool vec = D % 4 == 0 && D <= 2048 && reinterpret_cast<uintptr_t>(out) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(V) % 16 == 0 && reinterpret_cast<uintptr_t>(bd2) % 16 == 0;
+                     aligned && reinterpret_cast<uintptr_t>(bd2) % 16 == 0;
     if (vec) {
         const dim3 wgrid(static_cast<unsigned>((rows + 3) / 4));
         const int q = (D + 255) / 256;
         switch (q) {
-        case 1: hipLaunchKernelGGL(k_recon_wave<1>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 2: hipLaunchKernelGGL(k_recon_wave<2>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 3: hipLaunchKernelGGL(k_recon_wave<3>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 4: hipLaunchKernelGGL(k_recon_wave<4>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 5: hipLaunchKernelGGL(k_recon_wave<5>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 6: hipLaunchKernelGGL(k_recon_wave<6>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        case 7: hipLaunchKernelGGL(k_recon_wave<7>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
-        default: hipLaunchKernelGGL(k_recon_wave<8>, wgrid, dim3(256), 0, st, out, bd2, V, labels, logp, rows, D, inv_b, margin); break;
+        case 1: hipLaunchKernelGGL(k_recon_wave<1>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 2: hipLaunchKernelGGL(k_recon_wave<2>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 3: hipLaunchKernelGGL(k_recon_wave<3>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 4: hipLaunchKernelGGL(k_recon_wave<4>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 5: hipLaunchKernelGGL(k_recon_wave<5>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 6: hipLaunchKernelGGL(k_recon_wave<6>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        case 7: hipLaunchKernelGGL(k_recon_wave<7>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
+        default: hipLaunchKernelGGL(k_recon_wave<8>, wgrid, dim3(256), 0, st, out, bd2, sa, logp, rows, D, inv_b, margin); break;
         }
         return hipGetLastError();
     }
     const dim3 grid(static_cast<unsigned>(rows));
     if (D <= 256)
-        hipLaunchKernelGGL(k_recon<1>, grid, dim3(256), 0, st, out, bd2, V, labels, logp, D, inv_b, margin);
+        hipLaunchKernelGGL(k_recon<1>, grid, dim3(256), 0, st, out, bd2, sa, logp, D, inv_b, margin);
     else if (D <= 512)
-        hipLaunchKernelGGL(k_recon<2>, grid, dim3(256), 0, st, out, bd2, V, labels, logp, D, inv_b, margin);
+        hipLaunchKernelGGL(k_recon<2>, grid, dim3(256), 0, st, out, bd2, sa, logp, D, inv_b, margin);
     else if (D <= 1024)
-        hipLaunchKernelGGL(k_recon<4>, grid, dim3(256), 0, st, out, bd2, V, labels, logp, D, inv_b, margin);
+        hipLaunchKernelGGL(k_recon<4>, grid, dim3(256), 0, st, out, bd2, sa, logp, D, inv_b, margin);
     else if (D <= 2048)
-        hipLaunchKernelGGL(k_recon<8>, grid, dim3(256), 0, st, out, bd2, V, labels, logp, D, inv_b, margin);
+        hipLaunchKernelGGL(k_recon<8>, grid, dim3(256), 0, st, out, bd2, sa, logp, D, inv_b, margin);
     else
-        hipLaunchKernelGGL(k_recon<0>, grid, dim3(256), 0, st, out, bd2, V, labels, logp, D, inv_b, margin);
+        hipLaunchKernelGGL(k_recon<0>, grid, dim3(256), 0, st, out, bd2, sa, logp, D, inv_b, margin);
     return hipGetLastError();
 }
 
-hipError_t launch_beta(const float *kl, const float *logp, const float *labels, int rows, int D,
-                       const TrainHyper &h, float *state, float *beta, float *info, long long *step, float *corr,
+hipError_t launch_beta(const float *kl, const float *logp, const StepArgs *sa, int rows, int D,
+                       const TrainHyper &h, float *state, float *beta, long long *step, float *corr,
                        hipStream_t st)
 {
-    hipLaunchKernelGGL(k_beta, dim3(1), dim3(1024), 0, st, kl, logp, labels, rows, h.kl_set, h.kp, h.ki,
+    hipLaunchKernelGGL(k_beta, dim3(1), dim3(1024), 0, st, kl, logp, sa, rows, h.kl_set, h.kp, h.ki,
                        h.beta_min, h.beta_max, h.margin, 0.5f * static_cast<float>(D) * kLog2Pi, state, beta,
-                       info, h.b1, h.b2, step, corr);
+                       h.b1, h.b2, step, corr);
     return hipGetLastError();
 }
 
-hipError_t launch_latent_grad(const float *gz, float *gml, const float *ml, const float *sd, const float *eps,
-                              const float *labels, const float *beta, int rows, int L, hipStream_t st)
+hipError_t launch_latent_grad(const float *gz, float *gml, const float *ml, const float *sd,
+                              const StepArgs *sa, const float *beta, int rows, int L, hipStream_t st)
 {
     hipLaunchKernelGGL(k_latent_grad, dim3(blocks_for(static_cast<int64_t>(rows) * L)), dim3(256), 0, st, gz, gml,
-                       ml, sd, eps, labels, beta, rows, L, 1.0f / static_cast<float>(rows));
+                       ml, sd, sa, beta, rows, L, 1.0f / static_cast<float>(rows));
     return hipGetLastError();
 }
 

@@ -15,6 +15,13 @@ struct TrainHyper {
     float kl_set, kp, ki, beta_min, beta_max;
     float margin;   // cap of an anomalous window's reconstruction error (+inf: none)
 };
+// The caller's arrays of a step, read by its kernels from device memory: the captured launches then
+// serve any batch of the same size, with the pointers set by one small launch before the replay.
+struct StepArgs {
+    const float *V, *labels, *eps;
+    float *info;
+};
+hipError_t launch_step_args(StepArgs *dst, const StepArgs &args, hipStream_t st);
 // A long reduction over few output tiles is split into slices whose partial tiles go to `work`
 // (gemm_workspace_floats(m, n, k) floats, gemm_plan.h; NULL: no split) and are then summed in slice order.
 // rowsum (or NULL) receives sum_k A(i, k) for every i < m. The epilogue fuses the element-wise
@@ -36,6 +43,9 @@ struct GemmEpilogue {
     float *sq = nullptr;    // kEpiRowReduce
     int ldv = 0;            // kEpiRowReduce: leading dimension of pre
     int groups = 0;         // kEpiRowReduce
+    // operands read through a pointer in device memory (StepArgs::V) when not NULL: A or B then only
+    // says how that array is aligned
+    const float *const *aind = nullptr, *const *bind = nullptr;
 };
 // A split product's slice partials left for a later pass: part [splits][m][n] and rows
 // [splits][m] (NULL without row sums), in `work`; splits == 0 when the product did not split and
@@ -53,18 +63,19 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
                        int64_t work_floats, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
                        GemmSplit *defer = nullptr);
 // ml: [rows][2L] = [mu | lv] per window (biases bml = [bmu | blv] added in place).
-hipError_t launch_latent(float *ml, const float *bml, const float *eps, float *sd, float *z, float *kl, int rows,
+hipError_t launch_latent(float *ml, const float *bml, const StepArgs *sa, float *sd, float *z, float *kl, int rows,
                          int L, hipStream_t st);
-hipError_t launch_recon(float *out, const float *bd2, const float *V, const float *labels, float *logp,
+// aligned: V starts on a 16-byte boundary
+hipError_t launch_recon(float *out, const float *bd2, const StepArgs *sa, bool aligned, float *logp,
                         int rows, int D, float margin, hipStream_t st);
 // state[0] = the controller's integral term, beta = this step's KL weight; step = the Adam step
 // count (advanced here), corr [2] = its bias corrections for launch_adam.
-hipError_t launch_beta(const float *kl, const float *logp, const float *labels, int rows, int D,
-                       const TrainHyper &h, float *state, float *beta, float *info, long long *step, float *corr,
+hipError_t launch_beta(const float *kl, const float *logp, const StepArgs *sa, int rows, int D,
+                       const TrainHyper &h, float *state, float *beta, long long *step, float *corr,
                        hipStream_t st);
 // gz: [rows][L] = dJ/dz; gml: [rows][2L] = [dJ/dmu | dJ/dlv].
-hipError_t launch_latent_grad(const float *gz, float *gml, const float *ml, const float *sd, const float *eps,
-                              const float *labels, const float *beta, int rows, int L, hipStream_t st);
+hipError_t launch_latent_grad(const float *gz, float *gml, const float *ml, const float *sd,
+                              const StepArgs *sa, const float *beta, int rows, int L, hipStream_t st);
 // The gradient of the flat range [begin, begin + count) as the sum of a deferred product's slices:
 // g[begin + i] = sum over s = 0, 1, ..., splits - 1 (in order) of src[s * stride + i].
 struct GradSum {

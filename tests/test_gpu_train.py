@@ -319,3 +319,39 @@ def test_graph_replay_matches_eager_steps():
     assert np.array_equal(ia.cpu().numpy(), ib.cpu().numpy())
     ga.close()
     eb.close()
+
+
+@pytest.mark.parametrize("metrics,window", [(8, 32), (5, 7)])
+def test_replay_over_new_buffers_matches_eager_steps(metrics, window):
+    """Steps over slices of one data set (new pointers every step; with D = 35 the slices start on
+    different alignments) and over more batch sizes than graphs are kept: bit for bit the eager steps,
+    with unrelated work and a wait between replays."""
+    import torch
+    cfg = _cfg(metrics, window, 48, 8, "relu")
+    p0 = _init(cfg)
+    ga, eb = _trainer(cfg, p0), _trainer(cfg, p0)
+    eb.set_graph(False)
+    b = wl.training_batch(cfg, 2400, seed=77)
+    V, lab, eps = (_dev(a) for a in (b.V, b.labels, b.eps))
+    infos = torch.zeros(2, 40, 4, dtype=torch.float32, device="cuda")
+    junk = torch.randn(1 << 18, device="cuda")
+    sizes = [300, 300, 301, 300, 130, 300, 77, 300, 512, 33, 300, 130]
+    at = 0
+    for k, n in enumerate(sizes):
+        log(f"new buffers D={cfg.d} step {k} batch {n} at {at}")
+        if at + n > 2400:
+            at = 0
+        d = (V[at:at + n], lab[at:at + n], eps[at:at + n])
+        at += n
+        ga.step(*d, infos[0, k])
+        junk.mul_(0.5).add_(1.0)
+        eb.step(*d, infos[1, k])
+        if k % 3 == 0:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    assert torch.equal(infos[0], infos[1])
+    pa, pb = ga.params(), eb.params()
+    for name in elbo.PARAMS:
+        assert np.array_equal(pa[name], pb[name]), name
+    ga.close()
+    eb.close()
