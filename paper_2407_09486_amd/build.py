@@ -19,7 +19,7 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE, "-I", CSRC,
           "-Wall", "-Wno-unused-function"]
 
-SOURCES = ["detector.cpp", "pot.cpp", "k_aux.hip", "k_score_valu.hip", "k_score_mfma.hip", "k_stream.hip",
+SOURCES = ["detector.cpp", "k_pot.hip", "k_aux.hip", "k_score_valu.hip", "k_score_mfma.hip", "k_stream.hip",
            "k_train.hip", "trainer.cpp", "k_config.hip", "config.cpp", "k_variants.hip", "scratch.hip",
            "k_score_ring.hip", "k_ext_fused.hip", "k_score_split.hip"]
 

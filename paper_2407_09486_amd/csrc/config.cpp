@@ -219,7 +219,7 @@ enova_status enova_config_scan(enova_config h, const void *x, const int64_t *sof
     enova_status st = grow(&h->tiles, &h->tiles_cap, static_cast<size_t>(n) + 1);
     if (st != ENOVA_OK)
         return st;
-    hipError_t e = launch_stream_scan(g, soff, woff, n, 0, h->nb, h->tiles, stream);
+    hipError_t e = launch_stream_scan(g, soff, woff, n, h->nb, h->tiles, stream);
     if (e != hipSuccess)
         return hip_fail(e, "tile scan kernel");
     const int64_t grid = (n_windows + h->nb - 1) / h->nb + n;

@@ -13,6 +13,7 @@
 
 #include "enova_detect.h"
 #include "internal.h"
+#include "pot_internal.h"
 #include "stream_internal.h"
 #include "variants_internal.h"
 
@@ -98,15 +99,14 @@ struct enova_detector_s {
     size_t tile_map_cap = 0;      // entries
     int64_t *cal = nullptr;
     size_t cal_cap = 0;
-    unsigned int *hist = nullptr; // 256 radix bins, then the radix state (RadixState at bin 256)
+    PotState *pot = nullptr;      // the threshold call's state, and the sums of its fit's chunks
+    double *pot_part = nullptr;
+    size_t pot_part_cap = 0;
     double *peaks = nullptr;      // excesses over the level quantile, calibration order
     size_t peaks_cap = 0;
     int64_t *blk = nullptr;       // per-block peak counts, then their exclusive scan
     size_t blk_cap = 0;
-    double *gx = nullptr;         // evaluation points of the GPD likelihood sums, then the sums
-    size_t gx_cap = 0;
-    double *gpin = nullptr;       // pinned host staging of those points and sums
-    size_t gpin_cap = 0;
+    PotOut *pot_out = nullptr;    // its result (pinned host memory)
     // this device's fixed scratch (kScratchBytes, shared by every detector on the device), the
     // only workspace of enova_detect_score_noalloc
     void *scratch = nullptr;
@@ -535,13 +535,13 @@ void free_detector(enova_detector d)
 {
     if (!d)
         return;
-    void *ptrs[] = {d->w1p, d->w1t, d->small, d->stats, d->tiles, d->tile_map, d->cal, d->hist,
-                    d->peaks, d->blk, d->gx, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w};
+    void *ptrs[] = {d->w1p, d->w1t, d->small, d->stats, d->tiles, d->tile_map, d->cal, d->pot,
+                    d->peaks, d->blk, d->pot_part, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
-    if (d->gpin)
-        (void)hipHostFree(d->gpin);
+    if (d->pot_out)
+        (void)hipHostFree(d->pot_out);
     for (hipEvent_t e : d->ev)
         if (e)
             (void)hipEventDestroy(e);
@@ -572,74 +572,6 @@ enova_status check_config(const enova_detect_config *c)
         return fail(ENOVA_EINVAL, "ref_frac must be in (0, 1]");
     return ENOVA_OK;
 }
-
-// Likelihood sums of the GPD fit, evaluated on the device over the compacted excesses.
-struct DeviceGpdSums : GpdSums {
-    enova_detector d;
-    const double *y;
-    int64_t n;
-    hipStream_t st;
-    enova_status status = ENOVA_OK;
-    DeviceGpdSums(enova_detector d_, const double *y_, int64_t n_, hipStream_t s_)
-        : d(d_), y(y_), n(n_), st(s_) {}
-    bool eval(const double *xs, int nx, double *sa, double *sb) override
-    {
-        return run(xs, nx, sa, sb, nullptr, nullptr);
-    }
-    bool eval_d(const double *xs, int nx, double *sa, double *sb, double *sda, double *sdb) override
-    {
-        return run(xs, nx, sa, sb, sda, sdb);
-    }
-    // the sums at nx points (with sda and sdb, else NULL, also their derivatives)
-    bool run(const double *xs, int nx, double *sa, double *sb, double *sda, double *sdb)
-    {
-        if (nx <= 0)
-            return true;
-        const int nv = sda ? 4 : 2;      // sums per point
-        const int ns = gpd_split(n, nx);
-        const size_t np = static_cast<size_t>(nx) * ns;
-        status = ensure(&d->gx, &d->gx_cap, 5 * static_cast<size_t>(nx) + 4 * np);
-        if (status != ENOVA_OK)
-            return false;
-        // pinned host staging: the points, then the sums per point (5 nx doubles at most)
-        if (d->gpin_cap < 5 * static_cast<size_t>(nx)) {
-            if (d->gpin)
-                (void)hipHostFree(d->gpin);
-            d->gpin = nullptr;
-            d->gpin_cap = 0;
-            const size_t cap = std::max<size_t>(5 * static_cast<size_t>(nx), 5 * 1024);
-            if (hipHostMalloc(reinterpret_cast<void **>(&d->gpin), cap * sizeof(double)) != hipSuccess) {
-                d->gpin = nullptr;
-                status = fail(ENOVA_ENOMEM, "pinned host buffer of %zu doubles", cap);
-                return false;
-            }
-            d->gpin_cap = cap;
-        }
-        // device: x, the sums [nv][nx], then the chunk partials [nv][nx][ns]
-        double *dx = d->gx, *ds = dx + nx, *dp = ds + 4 * static_cast<size_t>(nx);
-        double *dpart[4] = {dp, dp + np, dp + 2 * np, dp + 3 * np};
-        double *hx = d->gpin, *hs = hx + nx;
-        std::copy(xs, xs + nx, hx);
-        hipError_t e;
-        if ((e = hipMemcpyAsync(dx, hx, sizeof(double) * nx, hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = launch_gpd_sums(y, n, dx, nx, ns, dpart[0], dpart[1], sda ? dpart[2] : nullptr,
-                                 sda ? dpart[3] : nullptr, st)) != hipSuccess ||
-            (e = launch_gpd_reduce(dpart[0], dpart[1], nx, ns, ds, ds + nx, st)) != hipSuccess ||
-            (sda && (e = launch_gpd_reduce(dpart[2], dpart[3], nx, ns, ds + 2 * nx, ds + 3 * nx, st)) != hipSuccess) ||
-            (e = hipMemcpyAsync(hs, ds, sizeof(double) * nv * nx, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipStreamSynchronize(st)) != hipSuccess) {
-            status = hip_fail(e, "GPD likelihood sums");
-            return false;
-        }
-        std::copy(hs, hs + nx, sa);
-        std::copy(hs + nx, hs + 2 * nx, sb);
-        if (sda) {
-            std::copy(hs + 2 * nx, hs + 3 * nx, sda);
-            std::copy(hs + 3 * nx, hs + 4 * nx, sdb);
-        }
-        return true;
-    }
-};
 
 }  // namespace
 
@@ -926,12 +858,6 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
             st = pack_stream(d, w);
         if (st == ENOVA_OK && ext_fused_supported(g))
             st = pack_ext_fused(d, w);
-    }
-    if (st == ENOVA_OK) {
-        static_assert(sizeof(RadixState) <= 8 * sizeof(unsigned int), "radix state after the bins");
-        hipError_t e = hipMalloc(reinterpret_cast<void **>(&d->hist), (256 + 8) * sizeof(unsigned int));
-        if (e != hipSuccess)
-            st = fail(ENOVA_ENOMEM, "hipMalloc(hist)");
     }
     if (st != ENOVA_OK) {
         free_detector(d);
@@ -1448,114 +1374,73 @@ enova_status enova_detect_threshold(enova_detector det, const float *scores, con
     DeviceGuard dg(det->device);
     const Geometry &g = det->g;
     enova_status st = ensure(&det->cal, &det->cal_cap, static_cast<size_t>(n) + 1);
+    const size_t nblk = static_cast<size_t>(pot_blocks(n_windows));
+    if (st == ENOVA_OK)
+        st = ensure(&det->blk, &det->blk_cap, 2 * nblk);
+    if (st == ENOVA_OK && !det->pot) {
+        const hipError_t e = hipMalloc(reinterpret_cast<void **>(&det->pot), sizeof(PotState));
+        if (e != hipSuccess) {
+            det->pot = nullptr;
+            return fail(ENOVA_ENOMEM, "hipMalloc(%zu): %s", sizeof(PotState), hipGetErrorString(e));
+        }
+    }
+    if (st == ENOVA_OK && !det->pot_out &&
+        hipHostMalloc(reinterpret_cast<void **>(&det->pot_out), sizeof(PotOut)) != hipSuccess) {
+        det->pot_out = nullptr;
+        return fail(ENOVA_ENOMEM, "pinned host memory of the threshold's result");
+    }
     if (st != ENOVA_OK)
         return st;
-    hipError_t e = launch_stream_scan(g, soff, woff, n, 1, 1, det->cal, stream);
+    PotWork w{det->pot, det->cal, det->blk, det->blk + nblk, nullptr, nullptr, 0};
+    hipError_t e = launch_pot_select(g, scores, soff, woff, n, n_windows, level, w, stream);
     if (e != hipSuccess)
-        return hip_fail(e, "calibration scan kernel");
-    int64_t n_cal = 0;
-    if ((e = hipMemcpyAsync(&n_cal, det->cal + n, sizeof(int64_t), hipMemcpyDeviceToHost, stream)) !=
-            hipSuccess ||
-        (e = hipStreamSynchronize(stream)) != hipSuccess)
-        return hip_fail(e, "calibration count");
-    if (n_cal <= 0)
-        return fail(ENOVA_ESHAPE, "no window lies inside a reference prefix");
-
-    // exact order statistic at ceil(level*n) - 1 by a 4-pass radix select over float keys, each
-    // pass's digit picked on the device (no host round trip until the key is known)
-    int64_t rank = static_cast<int64_t>(std::ceil(level * static_cast<double>(n_cal))) - 1;
-    if (rank < 0)
-        rank = 0;
-    if (rank > n_cal - 1)
-        rank = n_cal - 1;
-    RadixState *rs = reinterpret_cast<RadixState *>(det->hist + 256);
-    if ((e = launch_radix_init(rs, rank, det->hist, stream)) != hipSuccess)
-        return hip_fail(e, "radix select start");
-    for (int shift = 24; shift >= 0; shift -= 8)
-        if ((e = launch_calib_hist(scores, woff, det->cal, n, n_cal, shift, rs, det->hist, stream)) != hipSuccess)
-            return hip_fail(e, "calibration histogram kernel");
-    RadixState rh{};
-    if ((e = hipMemcpyAsync(&rh, rs, sizeof(rh), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
-        (e = hipStreamSynchronize(stream)) != hipSuccess)
-        return hip_fail(e, "radix select state");
-    if (!rh.ok)
-        return fail(ENOVA_EHIP, "radix select lost the order statistic");
-    const int64_t n_greater = rh.n_greater;
-    const uint32_t key_t = rh.prefix;
-    const uint32_t bits = (key_t & 0x80000000u) ? (key_t & 0x7fffffffu) : ~key_t;
-    float t_f;
-    std::memcpy(&t_f, &bits, 4);
-    if (!std::isfinite(t_f))
-        return fail(ENOVA_ENUMERIC, "non-finite calibration score at the level quantile");
-    // stable compaction of the excesses y = score - t of every calibration score above t; with
-    // ten or more, their sum, minimum and maximum right behind it (one round trip for both)
-    PotResult r{};
-    const double t_d = static_cast<double>(t_f);
-    double ps[3] = {0.0, 0.0, 0.0};
-    if (n_greater > 0) {
-        const int64_t nblk = calib_blocks(n_cal);
-        if ((st = ensure(&det->peaks, &det->peaks_cap, static_cast<size_t>(n_greater))) != ENOVA_OK ||
-            (st = ensure(&det->blk, &det->blk_cap, 2 * static_cast<size_t>(nblk) + 2)) != ENOVA_OK ||
-            (st = ensure(&det->gx, &det->gx_cap, 4 + 3 * kPeakBlocks)) != ENOVA_OK)
-            return st;
-        int64_t *cnt = det->blk, *off = det->blk + nblk + 1;
-        if ((e = launch_calib_count(scores, woff, det->cal, n, n_cal, key_t, cnt, stream)) != hipSuccess ||
-            (e = launch_scan_i64(cnt, nblk, off, stream)) != hipSuccess ||
-            (e = launch_calib_compact(scores, woff, det->cal, n, n_cal, key_t, t_d, off, det->peaks,
-                                      n_greater, stream)) != hipSuccess)
-            return hip_fail(e, "peak compaction");
-        if (n_greater >= 10 && (e = launch_peak_stats(det->peaks, n_greater, det->gx, det->gx + 4, stream)) !=
-                                   hipSuccess)
-            return hip_fail(e, "peak statistics");
-        int64_t total = 0;
-        if ((e = hipMemcpyAsync(&total, off + nblk, sizeof(int64_t), hipMemcpyDeviceToHost, stream)) !=
-                hipSuccess ||
-            (n_greater >= 10 &&
-             (e = hipMemcpyAsync(ps, det->gx, sizeof(ps), hipMemcpyDeviceToHost, stream)) != hipSuccess) ||
+        return hip_fail(e, "level quantile kernels");
+    // at most (1 - level) of the calibration scores lie above the level quantile; the windows bound
+    // their number, and where that would be much memory the number itself is read back
+    int64_t n_cal = n_windows;
+    if ((1.0 - level) * static_cast<double>(n_windows) > 0x1p24) {
+        if ((e = hipMemcpyAsync(&n_cal, &det->pot->n_cal, sizeof(int64_t), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
             (e = hipStreamSynchronize(stream)) != hipSuccess)
-            return hip_fail(e, "peak count");
-        if (total != n_greater)
-            return fail(ENOVA_EHIP, "peak count mismatch (%lld vs %lld)", static_cast<long long>(total),
-                        static_cast<long long>(n_greater));
+            return hip_fail(e, "calibration count");
+        if (n_cal <= 0)
+            return fail(ENOVA_ESHAPE, "no window lies inside a reference prefix");
     }
-    if (n_greater >= 10) {
-        if (!std::isfinite(ps[0]) || !std::isfinite(ps[2]))
-            return fail(ENOVA_ENUMERIC, "non-finite calibration score");
-        DeviceGpdSums ev(det, det->peaks, n_greater, stream);
-        bool ok = false;
-        r = pot_mle(t_d, n_cal, n_greater, ps[0], ps[1], ps[2], q, ev, &ok);
-        if (!ok)
-            return ev.status != ENOVA_OK ? ev.status : fail(ENOVA_ENUMERIC, "GPD fit failed");
-    } else {
-        double ex[16];
-        if (n_greater > 0) {
-            if ((e = hipMemcpyAsync(ex, det->peaks, sizeof(double) * n_greater, hipMemcpyDeviceToHost,
-                                    stream)) != hipSuccess ||
-                (e = hipStreamSynchronize(stream)) != hipSuccess)
-                return hip_fail(e, "peak copy");
-            for (int64_t i = 0; i < n_greater; ++i)
-                if (!std::isfinite(ex[i]))
-                    return fail(ENOVA_ENUMERIC, "non-finite calibration score");
-            std::sort(ex, ex + n_greater);
+    w.cap = static_cast<int64_t>((1.0 - level) * static_cast<double>(n_cal)) + 2;
+    if ((st = ensure(&det->peaks, &det->peaks_cap, static_cast<size_t>(w.cap))) != ENOVA_OK ||
+        (st = ensure(&det->pot_part, &det->pot_part_cap, static_cast<size_t>(kPotPartDoubles))) != ENOVA_OK)
+        return st;
+    w.y = det->peaks;
+    w.part = det->pot_part;
+    if ((e = launch_pot_peaks(scores, woff, n, n_windows, q, w, stream)) != hipSuccess)
+        return hip_fail(e, "peak kernels");
+    // the grid, Newton steps and the candidates: five rounds end nearly every fit, the flags then
+    // follow at once; a fit that needs more gets them two at a time
+    PotOut *r = det->pot_out;
+    for (int rounds = 5;; rounds = 2) {
+        if ((e = launch_pot_rounds(rounds, q, w, stream)) != hipSuccess ||
+            (e = launch_pot_flag(scores, n_windows, w, r, out_flags, stream)) != hipSuccess ||
+            (e = hipStreamSynchronize(stream)) != hipSuccess)
+            return hip_fail(e, "tail fit kernels");
+        switch (r->err) {
+        case 0: break;
+        case kPotNoWindows: return fail(ENOVA_ESHAPE, "no window lies inside a reference prefix");
+        case kPotLost: return fail(ENOVA_EHIP, "radix select lost the order statistic");
+        case kPotLevelNotFinite:
+            return fail(ENOVA_ENUMERIC, "non-finite calibration score at the level quantile");
+        case kPotCount: return fail(ENOVA_EHIP, "peak count mismatch (%lld)", static_cast<long long>(r->n_peaks));
+        default: return fail(ENOVA_ENUMERIC, "non-finite calibration score");
         }
-        r = pot_small(t_d, n_cal, ex, n_greater, q);
+        if (r->phase == kPotDone)
+            break;
     }
-    const float thr = static_cast<float>(r.z);
-    *out_threshold = thr;
+    *out_threshold = static_cast<float>(r->z);
     if (out_info) {
-        out_info[0] = r.t;
-        out_info[1] = static_cast<double>(r.n);
-        out_info[2] = static_cast<double>(r.n_peaks);
-        out_info[3] = r.gamma;
-        out_info[4] = r.sigma;
-        out_info[5] = r.method;
-    }
-    if (out_flags) {
-        e = launch_flag(scores, n_windows, thr, out_flags, stream);
-        if (e != hipSuccess)
-            return hip_fail(e, "flag kernel");
-        if ((e = hipStreamSynchronize(stream)) != hipSuccess)
-            return hip_fail(e, "flag kernel");
+        out_info[0] = r->t;
+        out_info[1] = static_cast<double>(r->n_cal);
+        out_info[2] = static_cast<double>(r->n_peaks);
+        out_info[3] = r->gamma;
+        out_info[4] = r->sigma;
+        out_info[5] = r->method;
     }
     return ENOVA_OK;
 }

@@ -177,16 +177,15 @@ hipError_t launch_score_list(const Geometry &g, const ScoreParams &p, int nb, in
 size_t stat_part_bytes(int n, int M);
 hipError_t launch_ref_stats(const Geometry &g, const void *x, const int64_t *soff, int n,
                             float *mean, float *std, double *part, hipStream_t st);
-// The two launches that head a scoring pass: the tiles' scan (launch_stream_scan, mode 0) with the
+// The two launches that head a scoring pass: the tiles' scan (launch_stream_scan) with the
 // reference statistics unless mean is NULL, then the tile map with the statistics' last step.
 hipError_t launch_prep_scan(const Geometry &g, const void *x, const int64_t *soff, const int64_t *woff, int n,
                             int div, int64_t *tile_off, float *mean, float *std, double *part, hipStream_t st);
 hipError_t launch_prep_map(const Geometry &g, const void *x, const int64_t *soff, const int64_t *tile_off, int n,
                            int64_t grid, int *map, float *mean, float *std, const double *part, hipStream_t st);
-// out[s] = sum_{r<s} ceil(count(s)/div) for count(s) = (mode 0) windows of stream s,
-// (mode 1) calibration windows of stream s. out has n+1 entries.
+// out[s] = sum_{r<s} ceil(windows of stream r / div), n+1 entries.
 hipError_t launch_stream_scan(const Geometry &g, const int64_t *soff, const int64_t *woff, int n,
-                              int mode, int div, int64_t *out, hipStream_t st);
+                              int div, int64_t *out, hipStream_t st);
 // map[b] = the stream whose tiles include tile b (tile_off has n+1 entries), -1 for
 // tile_off[n] <= b < grid.
 hipError_t launch_tile_map(const int64_t *tile_off, int n, int64_t grid, int *map, hipStream_t st);
@@ -195,66 +194,5 @@ hipError_t launch_score_mfma(const Geometry &g, const ScoreParams &p, int64_t gr
 hipError_t prepare_score_ring(const Geometry &g);
 hipError_t launch_score_ring(const Geometry &g, const ScoreParams &p, int64_t grid, hipStream_t st);
 hipError_t launch_flag(const float *scores, int64_t n, float thr, uint8_t *flags, hipStream_t st);
-// Radix select over the calibration scores' float keys, every pass's digit picked on the device.
-// The state lives in device memory: the key prefix chosen so far, the rank still sought among
-// the keys that share it, the count of keys above it, and ok = 0 if a pass lost the rank.
-struct RadixState {
-    uint32_t prefix;
-    int32_t ok;
-    int64_t rank;
-    int64_t n_greater;
-};
-// rs = {0, 1, rank, 0}; hist (256 bins) cleared.
-hipError_t launch_radix_init(RadixState *rs, int64_t rank, unsigned int *hist, hipStream_t st);
-// One pass: the histogram of the 8-bit digit at `shift` among keys whose bits above shift+8 equal
-// rs->prefix, then (one block) the digit holding rs->rank: rs updated, hist cleared again.
-hipError_t launch_calib_hist(const float *scores, const int64_t *woff, const int64_t *cal_off,
-                             int n, int64_t n_cal, int shift, RadixState *rs,
-                             unsigned int *hist, hipStream_t st);
-// Stable compaction of the calibration scores whose key exceeds `key`:
-// calib_blocks() blocks; pass 1 counts per block, an exclusive scan gives each block's output
-// offset, pass 2 writes the excesses score - t in calibration order.
-int64_t calib_blocks(int64_t n_cal);
-hipError_t launch_calib_count(const float *scores, const int64_t *woff, const int64_t *cal_off, int n,
-                              int64_t n_cal, uint32_t key, int64_t *block_counts, hipStream_t st);
-hipError_t launch_calib_compact(const float *scores, const int64_t *woff, const int64_t *cal_off,
-                                int n, int64_t n_cal, uint32_t key, double t,
-                                const int64_t *block_off, double *y, int64_t cap, hipStream_t st);
-hipError_t launch_scan_i64(const int64_t *in, int64_t n, int64_t *out, hipStream_t st);
-// Partial likelihood sums at the points xs: pa[i*nsplit + j] = sum xs[i] y/(1 + xs[i] y) and
-// pb[i*nsplit + j] = sum log1p(xs[i] y) over the j-th of nsplit contiguous chunks of y (fixed-order
-// fp64 sums, device terms within a few ulps of gpd_terms); with pda and pdb (else NULL) also
-// their derivatives in x, sum y/(1 + xs[i] y)^2 and sum y/(1 + xs[i] y). gpd_split gives nsplit
-// for n excesses and nx points.
-int gpd_split(int64_t n, int nx);
-hipError_t launch_gpd_sums(const double *y, int64_t n, const double *xs, int nx, int nsplit,
-                           double *pa, double *pb, double *pda, double *pdb, hipStream_t st);
-// sa[i], sb[i] = the chunk partials of point i added in a fixed order (one wave per point).
-hipError_t launch_gpd_reduce(const double *pa, const double *pb, int nx, int nsplit, double *sa, double *sb,
-                             hipStream_t st);
-// out = {sum y, min y, max y}; work holds 3 * kPeakBlocks doubles of block partials
-constexpr int kPeakBlocks = 256;
-hipError_t launch_peak_stats(const double *y, int64_t n, double *out, double *work, hipStream_t st);
-
-// Peaks-over-threshold fit (fp64). The likelihood sums over the excesses are supplied by an
-// evaluator, so they can run where the excesses live.
-struct PotResult {
-    double z, t, gamma, sigma;
-    int64_t n, n_peaks;
-    int method;   // 0: the threshold is t, 1: method of moments, 2: maximum likelihood
-};
-struct GpdSums {
-    virtual ~GpdSums() = default;
-    // sa[i] = sum xs[i] y / (1 + xs[i] y), sb[i] = sum log1p(xs[i] y); false on failure
-    virtual bool eval(const double *xs, int nx, double *su, double *sv) = 0;
-    // the same sums and their derivatives in x: sda[i] = sum y / (1 + xs[i] y)^2,
-    // sdb[i] = sum y / (1 + xs[i] y)
-    virtual bool eval_d(const double *xs, int nx, double *su, double *sv, double *sda, double *sdb) = 0;
-};
-// Maximum likelihood (n_peaks >= 10) given the excesses' sum, minimum and maximum.
-PotResult pot_mle(double t, int64_t n, int64_t n_peaks, double ysum, double ymin, double ymax,
-                  double q, GpdSums &sums, bool *ok);
-// Method of moments / degenerate cases (n_peaks < 10) from the excesses on the host.
-PotResult pot_small(double t, int64_t n, const double *excess, int64_t n_peaks, double q);
 
 }  // namespace enova
