@@ -363,11 +363,12 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
 enova_status enova_detect_ext_time(enova_detector det, double *ms);
 
 /* How enova_detect_score_ext evaluates this detector's windows (fixed at init): *fused = 1 for
- * one launch per call that stages each tile's raw steps once and keeps every window's v, hidden
+ * one pass per call over the raw steps that stages each tile's raw steps once and keeps every window's v, hidden
  * layers and decoder output on chip (fp32 detectors of 4, 8 or 16 metrics, at most 128 hidden
  * units -- 64 with tanh and 16 metrics --, at most 16 latent units, W*M a multiple of 32, and a
- * tile that fits half a compute unit's LDS); 0 for the chunked evaluation of normalised windows
- * in device memory. Errors: EINVAL. */
+ * tile that fits half a compute unit's LDS); 0 for every other shape: other metric counts up to 16
+ * with at most 128 hidden units take one pass over padded steps where their tile fits, the rest the
+ * chunked evaluation of normalised windows in device memory. Errors: EINVAL. */
 enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused);
 
 /*

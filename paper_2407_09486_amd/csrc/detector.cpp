@@ -82,6 +82,10 @@ struct enova_detector_s {
     void *stream_w = nullptr;     // streaming kernel: W1, heads and decoder fragments (one allocation)
     const uint4 *w1s = nullptr;
     const float *whs = nullptr, *wds = nullptr;
+    void *ext_x = nullptr;        // split variant pass: Wd2's f16 parts and the padded bd2
+    const uint4 *wd2x = nullptr;
+    const float *bd2x = nullptr;
+    float wd2_unscale = 1.0f;
     void *ext_w = nullptr;        // fused variant pass: decoder-output fragments of Wd2
     const float4 *wd2p = nullptr;
     void *w1t = nullptr;          // [D][H] transposed W1
@@ -531,12 +535,66 @@ enova_status pack_split(enova_detector d, const enova_detect_weights *w)
     return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the split scoring kernel");
 }
 
+// Fragments of the split variant pass: Wd2's rows in the padded order j' = t Mp + m as two f16 parts,
+// scaled by the power of two that puts the largest |weight| into [2^13, 2^14): [Dp/32][HB][2][hi,
+// lo][64 lanes] x 8, where slot t of (ob, hb, m), lane l is the weight of row 32 ob + l % 32 at hidden
+// unit 32 hb + crow(8 m + t, l / 32); bd2 padded the same way follows.
+enova_status pack_ext_split(enova_detector d, const enova_detect_weights *w)
+{
+    const Geometry &g = d->g;
+    const int H = g.H, HB = g.HB, Mp = d->sg.Mp, Dp = ext_split_rows(g, d->sg);
+    float big = 0.0f;
+    for (size_t i = 0; i < static_cast<size_t>(g.D) * H; ++i)
+        big = std::max(big, std::fabs(w->wd2[i]));
+    const int e = big > 0.0f ? std::min(13 - std::ilogb(big), 100) : 0;
+    const float up = std::ldexp(1.0f, e);
+    d->wd2_unscale = std::ldexp(1.0f, -e);
+    const size_t n_w = static_cast<size_t>(Dp / 32) * HB * 2 * 2 * 64;   // 16-byte fragments
+    std::vector<uint16_t> buf(n_w * 8 + static_cast<size_t>(Dp) * 2, 0);
+    float *bd = reinterpret_cast<float *>(buf.data() + n_w * 8);
+    // slot of hidden unit h inside its block: crow(8 m + t, half) = h % 32
+    int slot[32];
+    for (int half = 0; half < 2; ++half)
+        for (int r = 0; r < 16; ++r)
+            slot[crow(r, half)] = ((r >> 3) * 2 * 64 + half * 32) * 8 + (r & 7);
+    for (int t = 0; t < g.W; ++t)
+        for (int m = 0; m < g.M; ++m) {
+            const int j = t * Mp + m;
+            bd[j] = w->bd2[t * g.M + m];
+            const float *row = w->wd2 + static_cast<int64_t>(t * g.M + m) * H;
+            uint16_t *dst = buf.data() + (static_cast<size_t>(j >> 5) * HB * 2 * 2 * 64 + (j & 31)) * 8;
+            for (int h = 0; h < H; ++h) {
+                uint16_t *at = dst + static_cast<size_t>(h >> 5) * 2 * 2 * 64 * 8 + slot[h & 31];
+                float hi, lo;
+                const float v = row[h] * up;
+                at[0] = float_to_f16(v, &hi);
+                at[64 * 8] = float_to_f16(v - hi, &lo);
+            }
+        }
+    enova_status st = dev_upload(&d->ext_x, buf.data(), buf.size() * sizeof(uint16_t));
+    if (st != ENOVA_OK)
+        return st;
+    d->wd2x = static_cast<const uint4 *>(d->ext_x);
+    d->bd2x = reinterpret_cast<const float *>(d->wd2x + n_w);
+    const hipError_t er = prepare_ext_split(g, d->sg);
+    return er == hipSuccess ? ENOVA_OK : hip_fail(er, "configure the split variant kernel");
+}
+
+// All weights of the decoder's output finite and below 2^20 (as split_weights_ok).
+bool split_output_ok(const Geometry &g, const enova_detect_weights *w)
+{
+    bool good = true;
+    for (size_t i = 0; i < static_cast<size_t>(g.D) * g.H; ++i)
+        good &= std::fabs(w->wd2[i]) < 0x1p20f;
+    return good;
+}
+
 void free_detector(enova_detector d)
 {
     if (!d)
         return;
     void *ptrs[] = {d->w1p, d->w1t, d->small, d->stats, d->tiles, d->tile_map, d->cal, d->pot,
-                    d->peaks, d->blk, d->pot_part, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w};
+                    d->peaks, d->blk, d->pot_part, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w, d->ext_x};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -856,7 +914,9 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
         }
         if (st == ENOVA_OK && stream_score_supported(g))
             st = pack_stream(d, w);
-        if (st == ENOVA_OK && ext_fused_supported(g))
+        if (st == ENOVA_OK && ext_split_supported(g, d->sg) && split_output_ok(g, w))
+            st = pack_ext_split(d, w);
+        if (st == ENOVA_OK && !d->wd2x && ext_fused_supported(g))
             st = pack_ext_fused(d, w);
     }
     if (st != ENOVA_OK) {
@@ -1170,7 +1230,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
                 return hip_fail(e, "hipEventCreate");
     }
     const int D = g.D, H = g.H, L = g.L, M = g.M;
-    if (det->wd2p) {
+    if (det->wd2x || det->wd2p) {
         // fused pass: one block per 256-window tile, every output written directly
         const int64_t grid = (n_windows + kExtFusedNb - 1) / kExtFusedNb + n;
         if (grid > 0x7fffffffLL)
@@ -1200,6 +1260,44 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
             return hip_fail(e, "tile scan and reference statistics kernels");
         if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
+        const int decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
+        if (det->wd2x) {
+            ExtSplitParams sp{};
+            sp.x = static_cast<const float *>(x);
+            sp.soff = soff;
+            sp.woff = woff;
+            sp.tile_off = tiles;
+            sp.tile_stream = tmap;
+            sp.mean = ref_mean;
+            sp.std = ref_std;
+            sp.w1x = det->w1x;
+            sp.whx = det->whx;
+            sp.wdx = det->wdx;
+            sp.w1scale = det->w1scale;
+            sp.wd2x = det->wd2x;
+            sp.bd2 = det->bd2x;
+            sp.b1 = det->b1;
+            sp.bd1 = det->bd1;
+            sp.bh = det->bh;
+            sp.w1 = det->d_w1;
+            sp.wml = det->d_wml;
+            sp.bml = det->d_bml;
+            sp.wd1 = det->d_wd1;
+            sp.wd2 = det->d_wd2;
+            sp.bd2d = det->d_bd2;
+            sp.scores = out_scores;
+            sp.md = out_md;
+            sp.mdm = out_md_metric;
+            sp.rec = out_recon;
+            sp.norm = norm;
+            sp.decode = decode;
+            if ((e = launch_ext_split(g, det->sg, sp, det->wd2_unscale, grid, stream)) != hipSuccess)
+                return hip_fail(e, "split variant kernels");
+            if (det->timing)
+                (void)hipEventRecord(det->ext_ev[1], stream);
+            det->ran_ext = true;
+            return ENOVA_OK;
+        }
         ExtFusedParams fp{};
         fp.x = static_cast<const float *>(x);
         fp.soff = soff;
@@ -1217,7 +1315,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         fp.mdm = out_md_metric;
         fp.rec = out_recon;
         fp.norm = norm;
-        fp.decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
+        fp.decode = decode;
         if ((e = launch_ext_fused(g, fp, grid, stream)) != hipSuccess)
             return hip_fail(e, "fused variant kernel");
         if (det->timing)
@@ -1481,7 +1579,7 @@ enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused)
 {
     if (!det || !fused)
         return fail(ENOVA_EINVAL, "NULL argument");
-    *fused = det->wd2p ? 1 : 0;
+    *fused = ext_fused_supported(det->g) && det->kind == 2 ? 1 : 0;
     return ENOVA_OK;
 }
 

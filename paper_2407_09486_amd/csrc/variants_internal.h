@@ -54,4 +54,35 @@ size_t ext_fused_lds_bytes(const Geometry &g);
 hipError_t prepare_ext_fused(const Geometry &g);
 hipError_t launch_ext_fused(const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st);
 
+// ---------------------------------------------------------------------------------------------
+// The same on the 16-bit matrix cores (k_ext_split.hip): fp32 detectors that the split scoring kernel
+// takes, with steps padded to 8 or 16 metrics, at most 128 hidden units and a tile within half a
+// compute unit's LDS; windows out of the split's range one by one, from the dense weights.
+// ---------------------------------------------------------------------------------------------
+struct ExtSplitParams {
+    const float *x;
+    const int64_t *soff, *woff, *tile_off;
+    int *tile_stream;
+    const float *mean, *std;     // reference statistics [n][M] (reference normalisation only)
+    const uint4 *w1x, *whx, *wdx;    // the split scoring kernel's fragments
+    const float *w1scale;
+    const uint4 *wd2x;           // [Dp/32][HB][2][hi, lo][64 lanes]: f16 parts of Wd2 (padded rows)
+    const float *bd2;            // [Dp]
+    const float *b1, *bd1, *bh;
+    const float *w1, *wml, *bml, *wd1, *wd2, *bd2d;   // dense weights
+    float *scores, *md, *mdm, *rec;   // any may be NULL
+    int norm, decode;
+};
+struct ExtSplitShape {
+    int M, S, W, D, H, L, act, Q, CPR, P, nsteps, spare, Dp;
+    float wd2_unscale, inv_w, inv_d;
+    int64_t list_grid;
+};
+bool ext_split_supported(const Geometry &g, const SplitGeometry &sg);
+int ext_split_rows(const Geometry &g, const SplitGeometry &sg);   // Dp
+hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg);
+// wd2_unscale: the inverse of the power of two that wd2x is scaled by
+hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,
+                            int64_t grid, hipStream_t st);
+
 }  // namespace enova

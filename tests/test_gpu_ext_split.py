@@ -1,0 +1,94 @@
+"""The output variants on the 16-bit matrix cores: padded metric counts, tile edges, output rows that end
+inside a 32-row block, hidden layers of one to four blocks, and the windows outside the range of the 16-bit
+parts (evaluated one by one in fp32), against the fp64 oracle. Sums of D products in fp32 differ by about
+sqrt(D) 2^-24 of their scale; the tests allow 3e-6 in the 2-norm (D <= 1024)."""
+import numpy as np
+import pytest
+
+from harness import detector, log, upload
+from oracle import variants as ov
+from paper_2407_09486_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(cfg, weights, w, norm):
+    import torch
+    det = detector(cfg, weights)
+    x, so = upload(w)
+    woff = det.window_offsets(w.stream_offsets)
+    out = det.score_ext(x, so, torch.from_numpy(woff).cuda(), int(woff[-1]), norm=norm)
+    torch.cuda.synchronize()
+    res = [o.cpu().numpy().astype(np.float64) for o in out]
+    det.close()
+    ref = ov.score_ext(w.values_f64(), w.stream_offsets, window=cfg.window, stride=cfg.stride,
+                       weights={k: np.asarray(getattr(weights, k), np.float64) for k in
+                                ("w1", "b1", "wmu", "bmu", "wlv", "blv", "wd1", "bd1", "wd2", "bd2")},
+                       act=cfg.act, norm=norm, ref_frac=cfg.ref_frac)
+    return res, ref
+
+
+def _check(res, ref, sel):
+    scale = ref["scale"][sel]
+    for name, g, o, s in (("score", res[0], ref["score"], None), ("md", res[1], ref["md"], scale),
+                          ("md_m", res[2], ref["md_metric"], scale[:, None]),
+                          ("recon", res[3], ref["recon"], None)):
+        g, o = g[sel], o[sel]
+        if s is None:
+            assert np.linalg.norm(g - o) <= 3e-6 * np.linalg.norm(o), name
+            assert np.all(np.abs(g - o) <= 1e-4 * np.abs(o) + 1e-6), name
+        else:
+            assert np.linalg.norm(g - o) <= 3e-6 * np.linalg.norm(s * np.ones_like(o)), name
+            assert np.all(np.abs(g - o) <= 1e-4 * s), name
+
+
+@pytest.mark.parametrize("norm", ["reference", "window"])
+@pytest.mark.parametrize("M,W,S,H,act", [(7, 9, 1, 64, "tanh"), (5, 33, 8, 32, "relu"), (12, 11, 1, 128, "tanh"),
+                                         (16, 14, 3, 100, "tanh"), (1, 50, 1, 40, "relu"), (8, 6, 9, 128, "relu"),
+                                         (9, 7, 1, 20, "relu"), (16, 64, 1, 128, "relu")])
+def test_tile_and_block_edges(norm, M, W, S, H, act):
+    counts = [1, 31, 64, 65, 255, 257, 513]
+    lengths = [W + (k - 1) * S for k in counts] + [W - 1, 0, W + 100 * S + S - 1]
+    cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, act=act, n_streams=len(lengths))
+    log(f"[ext split] {norm} M={M} W={W} S={S} H={H} {act}")
+    rng = np.random.default_rng(M + W)
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    w = wl.from_arrays(cfg, rng.standard_normal((int(offs[-1]), M)) * np.exp(rng.uniform(-2, 2, M)) + 3, offs)
+    res, ref = _run(cfg, wl.make_weights(cfg, bias_scale=0.1), w, norm)
+    _check(res, ref, np.arange(len(ref["score"])))
+
+
+@pytest.mark.parametrize("norm", ["reference", "window"])
+@pytest.mark.parametrize("M,H", [(7, 64), (16, 128)])
+def test_windows_outside_the_range(norm, M, H):
+    """Spikes, infinities, NaN and nearly constant stretches; every window that holds neither infinity nor
+    NaN against the oracle, the others not finite."""
+    cfg = wl.CONFIGS["c1"].replace(metrics=M, window=20, stride=1, hidden=H, n_streams=2)
+    rng = np.random.default_rng(4)
+    offs = np.array([0, 1500, 2300], np.int64)
+    x = rng.standard_normal((2300, M)).astype(np.float32)
+    x[900, 1] = 3e5
+    x[1000:1060] = 0.25 * np.arange(M)                    # constant metrics
+    x[1100:1160] = 2.0 + 2e-7 * rng.integers(0, 3, (60, M)).astype(np.float32)   # within a few last places
+    x[1300, 0] = np.inf
+    x[1400, M - 1] = np.nan
+    x[2200, 2] = -7e7
+    w = wl.from_arrays(cfg, x, offs)
+    log(f"[ext split] range {norm} M={M} H={H}")
+    res, ref = _run(cfg, wl.make_weights(cfg, bias_scale=0.1), w, norm)
+    start = np.concatenate([np.arange(1500 - 19), 1500 + np.arange(800 - 19)])
+    odd = np.zeros(len(start), bool)
+    for row in (1300, 1400):
+        odd |= (start <= row) & (start + 20 > row)
+    big = np.zeros(len(start), bool)
+    for row in (900, 2200):
+        big |= (start <= row) & (start + 20 > row)
+    _check(res, ref, np.flatnonzero(~odd & ~big))
+    sel = np.flatnonzero(big)
+    for g, o in ((res[0], ref["score"]), (res[3], ref["recon"])):
+        with np.errstate(over="ignore"):            # e^lv overflows on both sides
+            o = o.astype(np.float32).astype(np.float64)
+        np.testing.assert_allclose(g[sel], o[sel], rtol=1e-4, atol=1e-6)
+    nan = np.flatnonzero((start <= 1400) & (start + 20 > 1400))
+    assert np.all(np.isnan(res[0][nan])) and np.all(np.isnan(res[3][nan]))
+    assert not np.any(np.isfinite(res[3][odd]))
