@@ -1230,7 +1230,8 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
                 return hip_fail(e, "hipEventCreate");
     }
     const int D = g.D, H = g.H, L = g.L, M = g.M;
-    if (det->wd2x || det->wd2p) {
+    const bool split = det->wd2x && (ext_fused_supported(g) || ext_split_pays(g, det->sg, n_windows));
+    if (split || det->wd2p) {
         // fused pass: one block per 256-window tile, every output written directly
         const int64_t grid = (n_windows + kExtFusedNb - 1) / kExtFusedNb + n;
         if (grid > 0x7fffffffLL)
@@ -1261,7 +1262,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
         const int decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
-        if (det->wd2x) {
+        if (split) {
             ExtSplitParams sp{};
             sp.x = static_cast<const float *>(x);
             sp.soff = soff;

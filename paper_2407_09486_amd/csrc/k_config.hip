@@ -24,7 +24,65 @@ __device__ __forceinline__ float load_value(const void *x, int64_t idx)
         return static_cast<const float *>(x)[idx];
 }
 
-// One thread per window: two passes over the window's samples in LDS (means, then centred sums).
+// The window's line, t-test and memory line from its means and centred sums.
+__device__ __forceinline__ void cfg_window_out(const CfgParams &c, const CfgScanOut &o, int64_t out, double rm, double fm,
+                                               double mm, double sxx, double sxy, double syy, double sxz)
+{
+    const int W = c.W;
+    double a, b, t, g0, g1;
+    if (sxx == 0.0) {
+        a = fm;
+        b = 0.0;
+        t = 0.0;
+        g0 = mm;
+        g1 = 0.0;
+    } else {
+        b = sxy / sxx;
+        a = fm - b * rm;
+        const double rss = fmax(syy - b * sxy, 0.0);
+        t = b == 0.0 ? 0.0 : (rss == 0.0 ? copysign(HUGE_VAL, b) : b * sqrt((W - 2) * sxx / rss));
+        g1 = sxz / sxx;
+        g0 = mm - g1 * rm;
+    }
+    if (o.a)
+        o.a[out] = static_cast<float>(a);
+    if (o.b)
+        o.b[out] = static_cast<float>(b);
+    if (o.t)
+        o.t[out] = static_cast<float>(t);
+    if (o.sig)
+        o.sig[out] = fabs(t) > c.t_crit ? 1 : 0;
+    if (o.g0)
+        o.g0[out] = static_cast<float>(g0);
+    if (o.g1)
+        o.g1[out] = static_cast<float>(g1);
+}
+
+// Means and centred sums of a window by two passes over its samples.
+struct CfgSums {
+    double rm, fm, mm, sxx, sxy, syy, sxz;
+};
+__device__ __forceinline__ CfgSums cfg_two_pass(const float *r, const float *f, const float *m, int W)
+{
+    double sr = 0.0, sf = 0.0, smu = 0.0;
+    for (int j = 0; j < W; ++j) {
+        sr += r[j];
+        sf += f[j];
+        smu += m[j];
+    }
+    CfgSums q{sr / W, sf / W, smu / W, 0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < W; ++j) {
+        const double dx = r[j] - q.rm, dy = f[j] - q.fm, dz = m[j] - q.mm;
+        q.sxx = fma(dx, dx, q.sxx);
+        q.sxy = fma(dx, dy, q.sxy);
+        q.syy = fma(dy, dy, q.syy);
+        q.sxz = fma(dx, dz, q.sxz);
+    }
+    return q;
+}
+
+// Windows that share few steps (or are too long for the prefix form below): one thread per window,
+// two passes over its samples in LDS (means, then centred sums).
 template <int DT>
 __global__ __launch_bounds__(kCfgThreads) void k_cfg_scan(CfgParams c, int nb, const void *__restrict__ x,
                                                           const int64_t *__restrict__ soff,
@@ -55,49 +113,168 @@ __global__ __launch_bounds__(kCfgThreads) void k_cfg_scan(CfgParams c, int nb, c
     if (w >= nw)
         return;
     const float *r = xr + w * S, *f = xf + w * S, *m = xm + w * S;
-    double sr = 0.0, sf = 0.0, smu = 0.0;
-    for (int j = 0; j < W; ++j) {
-        sr += r[j];
-        sf += f[j];
-        smu += m[j];
+    const CfgSums q = cfg_two_pass(r, f, m, W);
+    cfg_window_out(c, o, woff[s] + k0 + w, q.rm, q.fm, q.mm, q.sxx, q.sxy, q.syy, q.sxz);
+}
+
+// Overlapping windows. The two passes cost 16 issue slots of fp64 per sample of every window, 14 W
+// flops, although neighbouring windows share all but S samples. Here a block of nb windows forms the
+// prefix sums of its (nb - 1) S + W samples once -- of dx, dy, dz (the three columns less the
+// block's first values, exact or rounded in fp64), dx^2, dx dy, dy^2, dx dz and dz^2 -- and each
+// window's sums are differences of two of them: some 25 fp64 operations a sample and 60 a window.
+// Precision. A difference carries the rounding of the block's whole sum, about 2^-52 P, and a
+// centred sum Sxx = sum dx^2 - (sum dx)^2 / W is what is left of it. Where Sxx, Syy - b Sxy and Szz
+// are each above 1e-4 of their block sum the outputs are within 1e-9 (they are stored as fp32); a
+// window below that (a column constant over the window but not over the block, a perfect line)
+// takes the two passes, so that exact zeros stay exact. A column constant over the whole block
+// has all its sums exactly zero.
+// Measured (1024 services x 16384 steps, W = 64, S = 1): 676 -> 288 us for the scan kernel; blocks of
+// 448 windows give every thread two samples (512: 421 us, 256: 545 us, both with a shuffle scan of
+// all eight quantities in every thread; that one at 448: 388 us).
+constexpr int kCfgSumsN = 8;
+constexpr double kCfgKeep = 1e-4;
+
+template <int DT>
+__global__ __launch_bounds__(kCfgThreads) void k_cfg_scan_prefix(CfgParams c, int nb, const void *__restrict__ x,
+                                                                 const int64_t *__restrict__ soff,
+                                                                 const int64_t *__restrict__ woff,
+                                                                 const int64_t *__restrict__ tile_off,
+                                                                 const int *__restrict__ tile_stream, CfgScanOut o)
+{
+    extern __shared__ double cfg_pre[];   // prefix sums [8][pp], then the columns [3][pitch] floats
+    __shared__ double wtot[kCfgThreads / 64][kCfgSumsN];
+    const int s = tile_stream[blockIdx.x];
+    if (s < 0)
+        return;
+    const int64_t k0 = (static_cast<int64_t>(blockIdx.x) - tile_off[s]) * nb;
+    const int64_t nwin = woff[s + 1] - woff[s];
+    const int nw = static_cast<int>(nwin - k0 < nb ? nwin - k0 : nb);
+    const int W = c.W, S = c.S, M = c.M;
+    const int seg = (nw - 1) * S + W;
+    const int pitch = (nb - 1) * S + W;
+    const int pp = (pitch + 1) | 1;       // odd: the eight quantities of a sample in different banks
+    float *xr = reinterpret_cast<float *>(cfg_pre + kCfgSumsN * pp), *xf = xr + pitch, *xm = xf + pitch;
+    const int64_t row0 = soff[s] + k0 * S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < seg; i += kCfgThreads) {
+        const int64_t base = (row0 + i) * M;
+        xr[i] = load_value<DT>(x, base + c.col_r);
+        xf[i] = load_value<DT>(x, base + c.col_f);
+        xm[i] = load_value<DT>(x, base + c.col_m);
     }
-    const double rm = sr / W, fm = sf / W, mm = smu / W;
-    double sxx = 0.0, sxy = 0.0, syy = 0.0, sxz = 0.0;
-    for (int j = 0; j < W; ++j) {
-        const double dx = r[j] - rm, dy = f[j] - fm, dz = m[j] - mm;
-        sxx = fma(dx, dx, sxx);
-        sxy = fma(dx, dy, sxy);
-        syy = fma(dy, dy, syy);
-        sxz = fma(dx, dz, sxz);
+    __syncthreads();
+    // thread tid owns the samples tid * per .. + per - 1
+    const int per = (seg + kCfgThreads - 1) / kCfgThreads;
+    const int i0 = tid * per < seg ? tid * per : seg, i1 = i0 + per < seg ? i0 + per : seg;
+    const double pr = xr[0], pf = xf[0], pm = xm[0];
+    double v[kCfgSumsN];
+#pragma unroll
+    for (int k = 0; k < kCfgSumsN; ++k)
+        v[k] = 0.0;
+    auto add = [&](double (&t)[kCfgSumsN], int i) {
+        const double dx = xr[i] - pr, dy = xf[i] - pf, dz = xm[i] - pm;
+        t[0] += dx;
+        t[1] += dy;
+        t[2] += dz;
+        t[3] = fma(dx, dx, t[3]);
+        t[4] = fma(dx, dy, t[4]);
+        t[5] = fma(dy, dy, t[5]);
+        t[6] = fma(dx, dz, t[6]);
+        t[7] = fma(dz, dz, t[7]);
+    };
+    for (int i = i0; i < i1; ++i)
+        add(v, i);
+    // exclusive prefix of the threads' sums (in the space of the samples' prefixes): thread (k, grp)
+    // takes eight threads' sums of quantity k, so one scan a thread; eight shuffle scans in every
+    // thread took a quarter of the kernel
+    const int used = (seg + per - 1) / per;       // threads that own samples, at most min(256, seg)
+    if (tid < used)
+#pragma unroll
+        for (int k = 0; k < kCfgSumsN; ++k)
+            cfg_pre[k * pp + tid] = v[k];
+    __syncthreads();
+    {
+        const int k = tid & 7, grp = tid >> 3;
+        double own[8], sum = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            own[u] = grp * 8 + u < used ? cfg_pre[k * pp + grp * 8 + u] : 0.0;
+            sum += own[u];
+        }
+        double inc = sum;
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) {
+            const double u = __shfl_up(inc, off);
+            inc += lane >= off ? u : 0.0;
+        }
+        if (lane >= 56)
+            wtot[wave][k] = inc;
+        __syncthreads();
+        const double before = __shfl_up(inc, 8);
+        double run = lane >= 8 ? before : 0.0;
+        for (int w = 0; w < wave; ++w)
+            run += wtot[w][k];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (grp * 8 + u < used)
+                cfg_pre[k * pp + grp * 8 + u] = run;
+            run += own[u];
+        }
     }
-    double a, b, t, g0, g1;
-    if (sxx == 0.0) {
-        a = fm;
-        b = 0.0;
-        t = 0.0;
-        g0 = mm;
-        g1 = 0.0;
-    } else {
-        b = sxy / sxx;
-        a = fm - b * rm;
-        const double rss = fmax(syy - b * sxy, 0.0);
-        t = b == 0.0 ? 0.0 : (rss == 0.0 ? copysign(HUGE_VAL, b) : b * sqrt((W - 2) * sxx / rss));
-        g1 = sxz / sxx;
-        g0 = mm - g1 * rm;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCfgSumsN; ++k)
+        v[k] = tid < used ? cfg_pre[k * pp + tid] : 0.0;
+    __syncthreads();
+    for (int i = i0; i < i1; ++i) {
+#pragma unroll
+        for (int k = 0; k < kCfgSumsN; ++k)
+            cfg_pre[k * pp + i] = v[k];
+        add(v, i);
     }
-    const int64_t out = woff[s] + k0 + w;
-    if (o.a)
-        o.a[out] = static_cast<float>(a);
-    if (o.b)
-        o.b[out] = static_cast<float>(b);
-    if (o.t)
-        o.t[out] = static_cast<float>(t);
-    if (o.sig)
-        o.sig[out] = fabs(t) > c.t_crit ? 1 : 0;
-    if (o.g0)
-        o.g0[out] = static_cast<float>(g0);
-    if (o.g1)
-        o.g1[out] = static_cast<float>(g1);
+    if (i1 == seg && i0 < i1)   // the owner of the last sample
+#pragma unroll
+        for (int k = 0; k < kCfgSumsN; ++k)
+            cfg_pre[k * pp + seg] = v[k];
+    __syncthreads();
+    const double inv_w = 1.0 / W;
+    const double pxx = cfg_pre[3 * pp + seg], pyy = cfg_pre[5 * pp + seg], pzz = cfg_pre[7 * pp + seg];
+    for (int w = tid; w < nw; w += kCfgThreads) {
+        const int at = w * S;
+        double d[kCfgSumsN];
+#pragma unroll
+        for (int k = 0; k < kCfgSumsN; ++k) {
+            const double *p = cfg_pre + k * pp + at;
+            d[k] = p[W] - p[0];
+        }
+        CfgSums q;
+        const double mx = d[0] * inv_w, my = d[1] * inv_w, mz = d[2] * inv_w;
+        q.rm = pr + mx;
+        q.fm = pf + my;
+        q.mm = pm + mz;
+        q.sxx = fma(-d[0], mx, d[3]);
+        q.sxy = fma(-d[0], my, d[4]);
+        q.syy = fma(-d[1], my, d[5]);
+        q.sxz = fma(-d[0], mz, d[6]);
+        const double szz = fma(-d[2], mz, d[7]);
+        const bool xc = pxx == 0.0, yc = pyy == 0.0, zc = pzz == 0.0;
+        // false where a sum is not a number: those windows, too, take the two passes
+        const bool good = (xc || q.sxx > kCfgKeep * pxx) && (zc || szz > kCfgKeep * pzz) &&
+                          (yc || (xc && q.syy > kCfgKeep * pyy) ||
+                           (q.syy - q.sxy * (q.sxy / q.sxx)) > kCfgKeep * pyy);
+        if (good) {
+            // exactly zero where a column is constant over the block
+            if (xc)
+                q.sxx = q.sxy = q.sxz = 0.0;
+            if (yc)
+                q.sxy = q.syy = 0.0;
+            if (zc)
+                q.sxz = 0.0;
+        } else {
+            q = cfg_two_pass(xr + at, xf + at, xm + at, W);
+        }
+        cfg_window_out(c, o, woff[s] + k0 + w, q.rm, q.fm, q.mm, q.sxx, q.sxy, q.syy, q.sxz);
+    }
 }
 
 // Fixed-order block sum: a butterfly in each wave, then the four wave sums as (w0 + w1) +
@@ -311,8 +488,30 @@ __global__ __launch_bounds__(kCfgThreads) void k_cfg_stream(CfgParams c, const v
 
 }  // namespace
 
+// The prefix form where windows share at least three quarters of their steps and a block of 64
+// windows or more fits its LDS (at W = 64, S = 1: 448 windows, 511 samples; four blocks a compute unit).
+constexpr size_t kCfgPrefixLds = 39 * 1024;
+
+static size_t prefix_lds_bytes(const CfgParams &c, int nb)
+{
+    const size_t pitch = static_cast<size_t>(nb - 1) * c.S + c.W;
+    return sizeof(double) * kCfgSumsN * ((pitch + 1) | 1) + sizeof(float) * 3 * pitch;
+}
+
+static int prefix_windows_per_block(const CfgParams &c)
+{
+    if (4LL * c.S > c.W)
+        return 0;
+    for (int nb = 448; nb >= 64; nb = nb > 256 ? 256 : nb >> 1)
+        if (prefix_lds_bytes(c, nb) <= kCfgPrefixLds)
+            return nb;
+    return 0;
+}
+
 int cfg_scan_windows_per_block(const CfgParams &c)
 {
+    if (const int nb = prefix_windows_per_block(c))
+        return nb;
     for (int nb = kCfgThreads; nb >= 1; nb >>= 1)
         if (cfg_scan_lds_bytes(c, nb) <= kCfgScanLds)
             return nb;
@@ -330,13 +529,15 @@ hipError_t launch_cfg_scan(const CfgParams &c, int nb, const void *x, const int6
 {
     if (grid <= 0)
         return hipSuccess;
-    const size_t lds = cfg_scan_lds_bytes(c, nb);
-    if (c.dtype == ENOVA_BF16)
-        hipLaunchKernelGGL(k_cfg_scan<ENOVA_BF16>, dim3(static_cast<unsigned>(grid)), dim3(kCfgThreads), lds, st, c,
-                           nb, x, soff, woff, tile_off, tile_stream, o);
-    else
-        hipLaunchKernelGGL(k_cfg_scan<ENOVA_F32>, dim3(static_cast<unsigned>(grid)), dim3(kCfgThreads), lds, st, c,
-                           nb, x, soff, woff, tile_off, tile_stream, o);
+    using Kernel = void (*)(CfgParams, int, const void *, const int64_t *, const int64_t *, const int64_t *, const int *,
+                            CfgScanOut);
+    const bool prefix = prefix_windows_per_block(c) == nb && nb > 0;
+    const bool bf = c.dtype == ENOVA_BF16;
+    const Kernel k = prefix ? (bf ? static_cast<Kernel>(k_cfg_scan_prefix<ENOVA_BF16>) : k_cfg_scan_prefix<ENOVA_F32>)
+                            : (bf ? static_cast<Kernel>(k_cfg_scan<ENOVA_BF16>) : k_cfg_scan<ENOVA_F32>);
+    const size_t lds = prefix ? prefix_lds_bytes(c, nb) : cfg_scan_lds_bytes(c, nb);
+    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(kCfgThreads), lds, st, c, nb, x, soff, woff, tile_off,
+                       tile_stream, o);
     return hipGetLastError();
 }
 

@@ -740,6 +740,16 @@ bool ext_split_supported(const Geometry &g, const SplitGeometry &sg)
 
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg) { return padded_d(g, sg); }
 
+// A tile's chain of steps takes about 0.18 us per padded element of a window however few tiles there
+// are (73 to 93 us at Dp = 480, 205 us at 1024), and that is the pass until the tiles fill the chip; the
+// chunked evaluation spreads few windows over its products' tiles, 50 us and 1.1e-5 us per window and
+// element (7 metrics, W = 60, H = 64: 48 us for 1000 windows, 73 for 4000, 142 for 16000). They meet at
+// n D = (0.18 Dp - 50) / 1.1e-5.
+bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows)
+{
+    return n_windows * g.D + 4500000 >= 16400LL * padded_d(g, sg);
+}
+
 hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg)
 {
     SplitKernel k = pick(g, sg);

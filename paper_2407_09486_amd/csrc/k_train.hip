@@ -134,7 +134,7 @@ struct EpiParams {
     const float *pre;    // kEpiDact; kEpiRowReduce: the minuend, leading dimension ldv
     float *sq;           // kEpiRowReduce: sums of squares
     int ldv, groups;     // kEpiRowReduce
-    const float *const *aind, *const *bind;   // GemmEpilogue
+    const int64_t *aoff, *boff;   // GemmEpilogue
 };
 
 template <int ACT>
@@ -219,10 +219,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm(const float *__restrict__ A, in
     static_assert(MA >= 1 && MB >= 1 && WM * WN == 4, "tile shape");
     __shared__ __align__(16) float As[2][stage_floats(TM, AK)];
     __shared__ __align__(16) float Bs[2][stage_floats(TN, BK)];
-    if (ep.aind)
-        A = *ep.aind;
-    if (ep.bind)
-        B = *ep.bind;
+    if (ep.aoff)
+        A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
+    if (ep.boff)
+        B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -496,10 +496,10 @@ __global__ __launch_bounds__(64 * kRsWaves) void k_gemm_rs(const float *__restri
     const int iters = kc / (kRsStep * WK);
     C += static_cast<int64_t>(blockIdx.z) * m * ldc;
 
-    if (ep.aind)
-        A = *ep.aind;
-    if (ep.bind)
-        B = *ep.bind;
+    if (ep.aoff)
+        A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
+    if (ep.boff)
+        B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
     // per-lane bases of iteration 0 and the stride between iterations
     const float *ab = AK ? A + static_cast<int64_t>(i0 + p) * lda + kw + 4 * g
                          : A + static_cast<int64_t>(kw + 4 * g) * lda + i0 + 4 * p;
@@ -1135,8 +1135,8 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
     if (epi.kind == kEpiRowReduce &&
         (epi.groups < 1 || epi.groups > 32 || (epi.groups & (epi.groups - 1)) != 0 || !epi.sq || !epi.out2))
         return hipErrorInvalidValue;
-    const EpiParams epp{epi.bias, epi.out2, epi.pre, epi.sq, epi.ldv, epi.groups, epi.aind, epi.bind};
-    const EpiParams ind{nullptr, nullptr, nullptr, nullptr, 0, 0, epi.aind, epi.bind};   // of split slices
+    const EpiParams epp{epi.bias, epi.out2, epi.pre, epi.sq, epi.ldv, epi.groups, epi.aoff, epi.boff};
+    const EpiParams ind{nullptr, nullptr, nullptr, nullptr, 0, 0, epi.aoff, epi.boff};   // of split slices
     {
         // whole tiles with aligned operands: the register-streamed kernel
         const bool epi_rs = epi.kind == kEpiStore || epi.kind == kEpiBiasAct || epi.kind == kEpiDact;

@@ -20,6 +20,11 @@ struct TrainHyper {
 struct StepArgs {
     const float *V, *labels, *eps;
     float *info;
+    // V's distance in bytes from the two bases that the products are launched with (16-byte aligned,
+    // and 4 bytes on). A pointer read from memory would turn the products' loads into flat ones,
+    // which wait on the LDS counter as well (the variants' chunked pass, on the same kernels, lost
+    // 1.5 to 3%).
+    int64_t v_from[2];
 };
 hipError_t launch_step_args(StepArgs *dst, const StepArgs &args, hipStream_t st);
 // A long reduction over few output tiles is split into slices whose partial tiles go to `work`
@@ -43,9 +48,8 @@ struct GemmEpilogue {
     float *sq = nullptr;    // kEpiRowReduce
     int ldv = 0;            // kEpiRowReduce: leading dimension of pre
     int groups = 0;         // kEpiRowReduce
-    // operands read through a pointer in device memory (StepArgs::V) when not NULL: A or B then only
-    // says how that array is aligned
-    const float *const *aind = nullptr, *const *bind = nullptr;
+    // bytes to add to A or B, read from device memory (StepArgs::v_from) when not NULL
+    const int64_t *aoff = nullptr, *boff = nullptr;
 };
 // A split product's slice partials left for a later pass: part [splits][m][n] and rows
 // [splits][m] (NULL without row sums), in `work`; splits == 0 when the product did not split and

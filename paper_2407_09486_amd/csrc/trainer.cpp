@@ -355,19 +355,21 @@ hipError_t enqueue_step(enova_trainer t, const float *V, const StepArgs *sa, int
     };
     mark();
     // forward: a1 = V W1^T + b1, h = act(a1)
-    const float *const *vp = &sa->V;   // an address in device memory, not read here
+    // V as a base of its alignment and the distance that sa holds (an address, not read here)
+    const bool va = reinterpret_cast<uintptr_t>(V) % 16 == 0;
+    const float *vb = va ? t->p : t->p + 1;
+    const int64_t *vo = &sa->v_from[va ? 0 : 1];
     GemmEpilogue enc = bias_act(P + o[P_B1], t->h), dw1;
-    enc.aind = vp;
-    dw1.bind = vp;
-    gemm(enc, V, D, 1, P + o[P_W1], 1, D, t->a1, H, B, H, D, nullptr);
+    enc.aoff = vo;
+    dw1.boff = vo;
+    gemm(enc, vb, D, 1, P + o[P_W1], 1, D, t->a1, H, B, H, D, nullptr);
     // fused heads [mu | lv] = h [Wmu; Wlv]^T, reparameterised latent and KL
     gemm(plain, t->h, H, 1, P + o[P_WMU], 1, H, t->ml, 2 * L, B, 2 * L, H, nullptr);
     run(launch_latent(t->ml, P + o[P_BMU], sa, t->sd, t->z, t->kl, B, L, s));
     // decoder: a2 = z Wd1^T + bd1, hd = act(a2), m' = hd Wd2^T (+ bd2) -> log p and dJ/dm'
     gemm(bias_act(P + o[P_BD1], t->hd), t->z, L, 1, P + o[P_WD1], 1, L, t->a2, H, B, H, L, nullptr);
     gemm(plain, t->hd, H, 1, P + o[P_WD2], 1, H, t->out, D, B, D, H, nullptr);
-    run(launch_recon(t->out, P + o[P_BD2], sa, reinterpret_cast<uintptr_t>(V) % 16 == 0, t->logp, B, D,
-                     t->hyper.margin, s));
+    run(launch_recon(t->out, P + o[P_BD2], sa, va, t->logp, B, D, t->hyper.margin, s));
     // beta(k) from this batch's KL, before the backward pass; the Adam step count and corrections
     run(launch_beta(t->kl, t->logp, sa, B, D, t->hyper, t->state, t->state + 1, t->step, t->state + 2, s));
     // backward through the decoder (G = dJ/dm' in out); bias gradients are the row sums of G^T
@@ -379,7 +381,7 @@ hipError_t enqueue_step(enova_trainer t, const float *V, const StepArgs *sa, int
     run(launch_latent_grad(t->gz, t->gml, t->ml, t->sd, sa, t->state + 1, B, L, s));
     gemm(plain, t->gml, 1, 2 * L, t->h, H, 1, G + o[P_WMU], H, 2 * L, H, B, G + o[P_BMU], 2);
     gemm(dact(t->a1), t->gml, 2 * L, 1, P + o[P_WMU], H, 1, t->gh, H, B, H, 2 * L, nullptr);
-    gemm(dw1, t->gh, 1, H, V, D, 1, G + o[P_W1], D, H, D, B, G + o[P_B1], 3);            // dW1 = G^T V
+    gemm(dw1, t->gh, 1, H, vb, D, 1, G + o[P_W1], D, H, D, B, G + o[P_B1], 3);            // dW1 = G^T V
     // Adam, forming the split weight gradients from their slices first
     run(launch_adam(P, G, t->m, t->v, t->total, t->hyper, t->state + 2, sums, s));
     mark();
@@ -451,7 +453,8 @@ enova_status enova_train_step(enova_trainer t, const float *V, const float *labe
     enova_status st = ensure_batch(t, B);
     if (st != ENOVA_OK)
         return st;
-    const StepArgs args{V, labels, eps, info};
+    const int64_t from = reinterpret_cast<const char *>(V) - reinterpret_cast<const char *>(t->p);
+    const StepArgs args{V, labels, eps, info, {from, from - static_cast<int64_t>(sizeof(float))}};
     if (t->timed || !t->use_graph) {
         hipError_t e = launch_step_args(t->args + 1, args, s);
         if (e == hipSuccess)

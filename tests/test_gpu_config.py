@@ -190,3 +190,45 @@ def test_recommend_longest_window():
         assert np.array_equal(np.isnan(got), np.isnan(exp))
         ok = ~np.isnan(exp)
         np.testing.assert_allclose(got[ok], exp[ok], rtol=1e-9, atol=0)
+
+
+@pytest.mark.parametrize("W,S,lengths", [(64, 1, [511, 512, 575, 64, 63, 2000]), (16, 4, [1900, 16, 20]),
+                                         (5, 1, [5, 6, 452, 900]), (200, 3, [1500, 200, 202, 700]),
+                                         (300, 1, [1400, 301]), (12, 4, [300, 12]), (3, 1, [700]), (40, 11, [900])])
+def test_scan_shapes_and_degenerate_stretches(W, S, lengths):
+    """Both forms of the scan at the edges of their blocks, over series with what a difference of running
+    sums must not blur: columns constant over a window but not over its block, a perfect line, a drift of
+    many window deviations, an offset of a million and one not-a-number."""
+    log(f"config scan W={W} S={S} {lengths}")
+    x, offs = _series(lengths, seed=W)
+    T = lengths[0]
+    a, b = T // 5, 2 * T // 5
+    x[a:b, 1] = 7.0                                     # n^r constant: no relation
+    x[b:b + T // 5, 5] = 0.125                          # m^u constant: a flat line, exactly
+    x[b:b + T // 10, 0] = 3.0 * x[b:b + T // 10, 1]     # a perfect line
+    x[T // 2:T, 1] += np.float32(30.0) * np.arange(T - T // 2, dtype=np.float32)   # drift
+    if len(lengths) > 1:
+        x[offs[1]:offs[2], 0] += 1e6
+    sc = _scanner(W, S)
+    wo = sc.window_offsets(offs)
+    import torch
+    so_d, wo_d = torch.from_numpy(offs).cuda(), torch.from_numpy(wo).cuda()
+    xd = _upload(x, "f32")
+    got = sc.scan(xd, so_d, wo_d, int(wo[-1]))
+    ref = cs.window_scan(x.astype(np.float64), offs, window=W, stride=S, col_f=0, col_r=1, col_m=5)
+    # on a perfect line the residual is the rounding of either side: t is large, or infinite, on both
+    line = ~(np.abs(ref["t"]) < 1e5)
+    assert np.all(np.abs(got[2].cpu().numpy()[line]) >= 1e4) and np.all(got[3].cpu().numpy()[line] == 1)
+    keep = torch.from_numpy(np.flatnonzero(~line)).cuda()
+    _check_scan([g[keep] for g in got], {k: v[~line] for k, v in ref.items()}, cs.t_critical(0.05, W - 2), f"W={W} S={S}")
+    flat = np.flatnonzero(ref["g1"] == 0.0)
+    assert np.all(got[5].cpu().numpy()[flat] == 0.0)
+    xd[3 * T // 4, 1] = float("nan")
+    bad = sc.scan(xd, so_d, wo_d, int(wo[-1]))
+    k = np.arange(int(wo[1]))
+    hit = (k * S <= 3 * T // 4) & (k * S + W > 3 * T // 4)
+    for g, h in zip(got, bad):
+        g, h = g.cpu().numpy(), h.cpu().numpy()
+        assert np.allclose(g[:wo[1]][~hit], h[:wo[1]][~hit], rtol=1e-6, atol=1e-12, equal_nan=True)
+    assert np.all(np.isnan(bad[1].cpu().numpy()[:wo[1]][hit]))
+    sc.close()
