@@ -205,7 +205,8 @@ __device__ __forceinline__ void epi_tile(float *__restrict__ C, int64_t ldc, int
 // to rowsum[z m + i] (the bias gradient of a weight-gradient product, read from the staged tiles).
 // Matrix op t of an 8-index group takes, in lane l, the reduction index 4 (l / 32) + t of the
 // group for both operands (a relabelling of the sum), so one 16-byte LDS read feeds four ops.
-template <bool AK, bool BK, int EPI, int ACT, int TM, int TN>
+// OFF: A or B takes the offset of ep (the training step's products of the caller's windows).
+template <bool AK, bool BK, int EPI, int ACT, int TM, int TN, bool OFF>
 __global__ __launch_bounds__(256, 2) void k_gemm(const float *__restrict__ A, int64_t lda, bool va,
                                                  const float *__restrict__ B, int64_t ldb, bool vb,
                                                  float *__restrict__ C, int64_t ldc, float *__restrict__ rowsum,
@@ -219,10 +220,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm(const float *__restrict__ A, in
     static_assert(MA >= 1 && MB >= 1 && WM * WN == 4, "tile shape");
     __shared__ __align__(16) float As[2][stage_floats(TM, AK)];
     __shared__ __align__(16) float Bs[2][stage_floats(TN, BK)];
-    if (ep.aoff)
-        A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
-    if (ep.boff)
-        B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
+    if constexpr (OFF) {
+        if (ep.aoff)
+            A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
+        if (ep.boff)
+            B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
+    }
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -474,7 +477,7 @@ __device__ __forceinline__ int rs_index(int blk, int slot)
 
 // MR 16-row blocks x NC 16-column blocks per wave, PD register slots of operand prefetch. RS: the
 // blocks of the first column tile also write rowsum[z m + i] = sum_k A(i, k) over the slice.
-template <bool AK, bool BK, int EPI, int ACT, int MR, int NC, int PD>
+template <bool AK, bool BK, int EPI, int ACT, int MR, int NC, int PD, bool OFF>
 __global__ __launch_bounds__(64 * kRsWaves) void k_gemm_rs(const float *__restrict__ A, int64_t lda,
                                                            const float *__restrict__ B, int64_t ldb,
                                                            float *__restrict__ C, int64_t ldc,
@@ -496,10 +499,12 @@ __global__ __launch_bounds__(64 * kRsWaves) void k_gemm_rs(const float *__restri
     const int iters = kc / (kRsStep * WK);
     C += static_cast<int64_t>(blockIdx.z) * m * ldc;
 
-    if (ep.aoff)
-        A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
-    if (ep.boff)
-        B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
+    if constexpr (OFF) {
+        if (ep.aoff)
+            A = reinterpret_cast<const float *>(reinterpret_cast<const char *>(A) + *ep.aoff);
+        if (ep.boff)
+            B = reinterpret_cast<const float *>(reinterpret_cast<const char *>(B) + *ep.boff);
+    }
     // per-lane bases of iteration 0 and the stride between iterations
     const float *ab = AK ? A + static_cast<int64_t>(i0 + p) * lda + kw + 4 * g
                          : A + static_cast<int64_t>(kw + 4 * g) * lda + i0 + 4 * p;
@@ -994,21 +999,36 @@ unsigned blocks_for(int64_t total)
 
 namespace {
 
-template <bool AK, bool BK, int EPI, int ACT>
-void gemm_run(dim3 grid, hipStream_t st, const float *A, int64_t lda, bool va, const float *B, int64_t ldb, bool vb,
-              float *C, int64_t ldc, float *rowsum, const EpiParams &ep, int m, int n, int k, int kc)
+// Products that may take an operand's offset: with bias + activation (the encoder's) or a plain store
+// (a weight gradient's, and the slices of either when it is split), in every layout (a hidden width or
+// input of one makes an operand contiguous both ways). launch_gemm refuses the others.
+constexpr bool takes_offset(int epi) { return epi == kEpiBiasAct || epi == kEpiStore; }
+
+template <bool AK, bool BK, int EPI, int ACT, bool OFF>
+void gemm_tiles(dim3 grid, hipStream_t st, const float *A, int64_t lda, bool va, const float *B, int64_t ldb, bool vb,
+                float *C, int64_t ldc, float *rowsum, const EpiParams &ep, int m, int n, int k, int kc)
 {
     int tm, tn;
     gemm_tile(m, n, tm, tn);
     if (tn == kGemmThin)
-        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmTile, kGemmThin>), grid, dim3(256), 0, st, A, lda, va, B,
-                           ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
+        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmTile, kGemmThin, OFF>), grid, dim3(256), 0, st, A, lda, va,
+                           B, ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
     else if (tm == kGemmThin)
-        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmThin, kGemmTile>), grid, dim3(256), 0, st, A, lda, va, B,
-                           ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
+        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmThin, kGemmTile, OFF>), grid, dim3(256), 0, st, A, lda, va,
+                           B, ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
     else
-        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmTile, kGemmTile>), grid, dim3(256), 0, st, A, lda, va, B,
-                           ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
+        hipLaunchKernelGGL((k_gemm<AK, BK, EPI, ACT, kGemmTile, kGemmTile, OFF>), grid, dim3(256), 0, st, A, lda, va,
+                           B, ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
+}
+
+template <bool AK, bool BK, int EPI, int ACT>
+void gemm_run(dim3 grid, hipStream_t st, const float *A, int64_t lda, bool va, const float *B, int64_t ldb, bool vb,
+              float *C, int64_t ldc, float *rowsum, const EpiParams &ep, int m, int n, int k, int kc)
+{
+    if constexpr (takes_offset(EPI))
+        if (ep.aoff || ep.boff)
+            return gemm_tiles<AK, BK, EPI, ACT, true>(grid, st, A, lda, va, B, ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
+    gemm_tiles<AK, BK, EPI, ACT, false>(grid, st, A, lda, va, B, ldb, vb, C, ldc, rowsum, ep, m, n, k, kc);
 }
 
 template <int EPI, int ACT>
@@ -1041,15 +1061,24 @@ void rs_layouts(int kind, bool a_k, bool b_k, dim3 grid, hipStream_t st, const f
 {
     // each kernel's tile is rs_shape(kind): tm = 16 MR, tn = 16 NC, pd register slots
     const dim3 block(64 * kRsWaves);
+    const bool off = ep.aoff || ep.boff;
+    auto go = [&](auto k) {
+        hipLaunchKernelGGL(k, grid, block, 0, st, A, lda, B, ldb, C, ldc, rowsum, ep, m, kc);
+    };
+    if constexpr (takes_offset(EPI))
+        if (off) {
+            if (kind == kRsK4 && b_k)
+                return go(k_gemm_rs<true, true, EPI, ACT, 2, 8, 2, true>);
+            if (kind == kRsK4)
+                return go(k_gemm_rs<true, false, EPI, ACT, 2, 8, 2, true>);
+            return go(k_gemm_rs<false, false, EPI, ACT, 4, 4, 2, true>);
+        }
     if (kind == kRsK4 && b_k)
-        hipLaunchKernelGGL((k_gemm_rs<true, true, EPI, ACT, 2, 8, 2>), grid, block, 0, st, A, lda, B, ldb, C, ldc,
-                           rowsum, ep, m, kc);
+        go(k_gemm_rs<true, true, EPI, ACT, 2, 8, 2, false>);
     else if (kind == kRsK4)
-        hipLaunchKernelGGL((k_gemm_rs<true, false, EPI, ACT, 2, 8, 2>), grid, block, 0, st, A, lda, B, ldb, C, ldc,
-                           rowsum, ep, m, kc);
+        go(k_gemm_rs<true, false, EPI, ACT, 2, 8, 2, false>);
     else
-        hipLaunchKernelGGL((k_gemm_rs<false, false, EPI, ACT, 4, 4, 2>), grid, block, 0, st, A, lda, B, ldb, C, ldc,
-                           rowsum, ep, m, kc);
+        go(k_gemm_rs<false, false, EPI, ACT, 4, 4, 2, false>);
     (void)a_k;
 }
 
@@ -1129,6 +1158,8 @@ hipError_t launch_gemm(const GemmEpilogue &epi, const float *A, int64_t ai, int6
     if ((ak != 1 && ai != 1) || (bk != 1 && bj != 1))
         return hipErrorInvalidValue;
     const bool a_k = ak == 1, b_k = bk == 1;
+    if ((epi.aoff || epi.boff) && !takes_offset(epi.kind))
+        return hipErrorInvalidValue;
     const int64_t lda = a_k ? ai : ak, ldb = b_k ? bj : bk;
     const bool va = lda % 4 == 0 && lda <= kGemmMaxLd32 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
     const bool vb = ldb % 4 == 0 && ldb <= kGemmMaxLd32 && reinterpret_cast<uintptr_t>(B) % 16 == 0;
