@@ -1,7 +1,8 @@
 """The threshold call over the sizes at which its launches change: more streams than its offsets table
-in LDS holds, both block sizes (beyond 4 M windows), calibration sets that end inside a block, none, one
-and nine peaks, and heavy and light tails, against the oracle's order statistic and fit on the same
-scores. Both sides fit in fp64; the roots agree to rounding, gamma and sigma to 1e-7."""
+in LDS holds, both block sizes (beyond 4 M windows), several runs a block (beyond 33 M), calibration
+sets that end inside a block, none, one and nine peaks, and heavy and light tails, against the oracle's
+order statistic and fit on the same scores. Both sides fit in fp64; the roots agree to rounding, gamma
+and sigma to 1e-7."""
 import numpy as np
 import pytest
 
@@ -26,6 +27,7 @@ def _det(W, S):
     ("2048 streams", [40] * 2047 + [900], 4, 1, 0.98, 0.1),
     ("3000 streams", list(range(3, 3003)), 4, 3, 0.95, 0.5),
     ("over 4 M windows", [4_300_000, 200_001], 2, 1, 0.98, 0.2),
+    ("over 33 M windows", [33_600_000, 3, 500_001], 2, 1, 0.999, 0.2),
     ("nine peaks", [920], 2, 1, 0.98, 0.2),
     ("ten peaks", [1002], 2, 1, 0.98, 0.2),
     ("one peak", [60], 2, 1, 0.98, 0.2),
