@@ -471,7 +471,9 @@ enova_status enova_train_step(enova_trainer t, const float *V, const float *labe
         if ((e = launch_step_args(t->args, args, s)) != hipSuccess)
             return hip_fail(e, "training step arguments");
         t->cur = args;
-        t->cur_set = true;
+        // a launch that a caller's capture only recorded has not set them
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        t->cur_set = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
     }
     e = hipGraphLaunch(q->exec, s);
     return e == hipSuccess ? ENOVA_OK : hip_fail(e, "hipGraphLaunch");
