@@ -449,8 +449,18 @@ enova_status pack_ext_fused(enova_detector d, const enova_detect_weights *w)
     return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the fused variant kernel");
 }
 
-// Weights the split kernel can take: all finite, and none so large that a product of three layers
-// could leave the fp32 range.
+// Weights the split kernel can take: all finite, none so large that a product of three layers could
+// leave the fp32 range, and no input whose weight stands out. An input's f16 parts hold it to 2^-29
+// whatever its size, and a window is only known to have one input of kSplitMin (split.h) or more, at any
+// place. With e_j = sum_h g_h |W1[h][j]|, g_h the heads' weights of hidden unit h, the heads err by
+// some 2^-30 sqrt(sum e_j^2) where they are of the order of 2^-2 e_j or more for that place j: not above
+// fp32's own rounding while all e_j are alike, but without a bound where small inputs have large
+// weights (half the metrics at 1e-6 under weights of 9e5: scores off by 6e-4, and 4e-3 at 1e-8; in fp32
+// 1e-6). So the places may differ by kSplitPlaces and the metrics, over all steps, by kSplitMetrics: that
+// keeps the error of such a window below 2^-28 sqrt(D) 16, 1.3e-6 at D = 512 (places: 5e-6). Randomly
+// drawn weights differ by 2 to 3 (64 hidden units) and by 1.1.
+constexpr float kSplitPlaces = 64.0f, kSplitMetrics = 16.0f;
+
 bool split_weights_ok(const Geometry &g, const enova_detect_weights *w)
 {
     const size_t H = g.H, L = g.L, D = g.D;
@@ -461,8 +471,30 @@ bool split_weights_ok(const Geometry &g, const enova_detect_weights *w)
             good &= std::fabs(f[i]) < 0x1p20f;   // false for NaN
         return good;
     };
-    return ok(w->w1, H * D) && ok(w->b1, H) && ok(w->wmu, L * H) && ok(w->bmu, L) && ok(w->wlv, L * H) &&
-           ok(w->blv, L) && ok(w->wd1, H * L) && ok(w->bd1, H);
+    if (!(ok(w->w1, H * D) && ok(w->b1, H) && ok(w->wmu, L * H) && ok(w->bmu, L) && ok(w->wlv, L * H) &&
+          ok(w->blv, L) && ok(w->wd1, H * L) && ok(w->bd1, H)))
+        return false;
+    std::vector<float> e(D, 0.0f);
+    for (size_t h = 0; h < H; ++h) {
+        float gh = 0.0f;
+        for (size_t l = 0; l < L; ++l)
+            gh += std::fabs(w->wmu[l * H + h]) + std::fabs(w->wlv[l * H + h]);
+        const float *row = static_cast<const float *>(w->w1) + h * D;
+        for (size_t j = 0; j < D; ++j)
+            e[j] += gh * std::fabs(row[j]);
+    }
+    float lo = e[0], hi = e[0];
+    for (const float v : e) {
+        lo = std::min(lo, v);
+        hi = std::max(hi, v);
+    }
+    if (hi > kSplitPlaces * lo)
+        return false;
+    std::vector<double> em(g.M, 0.0);
+    for (size_t j = 0; j < D; ++j)
+        em[j % g.M] += e[j];
+    const auto mm = std::minmax_element(em.begin(), em.end());
+    return *mm.second <= kSplitMetrics * *mm.first;
 }
 
 // Fragments of the split kernel, one allocation:

@@ -13,11 +13,12 @@ namespace {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-// Normalised inputs are scaled by 2^4 before they are split: a |v| up to 4000 fits f16, and the
-// parts are exact down to 2^-29. Windows beyond it or altogether below 2^-4 (in scaled units:
-// kSplitMax, kSplitMin) take the fp32 kernel.
+// Normalised inputs are scaled by 2^4 before they are split: a |v| up to 4000 fits f16, and the parts
+// hold every one to 2^-29 (to 23 bits from 2^-6 on). Windows with an input beyond 4000, and windows
+// whose every input is below 2^-2, where 2^-29 would be more than the rounding of an fp32 sum, take the
+// fp32 kernel (in scaled units: kSplitMax, kSplitMin).
 constexpr float kSplitScale = 16.0f, kSplitUnscale = 1.0f / 16.0f;
-constexpr float kSplitMax = 64000.0f, kSplitMin = 1.0f;
+constexpr float kSplitMax = 64000.0f, kSplitMin = 4.0f;
 
 // 1/std of the scaled values (the scale is a power of two: (x - mean) * split_rinv(std) is exactly
 // kSplitScale times (x - mean) * (1 / std)).

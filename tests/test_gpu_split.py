@@ -110,3 +110,54 @@ def test_weight_scales():
     np.testing.assert_allclose(sc, rsc, rtol=1e-5)
     det.close()
     ref.close()
+
+
+# Half the inputs small under large weights, the other half ordinary: by metric, by step (the first half
+# of every stream, so windows at its end hold both) or with the large factor in the heads' weights.
+@pytest.mark.parametrize("where", ["metrics", "steps", "heads"])
+@pytest.mark.parametrize("small,big,other", [(1e-5, 1e5, 1.0), (1e-6, 9e5, 1.0), (1e-8, 1e6, 1e-2)])
+def test_small_inputs_under_large_weights(small, big, other, where):
+    """A 16-bit part holds nothing below 2^-24, so inputs far below the window's largest may lose digits that
+    large weights would bring back: such detectors keep fp32's precision (relative 2-norm 4e-6; fp32 sums
+    measure 6e-7 to 9e-7)."""
+    M, W, H = 8, 32, 64
+    cfg = _cfg(M, W, 1, H, n=2)
+    rng = np.random.default_rng(11)
+    offs = np.array([0, 700, 1500], np.int64)
+    x = rng.standard_normal((1500, M)) * 2.0
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    w1 = weights.w1.reshape(H, W, M)
+    if where == "metrics":
+        x[:, :4] *= small
+        w1[:, :, :4] *= big
+        w1[:, :, 4:] *= other
+    elif where == "steps":
+        x[:350] *= small
+        x[700:1100] *= small
+        w1[:, :W // 2] *= big
+        w1[:, W // 2:] *= other
+    else:
+        x[:, :4] *= small
+        w1[:H // 2, :, 4:] = 0.0
+        w1[H // 2:, :, :4] = 0.0
+        weights.b1[:H // 2] *= small
+        for a in (weights.wmu, weights.wlv):
+            a[:, :H // 2] *= big
+            a[:, H // 2:] *= other
+    w = wl.from_arrays(cfg, x, offs)
+    ref = (np.zeros((2, M)), np.ones((2, M)))
+    log(f"[split] small inputs {where} {small} {big} {other}")
+    det = detector(cfg, weights)
+    sc, md, _, _ = gpu_score(det, w, ref=ref)
+    o_sc, o_md, info = oracle_score(cfg, w, weights, ref=ref)
+    # large windows and the others apart: e^lv spans many decades, and leaves fp32's where ordinary inputs
+    # meet the large weights
+    few = np.flatnonzero(o_sc < 1e4)
+    assert len(few) > 200
+    for sel in (few, few[o_sc[few] < 10 * np.median(o_sc[few])]):
+        err = np.linalg.norm(sc[sel] - o_sc[sel]) / np.linalg.norm(o_sc[sel])
+        log(f"  {len(sel)} windows, relative error {err:.2e}")
+        assert err <= 4e-6
+    check_scores(sc[few], o_sc[few], "f32", where)
+    check_md(md[few], o_md[few], info["md_scale"][few], "f32", where)
+    det.close()
