@@ -92,3 +92,28 @@ def test_windows_outside_the_range(norm, M, H):
     nan = np.flatnonzero((start <= 1400) & (start + 20 > 1400))
     assert np.all(np.isnan(res[0][nan])) and np.all(np.isnan(res[3][nan]))
     assert not np.any(np.isfinite(res[3][odd]))
+
+
+@pytest.mark.parametrize("norm", ["reference", "window"])
+@pytest.mark.parametrize("where", ["rows", "units"])
+def test_decoder_output_scales(norm, where):
+    """Decoder output weights whose rows (here one metric's) or columns (hidden units, whose activations make
+    up for it) lie far apart: the other metrics' md keep fp32's precision (|v| and |m'| of about 1, one
+    rounding of 2^-24 each: 6e-8 rms; fp32 sums measure 5e-8)."""
+    M, W, H = 8, 8, 64
+    cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=1, hidden=H, n_streams=2)
+    rng = np.random.default_rng(8)
+    offs = np.array([0, 1200, 2100], np.int64)
+    w = wl.from_arrays(cfg, rng.standard_normal((2100, M)) * 2 + 1, offs)
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    if where == "rows":
+        weights.wd2.reshape(W, M, H)[:, 0] *= 1e6
+    else:
+        weights.wd1[:H // 2] *= 1e-6
+        weights.bd1[:H // 2] *= 1e-6
+        weights.wd2[:, :H // 2] *= 1e6
+    log(f"[ext split] decoder scales {norm} {where}, largest |Wd2| {np.abs(weights.wd2).max():.3g}")
+    res, ref = _run(cfg, weights, w, norm)
+    err = np.sqrt(np.mean((res[2] - ref["md_metric"])[:, 1:] ** 2))
+    log(f"  rms error {err:.2e}")
+    assert err <= 1e-7
