@@ -24,20 +24,22 @@ namespace enova {
 
 namespace {
 
-// Largest scaled |v| of a row's elements, as k_score_split forms it.
+// Largest scaled |v| of a row's elements el, el + 1, ..., and of those below tail_elems, as k_score_split
+// forms them.
 template <int N>
-__device__ __forceinline__ void row_max(unsigned *rm, const float (&x)[N], const float *mu, const float *ri)
+__device__ __forceinline__ void row_max(unsigned *rm, unsigned *rt, const float (&x)[N], const float *mu,
+                                        const float *ri, int el, int tail_elems)
 {
-    float big = 0.0f;
-    bool bad = false;
+    unsigned big = 0u, tail = 0u;
 #pragma unroll
     for (int e = 0; e < N; ++e) {
-        const float a = fabsf((x[e] - mu[e]) * (ri[e] * kSplitScale));
-        const bool out = !(a <= kSplitMax);
-        bad |= out;
-        big = fmaxf(big, out ? 0.0f : a);
+        const unsigned a = __float_as_uint((x[e] - mu[e]) * (ri[e] * kSplitScale)) & 0x7fffffffu;
+        big = max(big, a);
+        tail = el + e < tail_elems ? max(tail, a) : tail;
     }
-    atomicMax(rm, bad ? 0x7f800000u : __float_as_uint(big));
+    atomicMax(rm, big);
+    if (rt != rm && tail)
+        atomicMax(rt, tail);
 }
 
 struct MfmaShape {
@@ -56,9 +58,12 @@ struct MfmaShape {
 // CL: the epilogue weights are copied into LDS with each tile (else read from L2, leaving the
 // LDS to a larger segment).
 // LIST: the tile is one that k_score_split marked; only its windows outside the split's range are
-// written (see split.h).
+// written (see split.h): with raw_values those that hold an infinity or a NaN, else the others, for which such
+// values are staged as zeros (under zero weights they would make NaN of windows that end before them).
+// Returns whether the tile holds any.
 template <int DT, int HB, int NBW, int WH, int NW, int ACT, bool CL, bool LIST>
-__device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const MfmaShape &g, int s, int64_t k0, int nv)
+__device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const MfmaShape &g, int s, int64_t k0, int nv,
+                                                bool raw_values)
 {
     constexpr int NT = NW * 64;                   // threads of the block
     constexpr int WN = NW / WH;                   // window groups
@@ -109,11 +114,18 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
     float *s_bd1 = s_b1 + HP;
     float *s_u = s_bd1 + HP;
     float *s_bh = s_u + HP;
-    // list mode: the largest scaled |v| of each staged row
+    // list mode: the largest scaled |v| of each staged row, of its steps that a window's last row has
+    // (the same where that is all), and whether one of them is not finite
     unsigned *rm = reinterpret_cast<unsigned *>(CL ? ps + rows_alloc : s_bh + 32);
-    if constexpr (LIST)
+    unsigned *rt = g.tail_rows == S ? rm : rm + rows_alloc;
+    unsigned *s_odd = rt + rows_alloc;
+    const int tail_elems = g.tail_rows * Mp;
+    if constexpr (LIST) {
         for (int r = tid; r < nrows; r += NT)
-            rm[r] = 0u;
+            rm[r] = rt[r] = 0u;
+        if (tid == 0)
+            *s_odd = 0u;
+    }
 
     if constexpr (CL) {
         // the host lays the epilogue weights out contiguously in this LDS order; copy them with
@@ -218,7 +230,7 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
                     v[7] = bf16_hi(raw[u].w);
                 }
                 if constexpr (LIST)
-                    row_max(rm + r, v, mu, ri);
+                    row_max(rm + r, rt + r, v, mu, ri, c * EPC, tail_elems);
 #pragma unroll
                 for (int e = 0; e < EPC; ++e)
                     v[e] = (v[e] - mu[e]) * ri[e];
@@ -232,12 +244,17 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
                     if (off >= 0 && rel + off < eavail) {
                         const float raw1[1] = {load_x<DT>(p.x, ebase + rel + off)};
                         if constexpr (LIST)
-                            row_max(rm + r, raw1, mu + e, ri + e);
+                            row_max(rm + r, rt + r, raw1, mu + e, ri + e, c * EPC + e, tail_elems);
                         val = (raw1[0] - mu[e]) * ri[e];
                     }
                     v[e] = val;
                 }
             }
+            if constexpr (LIST)
+                if (!raw_values)
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e)
+                        v[e] = isfinite(v[e]) ? v[e] : 0.0f;
             uint4 out;
             if constexpr (DT == ENOVA_F32) {
                 out.x = __float_as_uint(v[0]);
@@ -267,8 +284,10 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
     __syncthreads();
 
     // ---- per-super-row sums of the staged values (full row, and the window's tail part)
-    const int tail_elems = g.tail_rows * Mp;
     for (int r = tid; r < nrows; r += NT) {
+        if constexpr (LIST)
+            if (rm[r] >= 0x7f800000u)
+                *s_odd = 1u;
         float full = 0.0f, part = 0.0f;
         for (int c = 0; c < CPR; ++c) {
             const uint4 q4 = seg[r * CPRP + c];
@@ -429,9 +448,10 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
             api += PD * HBT * 64;
         }
     }
+    const bool odd = LIST && *s_odd != 0u;
     if constexpr (WH == 1) {
         if (!wave_active)
-            return;
+            return odd;
     }
 
     // ---- epilogue (weights from LDS when CL, else from L2)
@@ -451,9 +471,10 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
         bool mine = true;
         if constexpr (LIST) {
             unsigned wm = 0u;
-            for (int qq = 0; qq < Q; ++qq)
+            for (int qq = 0; qq < Q - 1; ++qq)
                 wm = max(wm, rm[row0 + qq]);
-            mine = split_outside(wm);
+            wm = max(wm, rt[row0 + Q - 1]);
+            mine = split_outside(wm) && (wm >= 0x7f800000u) == raw_values;
         }
         if (storer && half == 0 && n < nv && mine) {
             const int64_t w = p.woff[s] + k0 + n;
@@ -464,6 +485,7 @@ __device__ __forceinline__ void score_mfma_tile(const ScoreParams &p, const Mfma
                 p.flags[w] = sc > p.threshold ? 1 : 0;
         }
     });
+    return odd;
 }
 
 template <int DT, int HB, int NBW, int WH, int NW, int ACT, bool CL>
@@ -478,7 +500,7 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
     const int64_t k0 = (b - p.tile_off[s]) * NB;
     const int64_t ns = p.woff[s + 1] - p.woff[s];
     const int nv = static_cast<int>(ns - k0 < NB ? ns - k0 : NB);
-    score_mfma_tile<DT, HB, NBW, WH, NW, ACT, CL, false>(p, g, s, k0, nv);
+    score_mfma_tile<DT, HB, NBW, WH, NW, ACT, CL, false>(p, g, s, k0, nv, true);
 }
 
 // The tiles that k_score_split marked (of list_nb <= NB windows each). A block looks through the
@@ -504,8 +526,13 @@ __global__ __launch_bounds__(256, 1) void k_score_mfma_list(ScoreParams p, MfmaS
                 const int64_t k0 = (b - p.tile_off[s]) * g.list_nb;
                 const int64_t ns = p.woff[s + 1] - p.woff[s];
                 const int nv = static_cast<int>(ns - k0 < g.list_nb ? ns - k0 : g.list_nb);
-                score_mfma_tile<ENOVA_F32, HB, NBW, 1, 4, ACT, true, true>(p, g, s, k0, nv);
-                __syncthreads();   // the tile's LDS is written again
+                bool raw = false, odd;
+#pragma unroll 1
+                do {
+                    odd = score_mfma_tile<ENOVA_F32, HB, NBW, 1, 4, ACT, true, true>(p, g, s, k0, nv, raw) && !raw;
+                    raw = true;
+                    __syncthreads();   // the tile's LDS is written again
+                } while (odd);
             }
     }
 }
@@ -584,7 +611,7 @@ static ScoreKernel pick_list(const Geometry &g)
 
 size_t score_list_lds(const Geometry &g)
 {
-    return g.lds_bytes + sizeof(unsigned) * static_cast<size_t>(g.Nb + g.Q - 1 + g.spare);
+    return g.lds_bytes + sizeof(unsigned) * ((g.W % g.S == 0 ? 1 : 2) * static_cast<size_t>(g.Nb + g.Q - 1 + g.spare) + 1);
 }
 
 hipError_t prepare_score_list(const Geometry &g)

@@ -21,8 +21,9 @@
 // off exactly with the bias (one fused multiply-add). A window whose largest |v| exceeds
 // kSplitMax (or is not finite), or is not zero but below kSplitMin, does not fit that range: it
 // is left to k_score_mfma's list mode, which evaluates the marked tiles in fp32 and writes
-// those windows only. The choice depends on the window's own steps alone, so scores stay
-// independent of batch composition.
+// those windows only. The choice depends on the window's own steps alone (a super-row's maximum is
+// kept for all its steps and for those that a window ends with), so scores stay independent of what
+// else a stream or a batch holds.
 //
 // The posterior heads and the decoder's hidden layer chain from the accumulators as in the other
 // kernels, on 32x32x16 bf16 ops: activations, mu and weights as three bf16 parts each (24 bits,
@@ -72,7 +73,8 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
     const int nrows = nv + Q - 1 + g.spare;
     // LDS: the segment [rows][P] chunks (chunk c of a row: hi at 2c, lo at 2c + 1; P is odd so that
     // consecutive rows start in different banks), then per column of a super-row its mean, scaled
-    // 1/std and offset, per row the sums and the largest |v|, and b1, its row scale, bd1, u, biases
+    // 1/std and offset, per row the sums and the largest |v| (both for the whole row and for the steps
+    // that a window's last row has; one maximum where these are all), and b1, its row scale, bd1, u, biases
     uint4 *seg = lds;
     const int rows_alloc = NB + Q - 1 + g.spare;
     const size_t seg_chunks = static_cast<size_t>(rows_alloc) * P;
@@ -84,7 +86,9 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
     float *rs = reinterpret_cast<float *>(coff + SMp);
     float *ps = rs + rows_alloc;
     unsigned *rm = reinterpret_cast<unsigned *>(ps + rows_alloc);
-    float *s_b1 = reinterpret_cast<float *>(rm + rows_alloc);
+    const bool whole = g.tail_rows == S;
+    unsigned *rt = whole ? rm : rm + rows_alloc;
+    float *s_b1 = reinterpret_cast<float *>(rt + rows_alloc);
     float *s_sc = s_b1 + HP, *s_bd1 = s_sc + HP, *s_u = s_bd1 + HP, *s_bh = s_u + HP;
     int *s_mark = reinterpret_cast<int *>(s_bh + 32);
 
@@ -112,13 +116,14 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
         }
     }
     for (int r = tid; r < nrows; r += NT)
-        rm[r] = 0u;
+        rm[r] = rt[r] = 0u;
     __syncthreads();
 
     // ---- stage: super-row r of the tile covers stream steps (k0 + r)*S .. +S-1
     const int64_t eavail = (T - k0 * S) * M;       // stream elements from super-row 0 on
     const int64_t ebase = (srow + k0 * S) * M;     // element index of super-row 0
     const bool linear = Mp == M && ebase % 4 == 0 && reinterpret_cast<uintptr_t>(p.x) % 16 == 0;
+    const int tail_elems = g.tail_rows * Mp;
     const float *x = static_cast<const float *>(p.x);
     constexpr int SU = 4;                          // chunks (32 bytes) in flight per thread
     const int n_chunks = nrows * CPR;
@@ -165,27 +170,30 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
                         v[e] = (x[ebase + rel + off] - cmean[c * 8 + e]) * crinv[c * 8 + e];
                 }
             }
-            float big = 0.0f;
-            bool bad = false;
+            unsigned big = 0u, bits[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float a = fabsf(v[e]);
-                const bool out = !(a <= kSplitMax);
-                bad |= out;
-                v[e] = out ? 0.0f : v[e];
-                big = fmaxf(big, out ? 0.0f : a);
+                bits[e] = __float_as_uint(v[e]) & 0x7fffffffu;
+                big = max(big, bits[e]);
+                v[e] = bits[e] > __float_as_uint(kSplitMax) ? 0.0f : v[e];
             }
             v8h hi, lo;
             split_f16x8(v, hi, lo);
             seg[r * P + 2 * c] = __builtin_bit_cast(uint4, hi);
             seg[r * P + 2 * c + 1] = __builtin_bit_cast(uint4, lo);
-            atomicMax(&rm[r], bad ? 0x7f800000u : __float_as_uint(big));
+            atomicMax(&rm[r], big);
+            if (!whole && c * 8 < tail_elems) {
+                unsigned tail = 0u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    tail = c * 8 + e < tail_elems ? max(tail, bits[e]) : tail;
+                atomicMax(&rt[r], tail);
+            }
         }
     }
     __syncthreads();
 
     // ---- per-super-row sums of the staged values (full row, and the window's tail part)
-    const int tail_elems = g.tail_rows * Mp;
     for (int r = tid; r < nrows; r += NT) {
         float full = 0.0f, part = 0.0f;
         for (int c = 0; c < CPR; ++c) {
@@ -311,7 +319,7 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
             }
             if (((Q - 1) & 1) == half) {
                 vsum += ps[row0 + Q - 1];
-                wm = max(wm, rm[row0 + Q - 1]);
+                wm = max(wm, rt[row0 + Q - 1]);
             }
             vsum += __shfl_xor(vsum, 32);
             wm = max(wm, static_cast<unsigned>(__shfl_xor(static_cast<int>(wm), 32)));
@@ -363,12 +371,14 @@ int split_nb(int hbt, bool small)
     }
 }
 
-size_t split_lds(const SplitGeometry &sg, int hbt, int nb)
+size_t split_lds(const Geometry &g, const SplitGeometry &sg, int nb)
 {
+    const int hbt = g.HB;
     const size_t rows = static_cast<size_t>(nb + sg.Q - 1 + sg.spare);
+    const size_t per_row = g.W % g.S == 0 ? 3 : 4;   // floats: two sums, one or two maxima
     const size_t xchg = hbt == 8 ? epi_xchg_floats(4, nb / 64) * sizeof(float) : 0;
     const size_t hp = 32 * static_cast<size_t>(hbt);
-    return std::max(rows * sg.P * 16, xchg) + 3 * sizeof(float) * 8 * sg.CPR + 3 * sizeof(float) * rows +
+    return std::max(rows * sg.P * 16, xchg) + 3 * sizeof(float) * 8 * sg.CPR + per_row * sizeof(float) * rows +
            sizeof(float) * (4 * hp + 32 + 4);
 }
 
@@ -395,8 +405,8 @@ SplitGeometry plan_split(const Geometry &g)
     s.spare = static_cast<int>((kc + 1) / cpr - s.Q + 2);
     s.nb_small = split_nb(g.HB, true);
     s.nb_large = split_nb(g.HB, false);
-    s.lds_small = split_lds(s, g.HB, s.nb_small);
-    s.lds_large = split_lds(s, g.HB, s.nb_large);
+    s.lds_small = split_lds(g, s, s.nb_small);
+    s.lds_large = split_lds(g, s, s.nb_large);
     // the large tile where two blocks fit a compute unit's LDS, else the small one alone
     if (s.lds_large > kLdsLimit / 2) {
         s.nb_large = s.nb_small;

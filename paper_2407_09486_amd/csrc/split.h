@@ -24,10 +24,10 @@ constexpr float kSplitMax = 64000.0f, kSplitMin = 4.0f;
 // kSplitScale times (x - mean) * (1 / std)).
 __device__ __forceinline__ float split_rinv(float std) { return (1.0f / std) * kSplitScale; }
 
-// wm: the bits of a window's largest scaled |v|, infinity if one is out of range or not finite.
+// wm: the bits of a window's largest scaled |v| (an infinity's or a NaN's where one is not finite).
 __device__ __forceinline__ bool split_outside(unsigned wm)
 {
-    return wm != 0u && (wm >= 0x7f800000u || __uint_as_float(wm) < kSplitMin);
+    return wm > __builtin_bit_cast(unsigned, kSplitMax) || (wm != 0u && wm < __builtin_bit_cast(unsigned, kSplitMin));
 }
 
 // A tile's entry in the tile map once some of its windows are left to the fp32 kernel.

@@ -161,3 +161,39 @@ def test_small_inputs_under_large_weights(small, big, other, where):
     check_scores(sc[few], o_sc[few], "f32", where)
     check_md(md[few], o_md[few], info["md_scale"][few], "f32", where)
     det.close()
+
+
+@pytest.mark.parametrize("M,W,S,H", [(7, 5, 2, 64), (4, 4, 8, 32), (5, 9, 4, 128), (3, 10, 8, 256), (16, 7, 3, 100)])
+def test_steps_beside_a_window_do_not_count(M, W, S, H):
+    """With W no multiple of S (or below it), a window's last super-row holds steps behind the window. Large,
+    infinite and NaN ones there leave it finite, as the vector kernel has it, and its bits those of the
+    stream cut off at its end, also where the window itself is out of the range."""
+    cfg = _cfg(M, W, S, H, n=1)
+    rng = np.random.default_rng(M * W)
+    K = 150
+    T = W + (K - 1) * S + S
+    x = rng.standard_normal((T, M)).astype(np.float32)
+    tail = W - (W - 1) // S * S                          # steps of the last super-row inside the window
+    behind = [(k * S + W + (S - tail) // 2, k) for k in range(10, K - 1, 10)]
+    for i, (t, k) in enumerate(behind):
+        x[t, i % M] = [1e6, np.inf, np.nan, -np.inf, 4500.0][i % 5]
+        if i % 2:
+            x[k * S, 0] = 2e5                             # window k is out of the range by itself
+    w = wl.from_arrays(cfg, x, np.array([0, T]))
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    ref = (np.zeros((1, M)), np.ones((1, M)))
+    log(f"[split] steps beside a window M={M} W={W} S={S} H={H}")
+    det, valu = detector(cfg, weights), detector(cfg, weights, "valu")
+    (sc, md, _, _), (rsc, rmd, _, _) = gpu_score(det, w, pad=16, ref=ref), gpu_score(valu, w, ref=ref)
+    own = np.array([np.isfinite(x[k * S:k * S + W]).all() for k in range(len(sc))])
+    assert own[[k for _, k in behind]].all() and np.array_equal(np.isfinite(rmd), own)
+    assert np.array_equal(np.isnan(md) | np.isinf(md), ~own)
+    fin = own & np.isfinite(rsc) & (np.abs(rsc) < 1e30)
+    assert np.array_equal(np.isinf(sc[own]), np.isinf(rsc[own])) and not np.any(np.isnan(sc[own]))
+    np.testing.assert_allclose(sc[fin], rsc[fin], rtol=1e-5, atol=1e-6)
+    for t, k in behind:
+        cut = wl.from_arrays(cfg, x[:k * S + W], np.array([0, k * S + W]))
+        a, b, _, _ = gpu_score(det, cut, ref=ref)
+        assert len(a) == k + 1 and a[k] == sc[k] and b[k] == md[k], (k, a[k], sc[k])
+    det.close()
+    valu.close()
