@@ -99,7 +99,7 @@ struct enova_detector_s {
     size_t stats_cap = 0;         // floats
     int64_t *tiles = nullptr;
     size_t tiles_cap = 0;         // entries
-    int *tile_map = nullptr;      // stream of each matrix-core block
+    int *tile_map = nullptr;      // stream of each matrix-core block, and the split kernel's marks
     size_t tile_map_cap = 0;      // entries
     int64_t *cal = nullptr;
     size_t cal_cap = 0;
@@ -1033,13 +1033,20 @@ namespace {
 
 // The scoring path's workspace: reference statistics [2][n][M] floats (when the caller gives
 // none) and their chunk sums, the matrix-core kernel's first tile of each stream [n+1] and stream
-// of each block [grid].
+// of each block [grid], with the split kernel's marks behind it.
 struct ScoreWork {
     float *stats = nullptr;
     double *part = nullptr;
     int64_t *tiles = nullptr;
     int *tile_map = nullptr;
 };
+
+// Entries of the tile map (and of the marks: a tile holds a window at the least).
+size_t map_ints(int64_t grid, int64_t n_windows, bool split)
+{
+    const size_t map = static_cast<size_t>(grid > 0 ? grid : 1);
+    return split ? map + 1 + static_cast<size_t>(std::min(grid, n_windows)) : map;
+}
 
 // Floats of the statistics and of their chunk sums behind them (on a 16-byte boundary).
 size_t stats_floats(int32_t n, int M, size_t *o_part)
@@ -1050,8 +1057,8 @@ size_t stats_floats(int32_t n, int M, size_t *o_part)
 
 // Bytes of the fixed-scratch layout of that workspace, each part on a 256-byte boundary. The chunk
 // sums come last and only where they still fit the scratch (*o_part = 0: one block per stream).
-size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, bool stats, size_t *o_tiles,
-                     size_t *o_map, size_t *o_part)
+size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, int64_t n_windows, bool split, bool stats,
+                     size_t *o_tiles, size_t *o_map, size_t *o_part)
 {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     size_t o = stats ? up(2 * static_cast<size_t>(n) * g.M * sizeof(float)) : 0;
@@ -1060,7 +1067,7 @@ size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, bool 
         o += up((static_cast<size_t>(n) + 1) * sizeof(int64_t));
     *o_map = o;
     if (kind == 2)
-        o += up(static_cast<size_t>(grid > 0 ? grid : 1) * sizeof(int));
+        o += up(map_ints(grid, n_windows, split) * sizeof(int));
     *o_part = 0;
     const size_t part = stats ? stat_part_bytes(n, g.M) : 0;
     if (part > 0 && o > 0 && o + part <= kScratchBytes) {
@@ -1095,12 +1102,15 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     int nb = split ? det->sg.nb(n_windows, n) : g.Nb;
     int64_t grid = det->kind == 2 ? (n_windows + nb - 1) / nb + n : 0;
     size_t o_tiles = 0, o_map = 0, o_part = 0;
-    size_t need = noalloc ? noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part) : 0;
-    if (split && (grid > 0x7fffffffLL || need > kScratchBytes)) {
+    auto layout = [&]() {
+        return noalloc ? noalloc_bytes(g, det->kind, n, grid, n_windows, split, !ref_mean, &o_tiles, &o_map, &o_part) : 0;
+    };
+    size_t need = layout();
+    if (split && (grid > kMaxMarked || need > kScratchBytes)) {
         split = false;
         nb = g.Nb;
         grid = (n_windows + nb - 1) / nb + n;
-        need = noalloc ? noalloc_bytes(g, det->kind, n, grid, !ref_mean, &o_tiles, &o_map, &o_part) : 0;
+        need = layout();
     }
     if (grid > 0x7fffffffLL)
         return fail(ENOVA_EUNSUPPORTED, "too many tiles (%lld)", static_cast<long long>(grid));
@@ -1139,7 +1149,7 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         if (st == ENOVA_OK && det->kind == 2) {
             st = ensure(&det->tiles, &det->tiles_cap, static_cast<size_t>(n) + 1);
             if (st == ENOVA_OK)
-                st = ensure(&det->tile_map, &det->tile_map_cap, static_cast<size_t>(grid > 0 ? grid : 1));
+                st = ensure(&det->tile_map, &det->tile_map_cap, map_ints(grid, n_windows, split));
         }
         if (st != ENOVA_OK)
             return st;
@@ -1205,7 +1215,8 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     p.flags = out_flags;
     if (det->kind == 2) {
         p.tile_off = wk.tiles;
-        e = launch_prep_map(g, x, soff, wk.tiles, n, grid, wk.tile_map, own_mean, own_std, wk.part, stream);
+        p.marks = split ? reinterpret_cast<unsigned *>(wk.tile_map + grid) : nullptr;
+        e = launch_prep_map(g, x, soff, wk.tiles, n, grid, wk.tile_map, p.marks, own_mean, own_std, wk.part, stream);
         if (e != hipSuccess)
             return hip_fail(e, "tile map kernel");
         p.tile_stream = wk.tile_map;
@@ -1313,7 +1324,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         if ((e = launch_prep_scan(g, x, soff, woff, n, kExtFusedNb, tiles, own_mean, own_std, part, stream)) !=
             hipSuccess)
             return hip_fail(e, "tile scan and reference statistics kernels");
-        if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, own_mean, own_std, part, stream)) != hipSuccess)
+        if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, nullptr, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
         const int decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
         if (split) {

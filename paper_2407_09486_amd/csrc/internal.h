@@ -106,8 +106,10 @@ struct ScoreParams {
     const int64_t *soff;
     const int64_t *woff;
     const int64_t *tile_off;     // matrix-core kernel only: first tile of each stream
-    int *tile_stream;            // matrix-core kernel only: stream of each block (-1: none; the split
-                                 // kernel marks tiles it leaves windows of to the fp32 kernel)
+    const int *tile_stream;      // matrix-core kernel only: stream of each block (-1: none)
+    // split kernel: the tiles with windows it leaves to the fp32 kernel, marks[0] of them (cleared with
+    // the tile map), each as tile << 4 | parts of kListNb windows that hold some
+    unsigned *marks;
     int n_streams;
     int64_t n_windows;
     const float *mean;
@@ -168,7 +170,10 @@ hipError_t prepare_score_split(const Geometry &g, const SplitGeometry &sg);
 hipError_t launch_score_split(const Geometry &g, const SplitGeometry &sg, const ScoreParams &p, int nb, int64_t grid,
                               hipStream_t st);
 // The fp32 kernel over the tiles (of nb windows) that the split kernel marked, writing only their
-// windows outside the split's range; score_list_lds is its dynamic LDS.
+// windows outside the split's range; score_list_lds is its dynamic LDS. A mark holds four parts of
+// kListNb windows and a tile index below kMaxMarked.
+constexpr int kListNb = 128;
+constexpr int64_t kMaxMarked = 1LL << 28;
 size_t score_list_lds(const Geometry &g);
 hipError_t prepare_score_list(const Geometry &g);
 hipError_t launch_score_list(const Geometry &g, const ScoreParams &p, int nb, int64_t grid, hipStream_t st);
@@ -178,11 +183,13 @@ size_t stat_part_bytes(int n, int M);
 hipError_t launch_ref_stats(const Geometry &g, const void *x, const int64_t *soff, int n,
                             float *mean, float *std, double *part, hipStream_t st);
 // The two launches that head a scoring pass: the tiles' scan (launch_stream_scan) with the
-// reference statistics unless mean is NULL, then the tile map with the statistics' last step.
+// reference statistics unless mean is NULL, then the tile map with the statistics' last step and the
+// cleared count of marks (NULL: none).
 hipError_t launch_prep_scan(const Geometry &g, const void *x, const int64_t *soff, const int64_t *woff, int n,
                             int div, int64_t *tile_off, float *mean, float *std, double *part, hipStream_t st);
 hipError_t launch_prep_map(const Geometry &g, const void *x, const int64_t *soff, const int64_t *tile_off, int n,
-                           int64_t grid, int *map, float *mean, float *std, const double *part, hipStream_t st);
+                           int64_t grid, int *map, unsigned *marks, float *mean, float *std, const double *part,
+                           hipStream_t st);
 // out[s] = sum_{r<s} ceil(windows of stream r / div), n+1 entries.
 hipError_t launch_stream_scan(const Geometry &g, const int64_t *soff, const int64_t *woff, int n,
                               int div, int64_t *out, hipStream_t st);

@@ -318,9 +318,11 @@ struct StatFinish {
 };
 
 __global__ __launch_bounds__(256) void k_tile_map(const int64_t *__restrict__ tile_off, int n, int64_t grid,
-                                                  int *__restrict__ map, StatFinish f)
+                                                  int *__restrict__ map, unsigned *__restrict__ marks, StatFinish f)
 {
     const int64_t first = blockIdx.x * 256LL + threadIdx.x, step = static_cast<int64_t>(gridDim.x) * 256;
+    if (marks && first == 0)
+        *marks = 0u;
     if (f.part)
         for (int64_t i = first; i < static_cast<int64_t>(n) * f.M; i += step) {
             if (f.dtype == ENOVA_F32)
@@ -449,7 +451,8 @@ hipError_t launch_prep_scan(const Geometry &g, const void *x, const int64_t *sof
 }
 
 hipError_t launch_prep_map(const Geometry &g, const void *x, const int64_t *soff, const int64_t *tile_off, int n,
-                           int64_t grid, int *map, float *mean, float *std, const double *part, hipStream_t st)
+                           int64_t grid, int *map, unsigned *marks, float *mean, float *std, const double *part,
+                           hipStream_t st)
 {
     if (grid <= 0)
         return hipSuccess;
@@ -462,13 +465,15 @@ hipError_t launch_prep_map(const Geometry &g, const void *x, const int64_t *soff
     int64_t blocks = (items + 255) / 256;
     if (blocks > 65536)
         blocks = 65536;
-    hipLaunchKernelGGL(k_tile_map, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, tile_off, n, grid, map, f);
+    hipLaunchKernelGGL(k_tile_map, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, tile_off, n, grid, map, marks,
+                       f);
     return hipGetLastError();
 }
 
 hipError_t launch_tile_map(const int64_t *tile_off, int n, int64_t grid, int *map, hipStream_t st)
 {
-    return launch_prep_map(Geometry{}, nullptr, nullptr, tile_off, n, grid, map, nullptr, nullptr, nullptr, st);
+    return launch_prep_map(Geometry{}, nullptr, nullptr, tile_off, n, grid, map, nullptr, nullptr, nullptr, nullptr,
+                           st);
 }
 
 hipError_t launch_flag(const float *scores, int64_t n, float thr, uint8_t *flags, hipStream_t st)

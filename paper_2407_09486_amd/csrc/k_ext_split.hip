@@ -37,6 +37,10 @@ namespace {
 constexpr int kNb = kExtFusedNb;     // windows per tile
 constexpr int kNbw = 2;              // 32-window blocks per wave
 
+// A tile's entry in the tile map once some of its windows are left to k_ext_list.
+__host__ __device__ __forceinline__ int split_mark(int s) { return -2 - s; }
+__host__ __device__ __forceinline__ int split_marked(int entry) { return -2 - entry; }   // the stream, or < 0
+
 // One metric of one window: v = (x - k) * ca, k the mean, scaled by kSplitScale, and the bits of its
 // largest |v| (infinity when out of range or not finite). x(t), t < W: the metric's values. (With
 // v = x * ca + cb the rounding of cb, at the scale of mean / std, doubles that of the mean.)

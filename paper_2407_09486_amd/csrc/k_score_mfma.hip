@@ -47,8 +47,7 @@ struct MfmaShape {
     int spare;       // staged super-rows after a tile's last window's Q - 1
     int tail_rows;   // steps of the window's last super-row that belong to the window
     float inv_d;
-    int64_t list_grid;   // list mode: entries of the tile map, and windows of a marked tile
-    int list_nb;
+    int list_nb;     // list mode: windows of a marked tile
 };
 
 // Wave layout: the NW waves form WH groups along the hidden rows and NW/WH groups along the
@@ -95,8 +94,12 @@ __device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const Mfma
     constexpr int N_XCHG = WH > 1 ? epi_xchg_floats(NW, NBW) : 0;   // floats
     float *s_whp = reinterpret_cast<float *>(lds);
     float *s_wd1p = s_whp + N_WHP;
-    const float *e_whp = CL ? s_whp : p.whp;      // epilogue fragments: the copied block, or L2
-    const float *e_wd1p = CL ? s_wd1p : p.wd1p;
+    const uint4 *w1p = p.w1p;
+    const float *g_whp = p.whp, *g_wd1p = p.wd1p;
+    if constexpr (LIST)   // or loads of weights move out of the list's loops, into 400 spilled registers
+        asm volatile("" : "+s"(w1p), "+s"(g_whp), "+s"(g_wd1p));
+    const float *e_whp = CL ? s_whp : g_whp;      // epilogue fragments: the copied block, or L2
+    const float *e_wd1p = CL ? s_wd1p : g_wd1p;
     uint4 *seg = lds + N_CONST / 4;
     const int rows_alloc = NB + Q - 1 + g.spare;
     const size_t seg_chunks = static_cast<size_t>(rows_alloc) * CPRP;
@@ -179,7 +182,7 @@ __device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const Mfma
     // ones are normalised (one load per loop trip would serialise a full HBM round trip per
     // chunk). Its chunks are tid + i*NT; their (row, column) advance by (NT / CPR, NT % CPR)
     // with a carry instead of a division each.
-    constexpr int SU = 8;
+    constexpr int SU = LIST ? 2 : 8;               // (the list's blocks hide the latency of one another)
     const int n_chunks = nrows * CPR;
     const int dr = NT / CPR, dc = NT - (NT / CPR) * CPR;
     int cr = tid / CPR, ccol = tid - (tid / CPR) * CPR;
@@ -334,10 +337,10 @@ __device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const Mfma
             for (int r = 0; r < 16; ++r)
                 acc[hb][nb][r] = 0.0f;
 
-    const bool wave_active = wn * NBW * 32 < nv;
+    bool wave_active = wn * NBW * 32 < nv;
     const int nsteps = g.KC / 2;                 // even: KC is a multiple of 4
     // A fragments of step i: w1p[(i * HBT + hb) * 64 + lane]; this wave's blocks start at wh * HB
-    const uint4 *ap = p.w1p + wh * HB * 64 + lane;
+    const uint4 *ap = w1p + wh * HB * 64 + lane;
     // LDS chunk offset of this lane's chunk kappa = 2*i + half inside a window:
     // (kappa / CPR) * CPRP + kappa % CPR, advanced without branches
     const int dpitch = CPRP - CPR;
@@ -376,6 +379,22 @@ __device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const Mfma
         }
     };
     __syncthreads();
+    bool mine[NBW];
+    if constexpr (LIST) {
+        bool any = false;
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb) {
+            const int n = wn * NBW * 32 + nb * 32 + (lane & 31);
+            const int row0 = rb[nb] / CPRP;
+            unsigned wm = rt[row0 + Q - 1];
+#pragma unroll 8
+            for (int qq = 0; qq < Q - 1; ++qq)
+                wm = max(wm, rm[row0 + qq]);
+            mine[nb] = n < nv && split_outside(wm) && (wm >= 0x7f800000u) == raw_values;
+            any |= mine[nb];
+        }
+        wave_active = __any(any);
+    }
     if (wave_active) {
         // W1 fragments run PD steps ahead in a register ring, window fragments PB steps ahead
         // (ring of 2*PB) from LDS: an fp32 step is 4*HB*NBW matrix ops, a bf16 step only
@@ -463,20 +482,18 @@ __device__ __forceinline__ bool score_mfma_tile(const ScoreParams &p, const Mfma
         const int n = wn * NBW * 32 + nb * 32 + (lane & 31);
         float vsum = 0.0f;
         const int row0 = rb[nb] / CPRP;
-        for (int qq = half; qq < Q - 1; qq += 2)
-            vsum += rs[row0 + qq];
+        if constexpr (LIST) {
+#pragma unroll 8
+            for (int qq = half; qq < Q - 1; qq += 2)
+                vsum += rs[row0 + qq];
+        } else {
+            for (int qq = half; qq < Q - 1; qq += 2)
+                vsum += rs[row0 + qq];
+        }
         if (((Q - 1) & 1) == half)
             vsum += ps[row0 + Q - 1];
         vsum += __shfl_xor(vsum, 32);
-        bool mine = true;
-        if constexpr (LIST) {
-            unsigned wm = 0u;
-            for (int qq = 0; qq < Q - 1; ++qq)
-                wm = max(wm, rm[row0 + qq]);
-            wm = max(wm, rt[row0 + Q - 1]);
-            mine = split_outside(wm) && (wm >= 0x7f800000u) == raw_values;
-        }
-        if (storer && half == 0 && n < nv && mine) {
+        if (storer && half == 0 && n < nv && (!LIST || mine[nb])) {
             const int64_t w = p.woff[s] + k0 + n;
             p.scores[w] = sc;
             if (p.md)
@@ -503,37 +520,38 @@ void k_score_mfma(ScoreParams p, MfmaShape g)
     score_mfma_tile<DT, HB, NBW, WH, NW, ACT, CL, false>(p, g, s, k0, nv, true);
 }
 
-// The tiles that k_score_split marked (of list_nb <= NB windows each). A block looks through the
-// entries blockIdx.x, blockIdx.x + gridDim.x, ... of the tile map, 256 at a time, so neighbouring
-// marked tiles go to different blocks; without a mark the kernel costs its launch and one load.
-template <int HB, int NBW, int ACT>
-__global__ __launch_bounds__(256, 1) void k_score_mfma_list(ScoreParams p, MfmaShape g)
+// The windows that k_score_split left: of the marked tiles (of list_nb windows each) the parts of kListNb
+// windows that hold some, dealt out evenly over the blocks; a wave takes 32 windows, so that a part's few
+// do not leave three waves idle beside one. Without a mark the kernel costs its launch and one load.
+// Its parts and the skipped waves are for data that leaves the range for long, as a metric does that was
+// constant over the reference prefix. 64 streams x 16384 steps x 8 metrics, W = 64, H = 64, a whole call (0.26 ms
+// in range, 0.62 when every window took k_score_mfma): half of the windows out 0.97 -> 0.60 ms, a NaN every 64
+// steps of half the stream 0.97 -> 0.60, every 1024 0.97 -> 0.35; every window out 0.76. H = 128, 16 metrics
+// (0.73 and 2.24): half 2.98 -> 1.70, every window 2.49.
+template <int HB, int ACT>
+__global__ __launch_bounds__(256, 2) void k_score_mfma_list(ScoreParams p, MfmaShape g)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t step = gridDim.x;
-    for (int64_t first = blockIdx.x; first < g.list_grid; first += 256 * step) {
-        uint64_t mask[4];   // the same in every wave
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t i = first + (q * 64 + lane) * step;
-            mask[q] = __ballot(i < g.list_grid && split_marked(p.tile_stream[i]) >= 0);
-        }
+    const int64_t count = p.marks[0];
+    const int64_t items = count * ((g.list_nb + kListNb - 1) / kListNb);
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        const int part = static_cast<int>(i / count);
+        const unsigned mark = p.marks[1 + i - part * count];
+        if (!((mark >> part) & 1u))
+            continue;
+        const int64_t b = mark >> 4;
+        const int s = p.tile_stream[b];
+        const int64_t k0 = (b - p.tile_off[s]) * g.list_nb + part * kListNb;
+        const int64_t ns = p.woff[s + 1] - p.woff[s];
+        int most = g.list_nb - part * kListNb;
+        most = most < kListNb ? most : kListNb;
+        const int nv = static_cast<int>(ns - k0 < most ? ns - k0 : most);
+        bool raw = false, odd;
 #pragma unroll 1
-        for (int q = 0; q < 4; ++q)
-            for (uint64_t m = mask[q]; m; m &= m - 1) {
-                const int64_t b = first + (q * 64 + __builtin_ctzll(m)) * step;
-                const int s = split_marked(p.tile_stream[b]);
-                const int64_t k0 = (b - p.tile_off[s]) * g.list_nb;
-                const int64_t ns = p.woff[s + 1] - p.woff[s];
-                const int nv = static_cast<int>(ns - k0 < g.list_nb ? ns - k0 : g.list_nb);
-                bool raw = false, odd;
-#pragma unroll 1
-                do {
-                    odd = score_mfma_tile<ENOVA_F32, HB, NBW, 1, 4, ACT, true, true>(p, g, s, k0, nv, raw) && !raw;
-                    raw = true;
-                    __syncthreads();   // the tile's LDS is written again
-                } while (odd);
-            }
+        do {
+            odd = score_mfma_tile<ENOVA_F32, HB, 1, 1, 4, ACT, false, true>(p, g, s, k0, nv, raw) && !raw;
+            raw = true;
+            __syncthreads();   // the tile's LDS is written again
+        } while (odd);
     }
 }
 
@@ -543,10 +561,10 @@ template <int ACT>
 ScoreKernel pick_list(int hb)
 {
     switch (hb) {
-    case 1: return k_score_mfma_list<1, 4, ACT>;
-    case 2: return k_score_mfma_list<2, 4, ACT>;
-    case 4: return k_score_mfma_list<4, 2, ACT>;
-    case 8: return k_score_mfma_list<8, 1, ACT>;
+    case 1: return k_score_mfma_list<1, ACT>;
+    case 2: return k_score_mfma_list<2, ACT>;
+    case 4: return k_score_mfma_list<4, ACT>;
+    case 8: return k_score_mfma_list<8, ACT>;
     default: return nullptr;
     }
 }
@@ -611,7 +629,9 @@ static ScoreKernel pick_list(const Geometry &g)
 
 size_t score_list_lds(const Geometry &g)
 {
-    return g.lds_bytes + sizeof(unsigned) * ((g.W % g.S == 0 ? 1 : 2) * static_cast<size_t>(g.Nb + g.Q - 1 + g.spare) + 1);
+    const size_t rows = static_cast<size_t>(kListNb + g.Q - 1 + g.spare);
+    const size_t per_row = g.W % g.S == 0 ? 3 : 4;   // floats: two sums, one or two maxima
+    return rows * g.CPRP * 16 + sizeof(float) * (3 * static_cast<size_t>(g.CPR) * g.epc + per_row * rows + 3 * static_cast<size_t>(g.Hp) + 32 + 1);
 }
 
 hipError_t prepare_score_list(const Geometry &g)
@@ -628,13 +648,13 @@ hipError_t launch_score_list(const Geometry &g, const ScoreParams &p, int nb, in
     if (grid <= 0)
         return hipSuccess;
     ScoreKernel k = pick_list(g);
-    if (!k || nb > g.Nb)
+    if (!k)
         return hipErrorInvalidValue;
     MfmaShape sh = shape_of(g);
-    sh.list_grid = grid;
     sh.list_nb = nb;
-    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid < 512 ? grid : 512)), dim3(256), score_list_lds(g), st, p,
-                       sh);
+    const int64_t items = grid * ((nb + kListNb - 1) / kListNb);
+    const int64_t most = g.HB == 1 ? 1024 : g.HB == 2 ? 768 : 512;   // what the chip holds at once
+    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(std::min(items, most))), dim3(256), score_list_lds(g), st, p, sh);
     return hipGetLastError();
 }
 

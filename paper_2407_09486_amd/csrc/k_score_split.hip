@@ -20,8 +20,8 @@
 // and each row of W1 by a power of two that puts its largest weight into [2^13, 2^14); both come
 // off exactly with the bias (one fused multiply-add). A window whose largest |v| exceeds
 // kSplitMax (or is not finite), or is not zero but below kSplitMin, does not fit that range: it
-// is left to k_score_mfma's list mode, which evaluates the marked tiles in fp32 and writes
-// those windows only. The choice depends on the window's own steps alone (a super-row's maximum is
+// is left to k_score_mfma's list mode, which goes through the marked tiles in fp32. Waves without a
+// window of their own kind skip the products on both sides. The choice depends on the window's own steps alone (a super-row's maximum is
 // kept for all its steps and for those that a window ends with), so scores stay independent of what
 // else a stream or a batch holds.
 //
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
     unsigned *rt = whole ? rm : rm + rows_alloc;
     float *s_b1 = reinterpret_cast<float *>(rt + rows_alloc);
     float *s_sc = s_b1 + HP, *s_bd1 = s_sc + HP, *s_u = s_bd1 + HP, *s_bh = s_u + HP;
-    int *s_mark = reinterpret_cast<int *>(s_bh + 32);
+    int *s_mark = reinterpret_cast<int *>(s_bh + 32), *s_look = s_mark + 1;
 
     for (int i = tid; i < HP; i += NT) {
         s_b1[i] = p.b1[i];
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
     if (tid < 32)
         s_bh[tid] = p.bh[tid];
     if (tid == 0)
-        *s_mark = 0;
+        *s_mark = *s_look = 0;
     for (int j = tid; j < SMp; j += NT) {
         const int tt = j / Mp;
         const int m = j - tt * Mp;
@@ -209,6 +209,8 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
         }
         rs[r] = full;
         ps[r] = part;
+        if (split_outside(rm[r]) || split_outside(rt[r]))
+            *s_look = 1;   // else every window's largest |v| is in range, or zero
     }
 
     // ---- main contraction
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[hb][nb][r] = 0.0f;
-    const bool wave_active = wn * NBW * 32 < nv;
+    bool wave_active = wn * NBW * 32 < nv;
     // A fragments of step i, block hb, part q: w1x[((i * HBT + hb) * 2 + q) * 64 + lane]
     const uint4 *ap = p.w1x + (wh * HB * 2) * 64 + lane;
     constexpr int ASTEP = HBT * 2 * 64;
@@ -244,6 +246,37 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
         }
     };
     __syncthreads();
+    // windows outside the range (by lane, of each window block), and whether the wave, or the block, has
+    // any other
+    uint64_t outside[NBW];
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb)
+        outside[nb] = 0u;
+    if (*s_look) {
+        bool inside = false;
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb) {
+            const int n = wn * NBW * 32 + nb * 32 + (lane & 31);
+            unsigned wm = 0u;
+            const int row0 = rb[nb] / P;
+#pragma unroll 8
+            for (int qq = half; qq < Q - 1; qq += 2)
+                wm = max(wm, rm[row0 + qq]);
+            wm = max(wm, rt[row0 + Q - 1]);
+            wm = max(wm, static_cast<unsigned>(__shfl_xor(static_cast<int>(wm), 32)));
+            const bool out = split_outside(wm);
+            outside[nb] = __ballot(out);
+            inside |= n < nv && !out;
+            if (n < nv && out)
+                atomicOr(s_mark, 1 << (n / kListNb));
+        }
+        wave_active = __any(inside);
+        const bool any = __syncthreads_or(wave_active);
+        if (tid == 0 && *s_mark)
+            p.marks[1 + atomicAdd(p.marks, 1u)] = static_cast<unsigned>(b) << 4 | static_cast<unsigned>(*s_mark);
+        if (!any)
+            return;
+    }
     if (wave_active) {
         // W1 fragments run two steps ahead in a register ring (a step is 3*HB*NBW matrix ops of 32
         // cycles), window fragments one step; a packed zero step and the spare rows make every
@@ -311,35 +344,22 @@ __global__ __launch_bounds__(256, 2) void k_score_split(ScoreParams p, SplitShap
             // window mean of the staged inputs: super-rows rb .. rb+Q-1, the last one partially
             const int n = wn * NBW * 32 + nb * 32 + (lane & 31);
             float vsum = 0.0f;
-            unsigned wm = 0u;
             const int row0 = rb[nb] / P;
-            for (int qq = half; qq < Q - 1; qq += 2) {
+            for (int qq = half; qq < Q - 1; qq += 2)
                 vsum += rs[row0 + qq];
-                wm = max(wm, rm[row0 + qq]);
-            }
-            if (((Q - 1) & 1) == half) {
+            if (((Q - 1) & 1) == half)
                 vsum += ps[row0 + Q - 1];
-                wm = max(wm, rt[row0 + Q - 1]);
-            }
             vsum += __shfl_xor(vsum, 32);
-            wm = max(wm, static_cast<unsigned>(__shfl_xor(static_cast<int>(wm), 32)));
-            if (storer && half == 0 && n < nv) {
-                if (split_outside(wm)) {
-                    *s_mark = 1;
-                } else {
-                    const int64_t w = p.woff[s] + k0 + n;
-                    p.scores[w] = sc;
-                    if (p.md)
-                        p.md[w] = vsum * kSplitUnscale * g.inv_d - (dot + p.sum_bd2) * g.inv_d;
-                    if (p.write_flags)
-                        p.flags[w] = sc > p.threshold ? 1 : 0;
-                }
+            if (storer && half == 0 && n < nv && !((outside[nb] >> lane) & 1u)) {
+                const int64_t w = p.woff[s] + k0 + n;
+                p.scores[w] = sc;
+                if (p.md)
+                    p.md[w] = vsum * kSplitUnscale * g.inv_d - (dot + p.sum_bd2) * g.inv_d;
+                if (p.write_flags)
+                    p.flags[w] = sc > p.threshold ? 1 : 0;
             }
         });
     }
-    __syncthreads();
-    if (tid == 0 && *s_mark)
-        p.tile_stream[b] = split_mark(s);
 }
 
 using SplitKernel = void (*)(ScoreParams, SplitShape);

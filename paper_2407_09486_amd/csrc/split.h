@@ -30,10 +30,6 @@ __device__ __forceinline__ bool split_outside(unsigned wm)
     return wm > __builtin_bit_cast(unsigned, kSplitMax) || (wm != 0u && wm < __builtin_bit_cast(unsigned, kSplitMin));
 }
 
-// A tile's entry in the tile map once some of its windows are left to the fp32 kernel.
-__host__ __device__ __forceinline__ int split_mark(int s) { return -2 - s; }
-__host__ __device__ __forceinline__ int split_marked(int entry) { return -2 - entry; }   // the stream, or < 0
-
 __device__ __forceinline__ void split_f16x8(const float (&v)[8], v8h &hi, v8h &lo)
 {
 #pragma unroll

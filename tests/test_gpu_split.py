@@ -197,3 +197,33 @@ def test_steps_beside_a_window_do_not_count(M, W, S, H):
         assert len(a) == k + 1 and a[k] == sc[k] and b[k] == md[k], (k, a[k], sc[k])
     det.close()
     valu.close()
+
+
+@pytest.mark.parametrize("H", [32, 64, 128, 256])
+def test_marked_parts_of_large_tiles(H):
+    """Large tiles whose windows leave the range at the edges of their parts and waves, for one window, for a
+    wave's, for a whole tile and more, against the vector kernel."""
+    cfg = _cfg(2, 4, 1, H, n=2)
+    n = {32: 262200, 64: 262200, 128: 131200, 256: 65700}[H]
+    rng = np.random.default_rng(H)
+    x = rng.standard_normal((n + 40, 2)).astype(np.float32)
+    offs = np.array([0, n // 2 + 17, n + 40], np.int64)
+    for at in (0, 31, 127, 131, 255, 512 + 64, 1024 + 383, 2048 + 511, offs[1] - 1, offs[1] + 3, offs[2] - 4):
+        x[at, 1] = 1e5
+    for a, b in ((5000, 5200), (7168, 8192), (9000, 11000), (int(offs[1]) + 4096 - 3, int(offs[1]) + 4608)):
+        x[a:b, 0] = -7e4
+    x[12000:60000:300, 1] = np.nan
+    x[12100:60000:700, 0] = np.inf
+    w = wl.from_arrays(cfg, x, offs)
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    ref = (np.zeros((2, 2)), np.ones((2, 2)))
+    log(f"[split] marked parts H={H}, {n} windows")
+    det, valu = detector(cfg, weights), detector(cfg, weights, "valu")
+    (sc, md, _, _), (rsc, rmd, _, _) = gpu_score(det, w, pad=32, ref=ref), gpu_score(valu, w, ref=ref)
+    assert np.array_equal(np.isfinite(md), np.isfinite(rmd)) and np.array_equal(np.isnan(sc), np.isnan(rsc))
+    fin = np.isfinite(rsc) & (np.abs(rsc) < 1e30)
+    np.testing.assert_allclose(sc[fin], rsc[fin], rtol=2e-5, atol=1e-6)
+    ok = np.isfinite(rmd)
+    np.testing.assert_allclose(md[ok], rmd[ok], rtol=2e-5, atol=1e-5)
+    det.close()
+    valu.close()
