@@ -306,8 +306,10 @@ enova_status enova_train_init(const enova_train_config *config, const enova_dete
  * of the trainer's own), and the graph is replayed for every batch of the same size and alignment
  * of V (whether on a 16-byte boundary), whatever its buffers; the last four such graphs are kept,
  * and capturing another first waits for the device. Steps taken with timing on, or with graph replay
- * off, launch their kernels one by one on `stream`; a caller that captures the step into a
- * graph of its own turns replay off. Errors: EINVAL, ENOMEM, EHIP.
+ * off, launch their kernels one by one on `stream`, as does a step on a stream that is being
+ * captured: the caller's graph then holds the step on these buffers (with timing off, and after a
+ * step of this batch size or a larger one, since a capture cannot allocate). Errors: EINVAL, ENOMEM,
+ * EHIP.
  */
 enova_status enova_train_step(enova_trainer t, const float *V, const float *labels, const float *eps,
                               int32_t batch, float *out_info, hipStream_t stream);

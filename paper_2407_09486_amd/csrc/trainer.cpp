@@ -51,8 +51,8 @@ struct enova_trainer_s {
     // device wait per step (eight steps of 500 x 420 windows and the weights' copy: 2.0 -> 0.97 ms,
     // four of 8192 x 1024: 1.43 -> 0.98 ms).
     // A few graphs are kept (an epoch's last batch is often a smaller one), the one used longest ago
-    // going first. Steps without replay read args[1]: a caller may have captured them into a graph
-    // of its own, whose replays set args[1] again.
+    // going first. Steps without replay, and steps on a stream that a caller captures into a graph of
+    // its own, read args[1], which they set each time (in such a graph: at every replay).
     bool use_graph = true;
     hipStream_t gstream = nullptr;
     struct StepGraph {
@@ -455,14 +455,19 @@ enova_status enova_train_step(enova_trainer t, const float *V, const float *labe
         return st;
     const int64_t from = reinterpret_cast<const char *>(V) - reinterpret_cast<const char *>(t->p);
     const StepArgs args{V, labels, eps, info, {from, from - static_cast<int64_t>(sizeof(float))}};
-    if (t->timed || !t->use_graph) {
-        hipError_t e = launch_step_args(t->args + 1, args, s);
+    // while the caller captures s, the launches are recorded one by one, with the arguments in args[1]
+    // (each replay sets them): args[0] changes only where the trainer knows of it
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &cap);
+    if (e != hipSuccess)
+        return hip_fail(e, "training step's stream");
+    if (t->timed || !t->use_graph || cap != hipStreamCaptureStatusNone) {
+        e = launch_step_args(t->args + 1, args, s);
         if (e == hipSuccess)
             e = enqueue_step(t, V, t->args + 1, B, s);
         return e == hipSuccess ? ENOVA_OK : hip_fail(e, "training kernels");
     }
     t->n_events = 0;
-    hipError_t e = hipSuccess;
     enova_trainer_s::StepGraph *q = step_graph(t, V, B, &e);
     if (!q)
         return hip_fail(e, "capturing the training step");
@@ -471,9 +476,7 @@ enova_status enova_train_step(enova_trainer t, const float *V, const float *labe
         if ((e = launch_step_args(t->args, args, s)) != hipSuccess)
             return hip_fail(e, "training step arguments");
         t->cur = args;
-        // a launch that a caller's capture only recorded has not set them
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        t->cur_set = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        t->cur_set = true;
     }
     e = hipGraphLaunch(q->exec, s);
     return e == hipSuccess ? ENOVA_OK : hip_fail(e, "hipGraphLaunch");

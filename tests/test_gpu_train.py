@@ -355,3 +355,41 @@ def test_replay_over_new_buffers_matches_eager_steps(metrics, window):
         assert np.array_equal(pa[name], pb[name]), name
     ga.close()
     eb.close()
+
+
+def test_steps_captured_by_a_caller():
+    """A step that a caller captures into a graph of its own (graph replay left on) trains on the captured
+    buffers at each replay, and leaves the trainer's next step on its own: bit for bit the eager steps."""
+    import torch
+    cfg = _cfg(8, 32, 48, 8, "relu")
+    p0 = _init(cfg)
+    ga, eb = _trainer(cfg, p0), _trainer(cfg, p0)
+    eb.set_graph(False)
+    b = wl.training_batch(cfg, 600, seed=5)
+    V, lab, eps = (_dev(a) for a in (b.V, b.labels, b.eps))
+    A, B, C = ((V[i:i + 200], lab[i:i + 200], eps[i:i + 200]) for i in (0, 200, 400))
+    log("a caller's capture of a training step")
+    junk = torch.randn(1 << 18, device="cuda")
+    ga.step(*A)                                       # the workspace and the trainer's own graph exist
+    ga.step(*C)
+    ga.step(*A)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        ga.step(*B)
+    for _ in range(3):
+        ga.step(*A)
+        g.replay()
+        junk.mul_(0.5).add_(1.0)
+        ga.step(*A)
+        torch.cuda.synchronize()
+        g.replay()
+        ga.step(*C)
+    torch.cuda.synchronize()
+    for batch in (A, C, A) + 3 * (A, B, A, B, C):
+        eb.step(*batch)
+    pa, pb = ga.params(), eb.params()
+    for name in elbo.PARAMS:
+        assert np.array_equal(pa[name], pb[name]), name
+    ga.close()
+    eb.close()
