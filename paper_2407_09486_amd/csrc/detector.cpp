@@ -1303,15 +1303,21 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
             return fail(ENOVA_EUNSUPPORTED, "too many tiles (%lld)", static_cast<long long>(grid));
         const bool stats = norm == ENOVA_NORM_REFERENCE && !ref_mean;
         // workspace: reference statistics [2][n][M] floats and their chunk sums, first tile of each
-        // stream [n+1] int64, stream of each block [grid] ints
+        // stream [n+1] int64, the split pass's masks [grid][4] int64, stream of each block [grid] ints, its
+        // marks (a tile holds a window at the least)
         size_t o_part = 0;
         const size_t n_st = stats ? stats_floats(n, M, &o_part) : 0;
         const size_t n_tiles = 2 * (static_cast<size_t>(n) + 1);
-        enova_status st = ensure(&det->ext_ws, &det->ext_ws_cap, n_st + n_tiles + static_cast<size_t>(grid) + 4);
+        const size_t n_masks = split ? 8 * static_cast<size_t>(grid) : 0;
+        const size_t n_marks = split ? 1 + static_cast<size_t>(std::min(grid, n_windows)) : 0;
+        enova_status st = ensure(&det->ext_ws, &det->ext_ws_cap,
+                                 n_st + n_tiles + n_masks + static_cast<size_t>(grid) + n_marks + 4);
         if (st != ENOVA_OK)
             return st;
         int64_t *tiles = reinterpret_cast<int64_t *>(det->ext_ws + n_st);
-        int *tmap = reinterpret_cast<int *>(tiles + n + 1);
+        uint64_t *masks = reinterpret_cast<uint64_t *>(tiles + n + 1);
+        int *tmap = reinterpret_cast<int *>(masks + n_masks / 2);
+        unsigned *marks = split ? reinterpret_cast<unsigned *>(tmap + grid) : nullptr;
         if (det->timing)
             (void)hipEventRecord(det->ext_ev[0], stream);
         float *own_mean = stats ? det->ext_ws : nullptr;
@@ -1324,7 +1330,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         if ((e = launch_prep_scan(g, x, soff, woff, n, kExtFusedNb, tiles, own_mean, own_std, part, stream)) !=
             hipSuccess)
             return hip_fail(e, "tile scan and reference statistics kernels");
-        if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, nullptr, own_mean, own_std, part, stream)) != hipSuccess)
+        if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, marks, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
         const int decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
         if (split) {
@@ -1334,6 +1340,8 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
             sp.woff = woff;
             sp.tile_off = tiles;
             sp.tile_stream = tmap;
+            sp.marks = marks;
+            sp.masks = masks;
             sp.mean = ref_mean;
             sp.std = ref_std;
             sp.w1x = det->w1x;

@@ -22,7 +22,7 @@
 // smaller: scores 4.2e-7 -> 3.0e-7, md 6.1e-6 -> 4.4e-6, reconstruction error 2.3e-7 -> 5.1e-8
 // on the first.
 //
-// Windows out of the parts' range (split.h) are marked and evaluated one by one by k_ext_list.
+// Windows out of the parts' range (split.h) are marked and evaluated in fp32 by k_ext_list.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,10 +36,6 @@ namespace {
 
 constexpr int kNb = kExtFusedNb;     // windows per tile
 constexpr int kNbw = 2;              // 32-window blocks per wave
-
-// A tile's entry in the tile map once some of its windows are left to k_ext_list.
-__host__ __device__ __forceinline__ int split_mark(int s) { return -2 - s; }
-__host__ __device__ __forceinline__ int split_marked(int entry) { return -2 - entry; }   // the stream, or < 0
 
 // One metric of one window: v = (x - k) * ca, k the mean, scaled by kSplitScale, and the bits of its
 // largest |v| (infinity when out of range or not finite). x(t), t < W: the metric's values. (With
@@ -141,7 +137,6 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
     float *s_bd2 = reinterpret_cast<float *>(wmx + kNb);
     float *s_b1 = s_bd2 + g.Dp;
     float *s_sc = s_b1 + HP, *s_bd1 = s_sc + HP, *s_bh = s_bd1 + HP;
-    int *s_mark = reinterpret_cast<int *>(s_bh + 32);
     for (int i = tid; i < HP; i += NT) {
         s_b1[i] = p.b1[i];
         s_sc[i] = p.w1scale[i];
@@ -152,8 +147,6 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
     if (tid < 32)
         s_bh[tid] = p.bh[tid];
     wmx[tid] = 0u;
-    if (tid == 0)
-        *s_mark = 0;
 
     // ---- stage the raw super-rows (zero past the stream's end and in the padding)
     {
@@ -236,9 +229,18 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
     }
     __syncthreads();
 
+    // windows outside the range (a wave holds 64): left to k_ext_list; waves without any other are done
+    static_assert(kNb == NT && kNbw == 2, "a thread per window, a mask's word per wave");
+    const bool out = tid < nv && split_outside(wmx[tid]);
+    const uint64_t outside = __ballot(out);
+    if (__syncthreads_or(out)) {
+        if (lane == 0)
+            p.masks[b * 4 + wave] = outside;
+        if (tid == 0)
+            p.marks[1 + atomicAdd(p.marks, 1u)] = static_cast<unsigned>(b);
+    }
     const int wn0 = wave * kNbw * 32;
-    const bool wave_active = wn0 < nv;
-    if (wave_active) {
+    if (__any(tid < nv && !out)) {
         int rb[kNbw], wi[kNbw];
 #pragma unroll
         for (int nb = 0; nb < kNbw; ++nb) {
@@ -532,12 +534,8 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
                 tot += (sm[i][j][0] + sm[i][j][1]) + (sm[i][j][2] + sm[i][j][3]);
             tot += __shfl_xor(tot, 32);
             const float sqt = sq[i] + __shfl_xor(sq[i], 32);
-            if (n >= nv)
+            if (n >= nv || ((outside >> (n - wn0)) & 1u))
                 continue;
-            if (split_outside(wmx[n])) {
-                *s_mark = 1;
-                continue;
-            }
             const int64_t w = p.woff[s] + k0 + n;
             if (half == 0) {
                 if (p.scores)
@@ -558,142 +556,331 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
                     }
         }
     }
-    __syncthreads();
-    if (tid == 0 && *s_mark)
-        p.tile_stream[b] = split_mark(s);
 }
 
-// The marked tiles' windows outside the split's range, one block a window, in plain fp32 sums. A
-// thread finds out for each window of the tile whether it is one (the statistics from global
-// memory), then the block evaluates those. Rare by construction, so built for size, not speed.
-__global__ __launch_bounds__(256) void k_ext_list(ExtSplitParams p, ExtSplitShape g)
+// a[t] = w[k + t], zero from index K on.
+template <int N>
+__device__ __forceinline__ void load_row(const float *w, int k, int K, float (&a)[N])
 {
-    extern __shared__ float sm[];
-    __shared__ int s_pick[kNb];
-    __shared__ float red[256];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int D = g.D, H = g.H, L = g.L, M = g.M, W = g.W;
-    float *v = sm, *h = v + D, *ml = h + H, *hd = ml + 2 * L, *ca = hd + H, *cb = ca + M;   // cb: k
-    const int64_t step = gridDim.x;
-    for (int64_t first = blockIdx.x; first < g.list_grid; first += 256 * step) {
-        uint64_t mask[4];   // the same in every wave
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));   // of any alignment
+    static_assert(N % 4 == 0, "16-byte loads");
+    if (k + N <= K) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t i = first + (q * 64 + lane) * step;
-            mask[q] = __ballot(i < g.list_grid && split_marked(p.tile_stream[i]) >= 0);
+        for (int q = 0; q < N / 4; ++q) {
+            const f4 v = *reinterpret_cast<const f4 *>(w + k + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                a[4 * q + e] = v[e];
         }
-#pragma unroll 1
-        for (int q = 0; q < 4; ++q)
-            for (uint64_t mk = mask[q]; mk; mk &= mk - 1) {
-                const int64_t b = first + (q * 64 + __builtin_ctzll(mk)) * step;
-                const int s = split_marked(p.tile_stream[b]);
-                const int64_t k0 = (b - p.tile_off[s]) * kNb;
-                const int64_t ns = p.woff[s + 1] - p.woff[s];
-                const int nv = static_cast<int>(ns - k0 < kNb ? ns - k0 : kNb);
-                const float *mean = p.mean + static_cast<int64_t>(s) * M, *std = p.std + static_cast<int64_t>(s) * M;
-                auto constants = [&](int n, int m, float &a, float &c) {
-                    const float *x = p.x + (p.soff[s] + (k0 + n) * g.S) * M + m;
-                    const bool own = p.norm == ENOVA_NORM_WINDOW;
-                    return window_constants([&](int t) { return x[static_cast<int64_t>(t) * M]; }, W, p.norm,
-                                            own ? 0.0f : mean[m], own ? 1.0f : std[m], a, c);
-                };
-                __syncthreads();   // the previous tile's picks are no longer read
-                s_pick[tid] = 0;
-                if (tid < nv) {
-                    unsigned big = 0u;
-                    for (int m = 0; m < M; ++m) {
-                        float a, c;
-                        big = max(big, constants(tid, m, a, c));
-                    }
-                    s_pick[tid] = split_outside(big) ? 1 : 0;
-                }
-                __syncthreads();
-                for (int n = 0; n < nv; ++n) {
-                    if (!s_pick[n])
-                        continue;
-                    const float *x = p.x + (p.soff[s] + (k0 + n) * g.S) * M;
-                    const int64_t w = p.woff[s] + k0 + n;
-                    for (int m = tid; m < M; m += 256) {
-                        float a, c;
-                        constants(n, m, a, c);
-                        ca[m] = a * kSplitUnscale;
-                        cb[m] = c;
-                    }
-                    __syncthreads();
-                    for (int j = tid; j < D; j += 256)
-                        v[j] = (x[j] - cb[j % M]) * ca[j % M];
-                    __syncthreads();
-                    auto dot = [&](const float *a, const float *c, int k) {
-                        float t = 0.0f;
-                        for (int j = lane; j < k; j += 64)
-                            t = fmaf(a[j], c[j], t);
+    } else {
 #pragma unroll
-                        for (int off = 32; off >= 1; off >>= 1)
-                            t += __shfl_xor(t, off);
-                        return t;
-                    };
-                    auto act = [&](float a) { return g.act == ENOVA_TANH ? tanhf(a) : (a < 0.0f ? 0.0f : a); };
-                    for (int i = wave; i < H; i += 4) {
-                        const float t = dot(p.w1 + static_cast<int64_t>(i) * D, v, D);
-                        if (lane == 0)
-                            h[i] = act(t + p.b1[i]);
+        for (int t = 0; t < N; ++t)
+            a[t] = k + t < K ? w[k + t] : 0.0f;
+    }
+}
+
+// The windows that k_ext_split left, in fp32: up to 64 of a marked tile (a mask's word) at a time, the
+// parts dealt out evenly over the blocks. The windows are the columns of fp32 matrix ops whose other
+// operand is a dense weight matrix read in place; in a run of 2 N reduction indices op t takes index t of
+// the lower lanes' and index N + t of the upper lanes' half, so that a lane reads whole cache lines. The
+// encoder's inputs are normalised into LDS once for the four waves, 64 indices of every window at a
+// time, while the previous ones are multiplied; its waves are 32-row blocks by shares of each run (added
+// in order). The output's blocks go to the waves in turn, and a lane adds its rows' v - m' per metric in
+// a place of its own in LDS.
+// This is for data that leaves the range for long (a metric constant over the reference prefix that
+// moves later, gaps held as NaN). One window per block and serial dot products, as it was first, took 94.9 ms
+// for 16 streams x 16384 steps x 16 metrics, W = 64, H = 128, half of the windows out; now 1.46 (0.67 in range; all
+// windows on the fp32 pass 1.19). 7 metrics, W = 60, H = 64, tanh: 26.6 -> 0.58 ms (chunked evaluation 2.6).
+constexpr int kExtListWin = 64, kExtListPitch = 65;   // windows, and floats of a row of them in LDS
+constexpr int kExtListRun = 64;                       // reduction indices of a run
+constexpr int kExtListPart = 2 * kExtListRun * kExtListPitch;   // two runs; partial sums later
+static_assert(kExtListPart >= 8 * 16 * kExtListWin && kExtListPart >= 4 * 2 * 16 * 64, "partial sums");
+
+template <int HB>
+__global__ __launch_bounds__(256, 2) void k_ext_list(ExtSplitParams p, ExtSplitShape g)
+{
+    constexpr int C = kExtListWin, PITCH = kExtListPitch, RUN = kExtListRun, Hp = 32 * HB;
+    constexpr int SL = 4 / HB, NT = RUN / 2 / SL;   // shares of a run, and the ops of one
+    extern __shared__ float lsm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
+    const int D = g.D, H = g.H, L = g.L, M = g.M, W = g.W;
+    // LDS: constants [M][C] (factor, mean), activations [Hp][PITCH], two runs of inputs or partial sums,
+    // squares [8][C], the windows
+    float2 *cak = reinterpret_cast<float2 *>(lsm);
+    float *act = lsm + 2 * M * C, *part = act + Hp * PITCH, *sqs = part + kExtListPart;
+    int *s_col = reinterpret_cast<int *>(sqs + 8 * C);
+    float *ml = part + 4 * 16 * 64;   // [32][C], behind the heads' partial sums
+    const int64_t count = p.marks[0];
+    auto activation = [&](float a) { return g.act == ENOVA_TANH ? tanhf(a) : (a < 0.0f ? 0.0f : a); };
+    // c[nb] += w[row] act over the groups [g0, g1) of 32 hidden units, of column blocks first, first + 1
+    // (rows past the end give rows that are not used)
+    auto product = [&](const float *w, int row, int rows, int g0, int g1, int first, int nbs, v16f (&c)[2]) {
+        const float *wr = w + static_cast<int64_t>(row < rows ? row : rows - 1) * H;
+        float a[2][16];
+        if (g0 < g1)
+            load_row<16>(wr, 32 * g0 + 16 * half, H, a[0]);
+#pragma unroll
+        for (int i = 0; i < HB; ++i) {
+            if (i < g0 || i >= g1)
+                continue;
+            const int u = i & 1;
+            if (i == g0 && u == 1)
+#pragma unroll
+                for (int t = 0; t < 16; ++t)
+                    a[1][t] = a[0][t];
+            if (i + 1 < g1)
+                load_row<16>(wr, 32 * (i + 1) + 16 * half, H, a[u ^ 1]);
+            const float *b = act + (32 * i + 16 * half) * PITCH + 32 * first + col;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                c[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][t], b[t * PITCH], c[0], 0, 0, 0);
+                if (nbs > 1)
+                    c[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][t], b[t * PITCH + 32], c[1], 0, 0, 0);
+            }
+        }
+    };
+    for (int64_t it = blockIdx.x; it < 4 * count; it += gridDim.x) {
+        const int quarter = static_cast<int>(it / count);
+        const int64_t b = p.marks[1 + it - quarter * count];
+        const uint64_t mask = p.masks[b * 4 + quarter];
+        if (mask == 0)
+            continue;
+        const int s = p.tile_stream[b], cnt = __popcll(mask), nbs = cnt > 32 ? 2 : 1;
+        const int64_t k0 = (b - p.tile_off[s]) * kNb + quarter * C;
+        const float *xs = p.x + (p.soff[s] + k0 * g.S) * M;   // window n of the word starts at n S M
+        const int64_t w0 = p.woff[s] + k0;
+        if (tid < C && ((mask >> tid) & 1u))
+            s_col[__popcll(mask & ((1ull << tid) - 1ull))] = tid;
+        __syncthreads();
+        // column c's window (past the last: that one again)
+        auto window = [&](int c) { return xs + static_cast<int64_t>(s_col[min(c, cnt - 1)]) * g.S * M; };
+        for (int i = tid; i < M * C; i += 256) {
+            const int m = i / C;
+            const float *x = window(i - m * C) + m;
+            float mean, f;
+            if (p.norm == ENOVA_NORM_WINDOW) {
+                const double shift = x[0], inv_w = 1.0 / W;
+                double s1 = 0.0, s2 = 0.0;
+#pragma unroll 8
+                for (int t = 0; t < W; ++t) {
+                    const double d = static_cast<double>(x[static_cast<int64_t>(t) * M]) - shift;
+                    s1 += d;
+                    s2 = fma(d, d, s2);
+                }
+                const double mu = shift + s1 * inv_w, var = (s2 - s1 * s1 * inv_w) * inv_w;
+                double sd = sqrt(var > 0.0 ? var : 0.0);
+                if (sd <= 1e-6 * fmax(1.0, fabs(mu)))
+                    sd = 1.0;   // constant metric inside the window
+                f = static_cast<float>(1.0 / sd);
+                mean = static_cast<float>(mu);
+            } else {
+                f = static_cast<float>(1.0 / static_cast<double>(p.std[static_cast<int64_t>(s) * M + m]));
+                mean = p.mean[static_cast<int64_t>(s) * M + m];
+            }
+            cak[i] = make_float2(f, mean);
+        }
+        __syncthreads();
+
+        // ---- encoder: wave = hidden block + HB share
+        v16f c[2];
+        auto clear = [&]() {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    c[nb][r] = 0.0f;
+        };
+        clear();
+        {
+            const int row = 32 * (wave % HB) + col;
+            const float *wr = p.w1 + static_cast<int64_t>(row < H ? row : H - 1) * D;
+            const int at = 32 * half + NT * (wave / HB);   // of the run: this lane's first index
+            // staging: thread = column and quarter of the run
+            const int sc = tid >> 2, sk = 16 * (tid & 3);
+            const float *xw = window(sc);
+            float a[2][NT], v[16];
+            auto put = [&](int run) {
+                float *dst = part + (run & 1) * RUN * PITCH + sk * PITCH + sc;
+                const int k = run * RUN + sk;
+                int m = k % M;
+#pragma unroll
+                for (int t = 0; t < 16; ++t) {
+                    const float2 q = cak[m * C + sc];
+                    dst[t * PITCH] = (v[t] - q.y) * q.x;   // (past the end under weights of zero)
+                    m = m + 1 == M ? 0 : m + 1;
+                }
+            };
+            load_row<16>(xw, sk, D, v);
+            load_row<NT>(wr, at, D, a[0]);
+            put(0);
+            const int runs = (D + RUN - 1) / RUN;
+            for (int r0 = 0; r0 < runs; r0 += 2) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int run = r0 + u;
+                    if (run >= runs)
+                        break;
+                    const int next = run + 1 < runs ? run + 1 : run;
+                    load_row<16>(xw, next * RUN + sk, D, v);
+                    load_row<NT>(wr, next * RUN + at, D, a[u ^ 1]);
+                    __syncthreads();   // the run is staged, and the one before no longer read
+                    const float *bq = part + (run & 1) * RUN * PITCH + at * PITCH + col;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        c[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][t], bq[t * PITCH], c[0], 0, 0, 0);
+                        if (nbs > 1)
+                            c[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][t], bq[t * PITCH + 32], c[1], 0, 0, 0);
                     }
-                    __syncthreads();
-                    for (int i = wave; i < 2 * L; i += 4) {
-                        const float t = dot(p.wml + static_cast<int64_t>(i) * H, h, H);
-                        if (lane == 0)
-                            ml[i] = t + p.bml[i];
-                    }
-                    __syncthreads();
-                    for (int i = tid; i < H; i += 256) {
-                        float t = 0.0f;
-                        for (int l = 0; l < L; ++l)
-                            t = fmaf(p.wd1[static_cast<int64_t>(i) * L + l], ml[l], t);
-                        hd[i] = act(t + p.bd1[i]);
-                    }
-                    if (tid == 0 && p.scores) {
-                        float kl = 0.0f;
-                        for (int l = 0; l < L; ++l)
-                            kl += ml[l] * ml[l] + kl_g(ml[L + l]);
-                        p.scores[w] = 0.5f * kl;
-                    }
-                    __syncthreads();
-                    if (p.decode) {
-                        float sq = 0.0f;
-                        for (int j = tid; j < D; j += 256) {
-                            const float *row = p.wd2 + static_cast<int64_t>(j) * H;
-                            float t = 0.0f;
-                            for (int i = 0; i < H; ++i)
-                                t = fmaf(row[i], hd[i], t);
-                            v[j] = (v[j] - p.bd2d[j]) - t;
-                            sq = fmaf(v[j], v[j], sq);
-                        }
-                        red[tid] = sq;
-                        __syncthreads();
-                        for (int m = tid; m < M; m += 256) {
-                            float t = 0.0f;
-                            for (int k = 0; k < W; ++k)
-                                t += v[k * M + m];
-                            ca[m] = t;
-                            if (p.mdm)
-                                p.mdm[w * M + m] = t * g.inv_w;
-                        }
-                        __syncthreads();
-                        if (tid == 0) {
-                            float t = 0.0f, e = 0.0f;
-                            for (int m = 0; m < M; ++m)
-                                t += ca[m];
-                            for (int k = 0; k < 256; ++k)
-                                e += red[k];
-                            if (p.md)
-                                p.md[w] = t * g.inv_d;
-                            if (p.rec)
-                                p.rec[w] = e * g.inv_d;
-                        }
-                    }
-                    __syncthreads();
+                    if (next > run)
+                        put(next);
                 }
             }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                part[((wave * 2 + nb) * 16 + r) * 64 + lane] = c[nb][r];
+        __syncthreads();
+        for (int i = tid; i < HB * 2 * 16 * 64; i += 256) {
+            const int ln = i & 63, r = (i >> 6) & 15, nb = (i >> 10) & 1, hb = i >> 11;
+            float t = 0.0f;
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl)
+                t += part[(((sl * HB + hb) * 2 + nb) * 16 + r) * 64 + ln];
+            const int h = 32 * hb + crow(r, ln >> 5);
+            act[h * PITCH + nb * 32 + (ln & 31)] = h < H ? activation(t + p.b1[h]) : 0.0f;
+        }
+        __syncthreads();
+
+        // ---- heads [mu; logvar]: wave = column block + 2 share of the hidden units
+        clear();
+        const int nbw = wave & 1, sh = wave >> 1;
+        if (nbw < nbs)
+            product(p.wml, col, 2 * L, HB * sh / 2, HB * (sh + 1) / 2, nbw, 1, c);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            part[(wave * 16 + r) * 64 + lane] = c[0][r];
+        __syncthreads();
+        for (int i = tid; i < 2 * 16 * 64; i += 256) {
+            const int ln = i & 63, r = (i >> 6) & 15, nb = i >> 10, row = crow(r, ln >> 5);
+            const float t = part[(nb * 16 + r) * 64 + ln] + part[((2 + nb) * 16 + r) * 64 + ln];
+            ml[row * C + nb * 32 + (ln & 31)] = t + (row < 2 * L ? p.bml[row] : 0.0f);
+        }
+        __syncthreads();
+        if (tid < cnt && p.scores) {
+            float kl = 0.0f;
+            for (int l = 0; l < L; ++l)
+                kl += ml[l * C + tid] * ml[l * C + tid] + kl_g(ml[(L + l) * C + tid]);
+            p.scores[w0 + s_col[tid]] = 0.5f * kl;
+        }
+        if (!p.decode) {
+            __syncthreads();
+            continue;
+        }
+
+        // ---- decoder: hidden layer, then the output blocks against v
+        if (wave < HB) {
+            const int row = 32 * wave + col;
+            float a[8];
+            load_row<8>(p.wd1 + static_cast<int64_t>(row < H ? row : H - 1) * L, 8 * half, L, a);
+            clear();
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float *b = ml + (8 * half + t) * C + col;   // (the rows from L on are log-variances)
+                const float b0 = 8 * half + t < L ? b[0] : 0.0f, b1 = 8 * half + t < L ? b[32] : 0.0f;
+                c[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b0, c[0], 0, 0, 0);
+                if (nbs > 1)
+                    c[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b1, c[1], 0, 0, 0);
+            }
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int h = 32 * wave + crow(r, half);
+                    act[h * PITCH + nb * 32 + col] = h < H ? activation(c[nb][r] + p.bd1[h]) : 0.0f;
+                }
+        }
+        __syncthreads();
+        for (int i = tid; i < 8 * M * C; i += 256)
+            part[i] = 0.0f;
+        __syncthreads();
+        // with M a divisor of 32 a lane's rows 8 q + e of every block belong to one metric, and its sums
+        // stay in registers
+        const bool fixed = 32 % M == 0;
+        float sq[2] = {0.0f, 0.0f}, own[2][2][4];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            own[i >> 3][(i >> 2) & 1][i & 3] = 0.0f;
+        float *sums = part + (wave * 2 + half) * M * C;   // this lane's: [M][C], column nb * 32 + col
+        const float *xc[2] = {window(col), window(32 + col)};
+        for (int ob = wave; ob * 32 < D; ob += 4) {
+            float xv[4][2][4], bd[4][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j0 = 32 * ob + 8 * q + 4 * half;
+                load_row<4>(p.bd2d, j0, D, bd[q]);
+                load_row<4>(xc[0], j0, D, xv[q][0]);
+                if (nbs > 1)
+                    load_row<4>(xc[1], j0, D, xv[q][1]);
+            }
+            clear();
+            product(p.wd2, 32 * ob + col, D, 0, HB, 0, nbs, c);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j0 = 32 * ob + 8 * q + 4 * half;
+                int m = j0 % M;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb)
+                        if (nb < nbs) {
+                            const float2 k = cak[m * C + nb * 32 + col];
+                            const float v = (xv[q][nb][e] - k.y) * k.x - bd[q][e];
+                            const float d = j0 + e < D ? v - c[nb][4 * q + e] : 0.0f;
+                            if (fixed)
+                                own[nb][q & 1][e] += d;
+                            else
+                                sums[m * C + nb * 32 + col] += d;
+                            sq[nb] = fmaf(d, d, sq[nb]);
+                        }
+                    m = m + 1 == M ? 0 : m + 1;
+                }
+            }
+        }
+        if (fixed)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int nb = i >> 3, q = (i >> 2) & 1, e = i & 3;
+                sums[(8 * q + 4 * half + e) % M * C + nb * 32 + col] += own[nb][q][e];
+            }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            sqs[(wave * 2 + half) * C + nb * 32 + col] = sq[nb];
+        __syncthreads();
+        for (int i = tid; i < M * C; i += 256) {
+            const int m = i / C, cc = i - m * C;
+            float t = 0.0f;
+            for (int k = 0; k < 8; ++k)
+                t += part[(k * M + m) * C + cc];
+            act[i] = t;
+            if (p.mdm && cc < cnt)
+                p.mdm[(w0 + s_col[cc]) * M + m] = t * g.inv_w;
+        }
+        __syncthreads();
+        if (tid < cnt) {
+            float t = 0.0f, e = 0.0f;
+            for (int m = 0; m < M; ++m)
+                t += act[m * C + tid];
+            for (int k = 0; k < 8; ++k)
+                e += sqs[k * C + tid];
+            if (p.md)
+                p.md[w0 + s_col[tid]] = t * g.inv_d;
+            if (p.rec)
+                p.rec[w0 + s_col[tid]] = e * g.inv_d;
+        }
+        __syncthreads();   // the LDS is written again
     }
 }
 
@@ -726,20 +913,23 @@ size_t lds_bytes(const Geometry &g, const SplitGeometry &sg)
 {
     const size_t rows = static_cast<size_t>(kNb + sg.Q - 1 + sg.spare);
     return rows * sg.P * 16 +
-           sizeof(float) * (static_cast<size_t>(kNb) * (2 * sg.Mp + 4) + kNb + padded_d(g, sg) + 3 * static_cast<size_t>(g.Hp) + 32 + 4);
+           sizeof(float) * (static_cast<size_t>(kNb) * (2 * sg.Mp + 4) + kNb + padded_d(g, sg) + 3 * static_cast<size_t>(g.Hp) + 32);
 }
 
+// (at most 75.3 KiB: 16 metrics and 128 hidden units)
 size_t list_lds_bytes(const Geometry &g)
 {
-    return sizeof(float) * (static_cast<size_t>(g.D) + 2 * static_cast<size_t>(g.H) + 2 * g.L + 2 * static_cast<size_t>(g.M));
+    return sizeof(float) * (kExtListWin * (2 * static_cast<size_t>(g.M) + 8 + 1) + kExtListPitch * static_cast<size_t>(g.Hp) +
+                            kExtListPart);
 }
+
+SplitKernel pick_list(int hb) { return hb == 1 ? k_ext_list<1> : hb == 2 ? k_ext_list<2> : k_ext_list<4>; }
 
 }  // namespace
 
 bool ext_split_supported(const Geometry &g, const SplitGeometry &sg)
 {
-    return sg.ok && (sg.Mp == 8 || sg.Mp == 16) && g.HB <= 4 && lds_bytes(g, sg) <= kLdsLimit / 2 &&
-           list_lds_bytes(g) <= 120 * 1024;
+    return sg.ok && (sg.Mp == 8 || sg.Mp == 16) && g.HB <= 4 && lds_bytes(g, sg) <= kLdsLimit / 2;
 }
 
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg) { return padded_d(g, sg); }
@@ -763,8 +953,8 @@ hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg)
                                              static_cast<int>(lds_bytes(g, sg)));
     if (e != hipSuccess)
         return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_ext_list), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               120 * 1024);
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(pick_list(g.HB)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(kLdsLimit / 2));
 }
 
 hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,
@@ -792,13 +982,12 @@ hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const Ex
     sh.wd2_unscale = wd2_unscale;
     sh.inv_w = 1.0f / static_cast<float>(g.W);
     sh.inv_d = 1.0f / static_cast<float>(g.D);
-    sh.list_grid = grid;
     hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(256), lds_bytes(g, sg), st, p, sh);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_ext_list, dim3(static_cast<unsigned>(grid < 512 ? grid : 512)), dim3(256), list_lds_bytes(g),
-                       st, p, sh);
+    hipLaunchKernelGGL(pick_list(g.HB), dim3(static_cast<unsigned>(std::min<int64_t>(4 * grid, 512))), dim3(256),
+                       list_lds_bytes(g), st, p, sh);
     return hipGetLastError();
 }
 

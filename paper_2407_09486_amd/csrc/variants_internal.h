@@ -57,12 +57,14 @@ hipError_t launch_ext_fused(const Geometry &g, const ExtFusedParams &p, int64_t 
 // ---------------------------------------------------------------------------------------------
 // The same on the 16-bit matrix cores (k_ext_split.hip): fp32 detectors that the split scoring kernel
 // takes, with steps padded to 8 or 16 metrics, at most 128 hidden units and a tile within half a
-// compute unit's LDS; windows out of the split's range one by one, from the dense weights.
+// compute unit's LDS; windows out of the split's range in fp32, from the dense weights.
 // ---------------------------------------------------------------------------------------------
 struct ExtSplitParams {
     const float *x;
     const int64_t *soff, *woff, *tile_off;
-    int *tile_stream;
+    const int *tile_stream;
+    unsigned *marks;             // the count of tiles with windows out of the range (cleared), and these tiles
+    uint64_t *masks;             // [tile][4] a bit for each of its 256 windows out of the range, where marked
     const float *mean, *std;     // reference statistics [n][M] (reference normalisation only)
     const uint4 *w1x, *whx, *wdx;    // the split scoring kernel's fragments
     const float *w1scale;
@@ -76,7 +78,6 @@ struct ExtSplitParams {
 struct ExtSplitShape {
     int M, S, W, D, H, L, act, Q, CPR, P, nsteps, spare, Dp;
     float wd2_unscale, inv_w, inv_d;
-    int64_t list_grid;
 };
 bool ext_split_supported(const Geometry &g, const SplitGeometry &sg);
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg);   // Dp

@@ -117,3 +117,45 @@ def test_decoder_output_scales(norm, where):
     err = np.sqrt(np.mean((res[2] - ref["md_metric"])[:, 1:] ** 2))
     log(f"  rms error {err:.2e}")
     assert err <= 1e-7
+
+
+@pytest.mark.parametrize("norm", ["reference", "window"])
+@pytest.mark.parametrize("M,W,S,H,L,act", [(7, 60, 1, 64, 16, "tanh"), (16, 64, 1, 128, 16, "relu"), (3, 9, 1, 96, 3, "relu"),
+                                           (12, 11, 2, 30, 5, "tanh"), (5, 40, 3, 128, 16, "relu"), (1, 100, 1, 64, 2, "relu"),
+                                           (8, 32, 1, 33, 16, "relu")])
+def test_stretches_outside_the_range(norm, M, W, S, H, L, act):
+    """Windows left to the fp32 kernel in all numbers, from one of a tile's 64 to whole tiles, beside others: a
+    metric that was constant over the reference prefix and moves by thousands later (reference normalisation),
+    stretches constant but for their last places (window normalisation)."""
+    counts = [700, 300, 64, 1]
+    lengths = [W + (k - 1) * S + W * S for k in counts]
+    cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, latent=L, act=act, n_streams=len(lengths))
+    log(f"[ext split] stretches {norm} M={M} W={W} S={S} H={H} L={L} {act}")
+    rng = np.random.default_rng(M + H)
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    x = rng.standard_normal((int(offs[-1]), M)).astype(np.float32)
+    small = rng.integers(-1, 2, x.shape).astype(np.float32) * np.float32(2.0 ** -20)
+    for i, T in enumerate(lengths):
+        y, z = x[offs[i]:offs[i + 1]], small[offs[i]:offs[i + 1]]
+        if norm == "reference":
+            y[:T // 2 + 1, 0] = 0.5
+            y[T // 2 + 1:, 0] = rng.uniform(-1, 1, T - T // 2 - 1)
+            y[5 * T // 8, 0] = 4500.0
+            y[3 * T // 4:, 0] = rng.uniform(4100, 5000, T - 3 * T // 4)
+            y[min(7 * T // 8 + 3, T - 1), 0] = -0.2
+        else:
+            for part in (slice(T // 8, T // 8 + W + 2 * S), slice(T // 2, 3 * T // 4)):
+                y[part] = 2.0 + z[part]
+    w = wl.from_arrays(cfg, x, offs)
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    if norm == "reference":
+        weights.w1 *= 1e-3                               # e^lv stays finite
+    res, ref = _run(cfg, weights, w, norm)
+    _check(res, ref, np.arange(len(ref["score"])))
+    import torch
+    det = detector(cfg, weights)
+    xd, so = upload(w)
+    wo = det.window_offsets(offs)
+    only = det.score_ext(xd, so, torch.from_numpy(wo).cuda(), int(wo[-1]), norm=norm, scores_only=True)[0]
+    assert np.array_equal(only.cpu().numpy().astype(np.float64), res[0])
+    det.close()
