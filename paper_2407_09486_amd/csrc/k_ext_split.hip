@@ -37,49 +37,43 @@ namespace {
 constexpr int kNb = kExtFusedNb;     // windows per tile
 constexpr int kNbw = 2;              // 32-window blocks per wave
 
-// One metric of one window: v = (x - k) * ca, k the mean, scaled by kSplitScale, and the bits of its
-// largest |v| (infinity when out of range or not finite). x(t), t < W: the metric's values. (With
-// v = x * ca + cb the rounding of cb, at the scale of mean / std, doubles that of the mean.)
-template <typename X>
-__device__ __forceinline__ unsigned window_constants(X x, int W, int norm, float ref_mean, float ref_std, float &ca,
-                                                     float &k)
+// Normalisation: v = (x - k) * ca, k the mean, scaled by kSplitScale. (With v = x * ca + cb the rounding of
+// cb, at the scale of mean / std, doubles that of the mean.)
+__device__ __forceinline__ float scaled_rstd(double std) { return static_cast<float>(1.0 / std) * kSplitScale; }
+
+// The bits of a value's |v|, more than infinity's where x is not a number.
+__device__ __forceinline__ unsigned size_of(float x, float ca, float k)
 {
+    return __float_as_uint((x - k) * ca) & 0x7fffffffu;
+}
+
+// One metric of one window against itself: its constants, and the bits of its largest |v| (infinity when
+// out of range or not finite). x(t), t < W: the metric's values.
+template <typename X>
+__device__ __forceinline__ unsigned window_constants(X x, int W, float &ca, float &k)
+{
+    // shifted sums (shift: the window's first value): mean and population std
     const float x0 = x(0);
     float mn = x0, mx = x0;
-    bool finite;
-    if (norm == ENOVA_NORM_WINDOW) {
-        // shifted sums (shift: the window's first value): mean and population std
-        const double inv_w = 1.0 / W, shift = static_cast<double>(x0);
-        double s1 = 0.0, s2 = 0.0;
-        for (int t = 0; t < W; ++t) {
-            const float v = x(t);
-            const double d = static_cast<double>(v) - shift;
-            s1 += d;
-            s2 = fma(d, d, s2);
-            mn = fminf(mn, v);
-            mx = fmaxf(mx, v);
-        }
-        const double mean = shift + s1 * inv_w;
-        double var = (s2 - s1 * s1 * inv_w) * inv_w;
-        finite = fabs(var) < INFINITY;         // NaN or infinite where a value was not
-        var = var > 0.0 ? var : 0.0;
-        double sd = sqrt(var);
-        if (sd <= 1e-6 * fmax(1.0, fabs(mean)))
-            sd = 1.0;   // constant metric inside the window
-        ca = static_cast<float>(1.0 / sd) * kSplitScale;
-        k = static_cast<float>(mean);
-    } else {
-        float odd = 0.0f;
-        for (int t = 0; t < W; ++t) {
-            const float v = x(t);
-            odd = fmaf(v, 0.0f, odd);          // NaN where a value is not finite
-            mn = fminf(mn, v);
-            mx = fmaxf(mx, v);
-        }
-        finite = odd == 0.0f;
-        ca = static_cast<float>(1.0 / static_cast<double>(ref_std)) * kSplitScale;
-        k = ref_mean;
+    const double inv_w = 1.0 / W, shift = static_cast<double>(x0);
+    double s1 = 0.0, s2 = 0.0;
+    for (int t = 0; t < W; ++t) {
+        const float v = x(t);
+        const double d = static_cast<double>(v) - shift;
+        s1 += d;
+        s2 = fma(d, d, s2);
+        mn = fminf(mn, v);
+        mx = fmaxf(mx, v);
     }
+    const double mean = shift + s1 * inv_w;
+    double var = (s2 - s1 * s1 * inv_w) * inv_w;
+    const bool finite = fabs(var) < INFINITY;   // NaN or infinite where a value was not
+    var = var > 0.0 ? var : 0.0;
+    double sd = sqrt(var);
+    if (sd <= 1e-6 * fmax(1.0, fabs(mean)))
+        sd = 1.0;   // constant metric inside the window
+    ca = scaled_rstd(sd);
+    k = static_cast<float>(mean);
     const float lo = fabsf((mn - k) * ca), hi = fabsf((mx - k) * ca);
     const bool in = lo <= kSplitMax && hi <= kSplitMax && finite;
     return in ? __float_as_uint(fmaxf(lo, hi)) : 0x7f800000u;
@@ -201,31 +195,79 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
     }
     __syncthreads();
 
-    // ---- every window's constants, one metric per thread and pass (consecutive threads:
-    // consecutive windows)
-    for (int idx = tid; idx < kNb * Mp; idx += NT) {
-        const int n = idx % kNb, m = idx / kNb;
-        float ca = 0.0f, cb = 0.0f;
-        if (n < nv && m < M) {
-            const float *row = reinterpret_cast<const float *>(seg) + n * P * 4 + m;
-            int q = 0, ts = 0, last = -1;
-            const float rm = p.norm == ENOVA_NORM_WINDOW ? 0.0f : p.mean[static_cast<int64_t>(s) * M + m];
-            const float rs = p.norm == ENOVA_NORM_WINDOW ? 1.0f : p.std[static_cast<int64_t>(s) * M + m];
-            auto at = [&](int t) {   // t = 0, then 0, 1, 2, ...
-                if (t == 0) {
-                    q = ts = 0;
-                } else if (t != last && ++ts == S) {
-                    ts = 0;
-                    ++q;
-                }
-                last = t;
-                return row[q * P * 4 + ts * Mp];
-            };
-            const unsigned big = window_constants(at, W, p.norm, rm, rs, ca, cb);
-            atomicMax(&wmx[n], big);
+    // ---- every window's constants and largest |v|
+    if (p.norm == ENOVA_NORM_WINDOW) {
+        // one metric per thread and pass (consecutive threads: consecutive windows)
+        for (int idx = tid; idx < kNb * Mp; idx += NT) {
+            const int n = idx % kNb, m = idx / kNb;
+            float ca = 0.0f, cb = 0.0f;
+            if (n < nv && m < M) {
+                const float *row = reinterpret_cast<const float *>(seg) + n * P * 4 + m;
+                int q = 0, ts = 0, last = -1;
+                auto at = [&](int t) {   // t = 0, then 0, 1, 2, ...
+                    if (t == 0) {
+                        q = ts = 0;
+                    } else if (t != last && ++ts == S) {
+                        ts = 0;
+                        ++q;
+                    }
+                    last = t;
+                    return row[q * P * 4 + ts * Mp];
+                };
+                const unsigned big = window_constants(at, W, ca, cb);
+                atomicMax(&wmx[n], big);
+            }
+            cab[n * CP + m] = ca;
+            cab[n * CP + Mp + m] = cb;
         }
-        cab[n * CP + m] = ca;
-        cab[n * CP + Mp + m] = cb;
+    } else {
+        // the same constants for all: the largest |v| of each super-row, and of its steps that a window ends
+        // with, then of the windows. (By window and metric this was a fifth of the pass on few windows.) The
+        // rows' maxima take the table's place until it is filled: 5120 floats at the least, at most 2 x 1706 + 32.
+        unsigned *rowm = reinterpret_cast<unsigned *>(cab), *tailm = rowm + rows_alloc;
+        float *rc = reinterpret_cast<float *>(tailm + rows_alloc);
+        const int rows = nv + Q - 1, tail = W - (Q - 1) * S;
+        const float *mean = p.mean + static_cast<int64_t>(s) * M, *std = p.std + static_cast<int64_t>(s) * M;
+        if (tid < M) {
+            rc[tid] = scaled_rstd(std[tid]);
+            rc[Mp + tid] = mean[tid];
+        }
+        __syncthreads();
+        for (int r = tid; r < rows; r += NT) {
+            const float *row = reinterpret_cast<const float *>(seg) + r * P * 4;
+            unsigned full = 0u, part = 0u;
+            for (int ts = 0; ts < S; ++ts) {
+                unsigned big = 0u;
+#pragma unroll 4
+                for (int m = 0; m < M; ++m)
+                    big = max(big, size_of(row[ts * Mp + m], rc[m], rc[Mp + m]));
+                full = max(full, big);
+                part = ts < tail ? max(part, big) : part;
+            }
+            rowm[r] = full;
+            tailm[r] = part;
+        }
+        __syncthreads();
+        unsigned big = 0u;
+        if (tid < nv) {
+            big = tailm[tid + Q - 1];
+#pragma unroll 8
+            for (int q = 0; q < Q - 1; ++q)
+                big = max(big, rowm[tid + q]);
+        }
+        __syncthreads();
+        wmx[tid] = big;
+        float ca[Mp], cb[Mp];
+#pragma unroll
+        for (int m = 0; m < Mp; ++m) {
+            ca[m] = m < M ? scaled_rstd(std[m]) : 0.0f;
+            cb[m] = m < M ? mean[m] : 0.0f;
+        }
+#pragma unroll
+        for (int m = 0; m < Mp; ++m) {
+            cab[tid * CP + m] = ca[m];
+            cab[tid * CP + Mp + m] = cb[m];
+        }
     }
     __syncthreads();
 
