@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <string>
@@ -70,26 +71,23 @@ struct enova_detector_s {
     Geometry g{};
     int device = 0;
     int kind = 1;                 // 1 vector-ALU, 2 matrix-core
-    // weights
-    void *w1p = nullptr;          // matrix-core A fragments
-    void *ring_w = nullptr;       // ring kernel: W1, heads and decoder fragments (one allocation)
+    // weights (in few allocations)
+    std::vector<void *> weights;
+    const uint4 *w1p = nullptr;   // matrix-core A fragments
+    // ring kernel: W1, heads and decoder fragments
     const uint4 *w1r = nullptr, *whr = nullptr;
     const uint2 *wdr = nullptr;
-    SplitGeometry sg;             // split kernel (fp32 detectors): its tiles and fragments (one allocation)
-    void *split_w = nullptr;
+    SplitGeometry sg;             // split kernel (fp32 detectors): its tiles and fragments
     const uint4 *w1x = nullptr, *whx = nullptr, *wdx = nullptr;
     const float *w1scale = nullptr;
-    void *stream_w = nullptr;     // streaming kernel: W1, heads and decoder fragments (one allocation)
-    const uint4 *w1s = nullptr;
+    const uint4 *w1s = nullptr;   // streaming kernel: W1, heads and decoder fragments
     const float *whs = nullptr, *wds = nullptr;
-    void *ext_x = nullptr;        // split variant pass: Wd2's f16 parts and the padded bd2
-    const uint4 *wd2x = nullptr;
+    const uint4 *wd2x = nullptr;  // split variant pass: Wd2's f16 parts and the padded bd2
     const float *bd2x = nullptr;
     float wd2_unscale = 1.0f;
-    void *ext_w = nullptr;        // fused variant pass: decoder-output fragments of Wd2
-    const float4 *wd2p = nullptr;
-    void *w1t = nullptr;          // [D][H] transposed W1
-    float *small = nullptr;       // every small weight array, one allocation
+    const float4 *wd2p = nullptr; // fused variant pass: decoder-output fragments of Wd2
+    const void *w1t = nullptr;    // [D][H] transposed W1
+    float *small = nullptr;       // every small weight array
     float *b1 = nullptr, *bh = nullptr, *bmu = nullptr, *blv = nullptr, *wmu = nullptr,
           *wlv = nullptr, *wd1 = nullptr, *bd1 = nullptr, *u = nullptr, *whp = nullptr,
           *wd1p = nullptr;
@@ -115,8 +113,7 @@ struct enova_detector_s {
     // only workspace of enova_detect_score_noalloc
     void *scratch = nullptr;
     // dense fp32 weights of the output variants: W1 [H][D], [Wmu; Wlv] [2L][H], [bmu | blv] [2L],
-    // Wd1 [H][L], Wd2 [D][H], bd2 [D] (one allocation)
-    float *dense = nullptr;
+    // Wd1 [H][L], Wd2 [D][H], bd2 [D]
     float *d_w1 = nullptr, *d_wml = nullptr, *d_bml = nullptr, *d_wd1 = nullptr, *d_wd2 = nullptr,
           *d_bd2 = nullptr;
     // workspace of the output variants (one chunk of windows; the fused pass's tile scan and map)
@@ -212,21 +209,67 @@ bool plan_geometry(const enova_detect_config &cfg, Geometry *g)
 
 namespace {
 
-template <typename T>
-enova_status dev_upload(T **dst, const void *src, size_t bytes)
-{
-    if (bytes == 0)
-        bytes = 16;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(dst), bytes);
-    if (e != hipSuccess)
-        return fail(ENOVA_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-    if (src) {
-        e = hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess)
-            return hip_fail(e, "hipMemcpy weights");
+// Arrays that are packed on the host and then go to the device together: small ones share an allocation
+// and a copy (each on its own took some 10 us, a third of a small detector's set-up). Large ones have
+// theirs: 4 MB in one allocation took 80 us to free.
+class Uploads {
+public:
+    ~Uploads()
+    {
+        for (const Part &q : parts_)
+            std::free(q.host);
     }
-    return ENOVA_OK;
-}
+    // n zeroed elements to fill; *dst is their device address once upload() has succeeded
+    template <typename T, typename P>
+    T *add(P **dst, size_t n)
+    {
+        const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
+        parts_.push_back(Part{dst, std::calloc(1, bytes), bytes});
+        if (!parts_.back().host)
+            throw std::bad_alloc();
+        return static_cast<T *>(parts_.back().host);
+    }
+    enova_status upload(std::vector<void *> &owned)
+    {
+        std::stable_partition(parts_.begin(), parts_.end(), [](const Part &q) { return q.bytes <= kTogether; });
+        std::vector<unsigned char> run;
+        for (size_t i = 0; i < parts_.size();) {
+            // small parts up to four times kTogether, or one large one
+            size_t n = i, bytes = 0;
+            run.clear();
+            do {
+                const Part &q = parts_[n++];
+                const unsigned char *host = static_cast<const unsigned char *>(q.host);
+                if (q.bytes <= kTogether)
+                    run.insert(run.end(), host, host + q.bytes);
+                bytes += q.bytes;
+            } while (n < parts_.size() && parts_[n].bytes <= kTogether && bytes + parts_[n].bytes <= 4 * kTogether);
+            owned.push_back(nullptr);
+            hipError_t e = hipMalloc(&owned.back(), bytes);
+            if (e != hipSuccess) {
+                owned.pop_back();
+                return fail(ENOVA_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
+            }
+            e = hipMemcpy(owned.back(), run.empty() ? parts_[i].host : run.data(), bytes, hipMemcpyHostToDevice);
+            if (e != hipSuccess)
+                return hip_fail(e, "hipMemcpy weights");
+            for (unsigned char *at = static_cast<unsigned char *>(owned.back()); i < n; ++i) {
+                std::memcpy(parts_[i].dst, &at, sizeof(at));
+                at += parts_[i].bytes;
+            }
+        }
+        return ENOVA_OK;
+    }
+
+private:
+    static constexpr size_t kTogether = 128 << 10;
+    struct Part {
+        void *dst;     // the pointer to set
+        void *host;
+        size_t bytes;
+    };
+    std::vector<Part> parts_;
+};
 
 template <typename T>
 enova_status ensure(T **buf, size_t *cap, size_t need)
@@ -246,21 +289,42 @@ enova_status ensure(T **buf, size_t *cap, size_t need)
     return ENOVA_OK;
 }
 
-// The f16 nearest to f (ties to even; |f| below 65520) and its value.
-uint16_t float_to_f16(float f, float *value)
+// Eight values as two f16 each, hi the nearest (ties to even; |v| below 65520) and lo the nearest to what is
+// left. Written without branches, for the compiler to take four at a time.
+inline uint32_t nearest_f16(float f, float *value)
 {
     uint32_t u;
     std::memcpy(&u, &f, sizeof(u));
     const uint32_t sign = u & 0x80000000u, a = u ^ sign;
-    if (a < 0x38800000u) {                       // below 2^-14: a multiple of 2^-24
-        volatile float t = f + 0.75f;            // 0.75 has 2^-24 as its last place
-        *value = t - 0.75f;
-        return static_cast<uint16_t>((sign >> 16) | static_cast<uint32_t>(std::fabs(*value) * 0x1p24f));
-    }
+    // from 2^-14 on: the mantissa rounded to 10 bits; below: a multiple of 2^-24, the last place of 0.5 to 1
     const uint32_t r = (a + 0xfffu + ((a >> 13) & 1u)) & ~0x1fffu;
-    const uint32_t v = r | sign;
-    std::memcpy(value, &v, sizeof(v));
-    return static_cast<uint16_t>((sign >> 16) | ((r - 0x38000000u) >> 13));
+    float m;
+    std::memcpy(&m, &a, sizeof(m));
+    const bool normal = a >= 0x38800000u;
+    const float low = ((normal ? 0.0f : m) + 0.75f) - 0.75f;
+    float big;
+    std::memcpy(&big, &r, sizeof(big));
+    const float v = normal ? big : low;
+    const uint32_t bits = normal ? (r - 0x38000000u) >> 13 : static_cast<uint32_t>(static_cast<int32_t>(low * 0x1p24f));
+    uint32_t q;
+    std::memcpy(&q, &v, sizeof(q));
+    q |= sign;
+    std::memcpy(value, &q, sizeof(q));
+    return bits | sign >> 16;
+}
+
+inline void f16_parts(const float (&v)[8], uint16_t *hi, uint16_t *lo)
+{
+    uint32_t h[8], l[8];
+    for (int e = 0; e < 8; ++e) {
+        float a, b;
+        h[e] = nearest_f16(v[e], &a);
+        l[e] = nearest_f16(v[e] - a, &b);
+    }
+    for (int e = 0; e < 8; ++e) {
+        hi[e] = static_cast<uint16_t>(h[e]);
+        lo[e] = static_cast<uint16_t>(l[e]);
+    }
 }
 
 // fn(src, kappa, e) for every weight src = t * M + m of a W1 row in the chunk order of super-rows of
@@ -269,16 +333,35 @@ template <typename F>
 void for_row(const Geometry &g, int mp, int cpr, int epc, F fn)
 {
     const int sh = epc == 8 ? 3 : 2;
-    for (int t = 0; t < g.W; ++t) {
-        const int q = t / g.S, base = (t - q * g.S) * mp;
+    for (int t = 0, q = 0, ts = 0; t < g.W; ++t) {
         for (int m = 0; m < g.M; ++m) {
-            const int el = base + m;
+            const int el = ts * mp + m;
             fn(t * g.M + m, q * cpr + (el >> sh), el & (epc - 1));
+        }
+        if (++ts == g.S) {
+            ts = 0;
+            ++q;
         }
     }
 }
 
-// Fragments of the ring kernel (bf16 detectors with 193..256 hidden units), one allocation:
+// W1's row h in the chunk order of g: at(kappa) is where the 16 bytes of chunk kappa go (without padded
+// metrics the row's elements as they come).
+template <typename F>
+void pack_row(const Geometry &g, const void *w1, int h, F at)
+{
+    const size_t esz = g.dtype == ENOVA_BF16 ? 2 : 4;
+    const unsigned char *row = static_cast<const unsigned char *>(w1) + static_cast<size_t>(h) * g.D * esz;
+    if (g.Mp == g.M)
+        for (int j = 0, kappa = 0; j < g.D; j += g.epc, ++kappa)
+            std::memcpy(at(kappa), row + j * esz, std::min(g.epc, g.D - j) * esz);
+    else
+        for_row(g, g.Mp, g.CPR, g.epc, [&](int j, int kappa, int e) {
+            std::memcpy(reinterpret_cast<unsigned char *>(at(kappa)) + e * esz, row + j * esz, esz);
+        });
+}
+
+// Fragments of the ring kernel (bf16 detectors with 193..256 hidden units):
 //  W1      step i = q * KS + sp (KS = P / 4), hidden block hb (16 rows), lane l: the 8 bf16 of
 //          W1[16 hb + l % 16] at the elements of chunk 4 sp + l / 16 of super-row q (zero past the
 //          window, the hidden width or the super-row's chunks); kPrefetchSteps zero steps follow.
@@ -287,7 +370,7 @@ void for_row(const Geometry &g, int mp, int cpr, int epc, F fn)
 //          16 (4w + 2m + 1) + 4 (l / 16) + t - 4 (t >= 4) -- the accumulator rows the lane holds.
 //  decoder [hidden block hb][hi, lo][lane l] 4 bf16: Wd1[16 hb + l % 16][4 (l / 16) + t].
 // Weights of the heads and the decoder are split into bf16 hi + lo (the remainder rounded).
-enova_status pack_ring(enova_detector d, const enova_detect_weights *w)
+hipError_t pack_ring(enova_detector d, const enova_detect_weights *w, Uploads &up)
 {
     const Geometry &g = d->g;
     const int H = g.H, L = g.L, D = g.D;
@@ -296,8 +379,8 @@ enova_status pack_ring(enova_detector d, const enova_detect_weights *w)
     const size_t n_w1 = static_cast<size_t>(NS + kPrefetchSteps) * HBT * 64;   // 16-byte fragments
     const size_t n_wh = static_cast<size_t>(kRingWaves) * 2 * 2 * 2 * 64;       // 16-byte fragments
     const size_t n_wd = static_cast<size_t>(HBT) * 2 * 64;                      // 8-byte fragments
-    std::vector<uint16_t> buf((n_w1 + n_wh) * 8 + n_wd * 4, 0);
-    uint16_t *w1r = buf.data(), *whr = w1r + n_w1 * 8, *wdr = whr + n_wh * 8;
+    uint16_t *w1r = up.add<uint16_t>(&d->w1r, n_w1 * 8), *whr = up.add<uint16_t>(&d->whr, n_wh * 8),
+             *wdr = up.add<uint16_t>(&d->wdr, n_wd * 4);
     const uint16_t *w1 = static_cast<const uint16_t *>(w->w1);
     for (int i = 0; i < NS; ++i) {
         const int q = i / KS, sp = i - q * KS;
@@ -353,15 +436,7 @@ enova_status pack_ring(enova_detector d, const enova_detect_weights *w)
                 wdr[((static_cast<size_t>(hb) * 2 + 0) * 64 + lane) * 4 + t] = hi;
                 wdr[((static_cast<size_t>(hb) * 2 + 1) * 64 + lane) * 4 + t] = lo;
             }
-    enova_status st = dev_upload(&d->ring_w, buf.data(), buf.size() * sizeof(uint16_t));
-    if (st != ENOVA_OK)
-        return st;
-    const uint4 *base = static_cast<const uint4 *>(d->ring_w);
-    d->w1r = base;
-    d->whr = base + n_w1;
-    d->wdr = reinterpret_cast<const uint2 *>(base + n_w1 + n_wh);
-    const hipError_t e = prepare_score_ring(g);
-    return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the ring scoring kernel");
+    return prepare_score_ring(g);
 }
 
 // Fragments of the streaming kernel's 16x16 matrix ops: W1 as A fragments
@@ -370,7 +445,7 @@ enova_status pack_ring(enova_detector d, const enova_detect_weights *w)
 // [Hp/16][4][2][64] floats (op (hb, r) of head 0 = mean, 1 = log-variance: lane l holds the head
 // row l%16 at hidden unit 16 hb + 4 (l/16) + r) and the decoder's hidden layer as [Hp/16][4][64]
 // floats (op (hb, r): lane l holds Wd1[16 hb + l%16][4 (l/16) + r]).
-enova_status pack_stream(enova_detector d, const enova_detect_weights *w)
+hipError_t pack_stream(enova_detector d, const enova_detect_weights *w, Uploads &up)
 {
     const Geometry &g = d->g;
     const int H = g.H, L = g.L, D = g.D, NHB = g.Hp / 16;
@@ -379,20 +454,14 @@ enova_status pack_stream(enova_detector d, const enova_detect_weights *w)
     const size_t n_w1 = static_cast<size_t>(steps) * NHB * 64;   // 16-byte fragments
     const size_t n_wh = static_cast<size_t>(NHB) * 4 * 2 * 64;   // floats
     const size_t n_wd = static_cast<size_t>(NHB) * 4 * 64;       // floats
-    std::vector<uint32_t> buf(n_w1 * 4 + n_wh + n_wd, 0u);
+    uint32_t *buf = up.add<uint32_t>(&d->w1s, n_w1 * 4);
+    float *wh = up.add<float>(&d->whs, n_wh), *wd = up.add<float>(&d->wds, n_wd);
     for (int h = 0; h < H; ++h) {
-        const int64_t row = static_cast<int64_t>(h) * D;
-        uint32_t *dst = buf.data() + (static_cast<size_t>(h >> 4) * 64 + (h & 15)) * 4;
-        for_row(g, g.Mp, g.CPR, g.epc, [&](int j, int kappa, int e) {
-            uint32_t *at = dst + (static_cast<size_t>(kappa >> 2) * NHB * 64 + (kappa & 3) * 16) * 4;
-            if (bf)
-                reinterpret_cast<uint16_t *>(at)[e] = static_cast<const uint16_t *>(w->w1)[row + j];
-            else
-                std::memcpy(at + e, static_cast<const float *>(w->w1) + row + j, 4);
+        uint32_t *dst = buf + (static_cast<size_t>(h >> 4) * 64 + (h & 15)) * 4;
+        pack_row(g, w->w1, h, [&](int kappa) {
+            return dst + (static_cast<size_t>(kappa >> 2) * NHB * 64 + (kappa & 3) * 16) * 4;
         });
     }
-    float *wh = reinterpret_cast<float *>(buf.data() + n_w1 * 4);
-    float *wd = wh + n_wh;
     for (int hb = 0; hb < NHB; ++hb)
         for (int r = 0; r < 4; ++r)
             for (int lane = 0; lane < 64; ++lane) {
@@ -407,14 +476,7 @@ enova_status pack_stream(enova_detector d, const enova_detect_weights *w)
                 if (hd < H && l < L)
                     wd[(hb * 4 + r) * 64 + lane] = w->wd1[hd * L + l];
             }
-    enova_status st = dev_upload(&d->stream_w, buf.data(), buf.size() * sizeof(uint32_t));
-    if (st != ENOVA_OK)
-        return st;
-    d->w1s = static_cast<const uint4 *>(d->stream_w);
-    d->whs = reinterpret_cast<const float *>(d->w1s + n_w1);
-    d->wds = d->whs + n_wh;
-    const hipError_t e = prepare_stream_score(g);
-    return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the streaming scoring kernel");
+    return prepare_stream_score(g);
 }
 
 // Row of register r for lane half g inside a 32x32 matrix-op accumulator block.
@@ -424,12 +486,12 @@ int crow(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
 // decoder hidden layer's accumulator): Wd2 as [D/32][HB][4][64 lanes] x 4 floats, where lane l,
 // component e of (ob, hb, r4) holds Wd2[32 ob + l%32][32 hb + crow(4 r4 + e, l/32)] (zero past
 // H).
-enova_status pack_ext_fused(enova_detector d, const enova_detect_weights *w)
+hipError_t pack_ext_fused(enova_detector d, const enova_detect_weights *w, Uploads &up)
 {
     const Geometry &g = d->g;
     const int H = g.H, D = g.D, HB = g.HB, nob = D / 32;
     const size_t n_w = static_cast<size_t>(nob) * HB * 4 * 64 * 4;
-    std::vector<float> buf(n_w, 0.0f);
+    float *buf = up.add<float>(&d->wd2p, n_w);
     for (int ob = 0; ob < nob; ++ob)
         for (int hb = 0; hb < HB; ++hb)
             for (int r4 = 0; r4 < 4; ++r4)
@@ -441,12 +503,7 @@ enova_status pack_ext_fused(enova_detector d, const enova_detect_weights *w)
                             buf[((((static_cast<size_t>(ob) * HB + hb) * 4 + r4) * 64 + lane) * 4) + e] =
                                 w->wd2[static_cast<int64_t>(j) * H + h];
                     }
-    enova_status st = dev_upload(&d->ext_w, buf.data(), buf.size() * sizeof(float));
-    if (st != ENOVA_OK)
-        return st;
-    d->wd2p = static_cast<const float4 *>(d->ext_w);
-    const hipError_t e = prepare_ext_fused(g);
-    return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the fused variant kernel");
+    return prepare_ext_fused(g);
 }
 
 // Weights the split kernel can take: all finite, none so large that a product of three layers could
@@ -497,7 +554,7 @@ bool split_weights_ok(const Geometry &g, const enova_detect_weights *w)
     return *mm.second <= kSplitMetrics * *mm.first;
 }
 
-// Fragments of the split kernel, one allocation:
+// Fragments of the split kernel:
 //  W1      step i, hidden block hb, part (hi, lo), lane l: the 8 f16 of W1[32 hb + l % 32] at chunk
 //          2i + l / 32 (8 elements; zero past the window, the hidden width or the row), each row
 //          scaled by 2^e with its largest |w| in [2^13, 2^14); kSplitPrefetch zero steps follow.
@@ -505,7 +562,7 @@ bool split_weights_ok(const Geometry &g, const enova_detect_weights *w)
 //          detectors' fragments (reduction slot t of lane half g is hidden row crow(8m + t, g),
 //          latent crow(t, g)), three parts of each weight.
 //  scale   2^-e / kSplitScale of each hidden row.
-enova_status pack_split(enova_detector d, const enova_detect_weights *w)
+hipError_t pack_split(enova_detector d, const enova_detect_weights *w, Uploads &up)
 {
     const Geometry &g = d->g;
     const SplitGeometry &sg = d->sg;
@@ -513,25 +570,32 @@ enova_status pack_split(enova_detector d, const enova_detect_weights *w)
     const float *w1 = static_cast<const float *>(w->w1);
     const size_t n_w1 = static_cast<size_t>(sg.nsteps + kSplitPrefetch) * HB * 2 * 64;   // 16-byte fragments
     const size_t n_wh = static_cast<size_t>(HB) * 2 * 3 * 64, n_wd = static_cast<size_t>(HB) * 3 * 64;
-    std::vector<uint16_t> buf((n_w1 + n_wh + n_wd) * 8 + static_cast<size_t>(g.Hp) * 2, 0);
-    uint16_t *w1x = buf.data(), *whx = w1x + n_w1 * 8, *wdx = whx + n_wh * 8;
-    float *scale = reinterpret_cast<float *>(wdx + n_wd * 8);
+    uint16_t *w1x = up.add<uint16_t>(&d->w1x, n_w1 * 8), *whx = up.add<uint16_t>(&d->whx, n_wh * 8),
+             *wdx = up.add<uint16_t>(&d->wdx, n_wd * 8);
+    float *scale = up.add<float>(&d->w1scale, g.Hp);
+    // the weight of every element of every chunk (g.D: none)
+    const int chunks = sg.Q * sg.CPR;
+    std::vector<int> at(static_cast<size_t>(chunks) * 8, g.D);
+    for_row(g, sg.Mp, sg.CPR, 8, [&](int j, int kappa, int e) { at[static_cast<size_t>(kappa) * 8 + e] = j; });
+    std::vector<float> row(g.D + 1, 0.0f);
     for (int h = 0; h < H; ++h) {
-        const float *row = w1 + static_cast<size_t>(h) * g.D;
+        const float *src = w1 + static_cast<size_t>(h) * g.D;
         float big = 0.0f;
         for (int j = 0; j < g.D; ++j)
-            big = std::max(big, std::fabs(row[j]));
+            big = std::max(big, std::fabs(src[j]));
         const int e = big > 0.0f ? std::min(13 - std::ilogb(big), 100) : 0;
-        const float up = std::ldexp(1.0f, e);
+        const float scaled = std::ldexp(1.0f, e);
         scale[h] = std::ldexp(1.0f, -e - 4);
+        for (int j = 0; j < g.D; ++j)
+            row[j] = src[j] * scaled;
         uint16_t *dst = w1x + (static_cast<size_t>(h >> 5) * 2 * 64 + (h & 31)) * 8;
-        for_row(g, sg.Mp, sg.CPR, 8, [&](int j, int kappa, int e) {
-            const float v = row[j] * up;
-            uint16_t *at = dst + (static_cast<size_t>(kappa >> 1) * HB * 2 * 64 + (kappa & 1) * 32) * 8 + e;
-            float hi, lo;
-            at[0] = float_to_f16(v, &hi);
-            at[64 * 8] = float_to_f16(v - hi, &lo);
-        });
+        for (int kappa = 0; kappa < chunks; ++kappa) {
+            float v[8];
+            for (int i = 0; i < 8; ++i)
+                v[i] = row[at[static_cast<size_t>(kappa) * 8 + i]];
+            uint16_t *to = dst + (static_cast<size_t>(kappa >> 1) * HB * 2 * 64 + (kappa & 1) * 32) * 8;
+            f16_parts(v, to, to + 64 * 8);
+        }
     }
     auto parts = [](float v, uint16_t *dst, size_t stride) {
         for (int q = 0; q < 3; ++q) {
@@ -554,24 +618,15 @@ enova_status pack_split(enova_detector d, const enova_detect_weights *w)
                 parts(h < H && l < L ? w->wd1[h * L + l] : 0.0f,
                       wdx + ((static_cast<size_t>(hb) * 3) * 64 + lane) * 8 + t, 64 * 8);
             }
-    enova_status st = dev_upload(&d->split_w, buf.data(), buf.size() * sizeof(uint16_t));
-    if (st != ENOVA_OK)
-        return st;
-    d->w1x = static_cast<const uint4 *>(d->split_w);
-    d->whx = d->w1x + n_w1;
-    d->wdx = d->whx + n_wh;
-    d->w1scale = reinterpret_cast<const float *>(d->wdx + n_wd);
-    hipError_t e = prepare_score_split(g, d->sg);
-    if (e == hipSuccess)
-        e = prepare_score_list(g);
-    return e == hipSuccess ? ENOVA_OK : hip_fail(e, "configure the split scoring kernel");
+    const hipError_t e = prepare_score_split(g, d->sg);
+    return e == hipSuccess ? prepare_score_list(g) : e;
 }
 
 // Fragments of the split variant pass: Wd2's rows in the padded order j' = t Mp + m as two f16 parts,
 // scaled by the power of two that puts the largest |weight| into [2^13, 2^14): [Dp/32][HB][2][hi,
 // lo][64 lanes] x 8, where slot t of (ob, hb, m), lane l is the weight of row 32 ob + l % 32 at hidden
 // unit 32 hb + crow(8 m + t, l / 32); bd2 padded the same way follows.
-enova_status pack_ext_split(enova_detector d, const enova_detect_weights *w)
+hipError_t pack_ext_split(enova_detector d, const enova_detect_weights *w, Uploads &uploads)
 {
     const Geometry &g = d->g;
     const int H = g.H, HB = g.HB, Mp = d->sg.Mp, Dp = ext_split_rows(g, d->sg);
@@ -582,34 +637,29 @@ enova_status pack_ext_split(enova_detector d, const enova_detect_weights *w)
     const float up = std::ldexp(1.0f, e);
     d->wd2_unscale = std::ldexp(1.0f, -e);
     const size_t n_w = static_cast<size_t>(Dp / 32) * HB * 2 * 2 * 64;   // 16-byte fragments
-    std::vector<uint16_t> buf(n_w * 8 + static_cast<size_t>(Dp) * 2, 0);
-    float *bd = reinterpret_cast<float *>(buf.data() + n_w * 8);
-    // slot of hidden unit h inside its block: crow(8 m + t, half) = h % 32
-    int slot[32];
-    for (int half = 0; half < 2; ++half)
-        for (int r = 0; r < 16; ++r)
-            slot[crow(r, half)] = ((r >> 3) * 2 * 64 + half * 32) * 8 + (r & 7);
+    uint16_t *buf = uploads.add<uint16_t>(&d->wd2x, n_w * 8);
+    float *bd = uploads.add<float>(&d->bd2x, Dp);
+    std::vector<float> units(g.Hp, 0.0f);
     for (int t = 0; t < g.W; ++t)
         for (int m = 0; m < g.M; ++m) {
             const int j = t * Mp + m;
             bd[j] = w->bd2[t * g.M + m];
             const float *row = w->wd2 + static_cast<int64_t>(t * g.M + m) * H;
-            uint16_t *dst = buf.data() + (static_cast<size_t>(j >> 5) * HB * 2 * 2 * 64 + (j & 31)) * 8;
-            for (int h = 0; h < H; ++h) {
-                uint16_t *at = dst + static_cast<size_t>(h >> 5) * 2 * 2 * 64 * 8 + slot[h & 31];
-                float hi, lo;
-                const float v = row[h] * up;
-                at[0] = float_to_f16(v, &hi);
-                at[64 * 8] = float_to_f16(v - hi, &lo);
-            }
+            for (int h = 0; h < H; ++h)
+                units[h] = row[h] * up;
+            uint16_t *dst = buf + (static_cast<size_t>(j >> 5) * HB * 2 * 2 * 64 + (j & 31)) * 8;
+            for (int f = 0; f < HB * 2; ++f)          // hidden block f / 2, fragment f % 2 of it
+                for (int half = 0; half < 2; ++half) {
+                    // crow(8 (f % 2) + t, half), t < 8: two runs of four
+                    const float *from = &units[16 * f + 4 * half];
+                    float v[8];
+                    for (int i = 0; i < 8; ++i)
+                        v[i] = from[8 * (i >> 2) + (i & 3)];
+                    uint16_t *to = dst + (static_cast<size_t>(f) * 2 * 64 + half * 32) * 8;
+                    f16_parts(v, to, to + 64 * 8);
+                }
         }
-    enova_status st = dev_upload(&d->ext_x, buf.data(), buf.size() * sizeof(uint16_t));
-    if (st != ENOVA_OK)
-        return st;
-    d->wd2x = static_cast<const uint4 *>(d->ext_x);
-    d->bd2x = reinterpret_cast<const float *>(d->wd2x + n_w);
-    const hipError_t er = prepare_ext_split(g, d->sg);
-    return er == hipSuccess ? ENOVA_OK : hip_fail(er, "configure the split variant kernel");
+    return prepare_ext_split(g, d->sg);
 }
 
 // Weights of the decoder's output that the split variant pass can take: finite and below 2^20 (as
@@ -647,8 +697,10 @@ void free_detector(enova_detector d)
 {
     if (!d)
         return;
-    void *ptrs[] = {d->w1p, d->w1t, d->small, d->stats, d->tiles, d->tile_map, d->cal, d->pot,
-                    d->peaks, d->blk, d->pot_part, d->dense, d->ext_ws, d->ring_w, d->stream_w, d->ext_w, d->split_w, d->ext_x};
+    for (void *p : d->weights)
+        (void)hipFree(p);
+    void *ptrs[] = {d->stats, d->tiles, d->tile_map, d->cal, d->pot,
+                    d->peaks, d->blk, d->pot_part, d->ext_ws};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -705,6 +757,8 @@ const char *enova_status_str(enova_status s)
 
 const char *enova_last_error(void) { return g_last_error.c_str(); }
 
+static enova_status fill_detector(enova_detector d, const enova_detect_weights *w);
+
 enova_status enova_detect_init(const enova_detect_config *config, const enova_detect_weights *w,
                                enova_detector *out)
 {
@@ -753,9 +807,26 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
             return hip_fail(e, "device scratch lookup");
         }
     }
+    try {
+        st = fill_detector(d, w);
+    } catch (const std::bad_alloc &) {
+        st = fail(ENOVA_ENOMEM, "host allocation");
+    }
+    if (st != ENOVA_OK) {
+        free_detector(d);
+        return st;
+    }
+    *out = d;
+    return ENOVA_OK;
+}
 
+// Packs the weights for the kernels that the shape takes and uploads them.
+static enova_status fill_detector(enova_detector d, const enova_detect_weights *w)
+{
+    const Geometry &g = d->g;
     const int H = g.H, L = g.L, D = g.D, Hp = g.Hp;
     const bool bf = g.dtype == ENOVA_BF16;
+    Uploads up;
     // small arrays: b1[Hp] bd1[Hp] u[Hp] bh[32] bmu[L] blv[L] wmu[L*H] wlv[L*H] wd1[H*L]
     //               whp[HB*16*64] wd1p[HB*8*64]
     const size_t n_whp = d->kind == 2 ? static_cast<size_t>(g.HB) * 16 * 64 : 0;
@@ -779,7 +850,7 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
     const size_t o_wmu = take(static_cast<size_t>(L) * H);
     const size_t o_wlv = take(static_cast<size_t>(L) * H);
     const size_t o_wd1 = take(static_cast<size_t>(H) * L);
-    std::vector<float> small(o, 0.0f);
+    float *small = up.add<float>(&d->small, o);
 
     std::vector<double> cs(H, 0.0);
     for (int j = 0; j < D; ++j)
@@ -868,11 +939,74 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
                     small[o_wd1p + (static_cast<size_t>(hb) * 8 + r) * 64 + lane] = v;
                 }
     }
-    st = dev_upload(&d->small, small.data(), small.size() * sizeof(float));
-    if (st != ENOVA_OK) {
-        free_detector(d);
-        return st;
+    // dense fp32 copies for the output variants (16-byte aligned sub-arrays)
+    float *w1 = up.add<float>(&d->d_w1, static_cast<size_t>(H) * D);
+    if (bf) {
+        const uint16_t *src = static_cast<const uint16_t *>(w->w1);
+        for (size_t i = 0; i < static_cast<size_t>(H) * D; ++i)
+            w1[i] = bf16_bits_to_float(src[i]);
+    } else {
+        std::memcpy(w1, w->w1, sizeof(float) * static_cast<size_t>(H) * D);
     }
+    float *wml = up.add<float>(&d->d_wml, 2 * static_cast<size_t>(L) * H), *bml = up.add<float>(&d->d_bml, 2 * L);
+    std::memcpy(wml, w->wmu, sizeof(float) * L * H);
+    std::memcpy(wml + static_cast<size_t>(L) * H, w->wlv, sizeof(float) * L * H);
+    std::memcpy(bml, w->bmu, sizeof(float) * L);
+    std::memcpy(bml + L, w->blv, sizeof(float) * L);
+    std::memcpy(up.add<float>(&d->d_wd1, static_cast<size_t>(H) * L), w->wd1, sizeof(float) * H * L);
+    std::memcpy(up.add<float>(&d->d_wd2, static_cast<size_t>(D) * H), w->wd2, sizeof(float) * static_cast<size_t>(D) * H);
+    std::memcpy(up.add<float>(&d->d_bd2, D), w->bd2, sizeof(float) * D);
+
+    hipError_t e = hipSuccess;
+    const char *what = "";
+    auto pack = [&](hipError_t (*fn)(enova_detector, const enova_detect_weights *, Uploads &), const char *kernel) {
+        if (e == hipSuccess) {
+            e = fn(d, w, up);
+            what = kernel;
+        }
+    };
+    if (d->kind == 1) {
+        // transposed W1 [D][H] in the storage type
+        const size_t esz = bf ? 2 : 4;
+        unsigned char *wt = up.add<unsigned char>(&d->w1t, static_cast<size_t>(D) * H * esz);
+        for (int h = 0; h < H; ++h)
+            for (int j = 0; j < D; ++j) {
+                const size_t dst = (static_cast<size_t>(j) * H + h) * esz;
+                const size_t src = (static_cast<size_t>(h) * D + j) * esz;
+                std::memcpy(&wt[dst], static_cast<const unsigned char *>(w->w1) + src, esz);
+            }
+    } else {
+        // A fragments: step i, hidden block hb, lane -> 16 bytes of W1[h][chunk 2i + lane/32]
+        // kPrefetchSteps zero steps follow the last one: the kernel's W1 prefetch runs past it
+        const int steps = g.KC / 2;
+        const size_t frag = static_cast<size_t>(steps + kPrefetchSteps) * g.HB * 64;
+        uint32_t *pk = up.add<uint32_t>(&d->w1p, frag * 4);
+        for (int h = 0; h < H; ++h) {
+            uint32_t *dst = pk + (static_cast<size_t>(h >> 5) * 64 + (h & 31)) * 4;
+            pack_row(g, w->w1, h, [&](int kappa) {
+                return dst + (static_cast<size_t>(kappa >> 1) * g.HB * 64 + (kappa & 1) * 32) * 4;
+            });
+        }
+        pack([](enova_detector q, const enova_detect_weights *, Uploads &) { return prepare_score_mfma(q->g); },
+             "configure matrix-core kernel");
+        if (g.ring)
+            pack(pack_ring, "configure the ring scoring kernel");
+        d->sg = plan_split(g);
+        d->sg.ok = d->sg.ok && score_list_lds(g) <= kLdsLimit && split_weights_ok(g, w);
+        if (d->sg.ok)
+            pack(pack_split, "configure the split scoring kernel");
+        if (stream_score_supported(g))
+            pack(pack_stream, "configure the streaming scoring kernel");
+        if (ext_split_supported(g, d->sg) && split_output_ok(g, w))
+            pack(pack_ext_split, "configure the split variant kernel");
+        else if (ext_fused_supported(g))
+            pack(pack_ext_fused, "configure the fused variant kernel");
+    }
+    if (e != hipSuccess)
+        return hip_fail(e, what);
+    const enova_status st = up.upload(d->weights);
+    if (st != ENOVA_OK)
+        return st;
     d->b1 = d->small + o_b1;
     d->bd1 = d->small + o_bd1;
     d->u = d->small + o_u;
@@ -884,100 +1018,6 @@ enova_status enova_detect_init(const enova_detect_config *config, const enova_de
     d->wd1 = d->small + o_wd1;
     d->whp = d->small + o_whp;
     d->wd1p = d->small + o_wd1p;
-
-    {
-        // dense fp32 copies for the output variants (16-byte aligned sub-arrays)
-        size_t od = 0;
-        auto takd = [&od](size_t n) {
-            const size_t at = od;
-            od += (n + 3) / 4 * 4;
-            return at;
-        };
-        const size_t p_w1 = takd(static_cast<size_t>(H) * D), p_wml = takd(2 * static_cast<size_t>(L) * H),
-                     p_bml = takd(2 * static_cast<size_t>(L)), p_wd1 = takd(static_cast<size_t>(H) * L),
-                     p_wd2 = takd(static_cast<size_t>(D) * H), p_bd2 = takd(D);
-        std::vector<float> dn(od, 0.0f);
-        if (bf) {
-            const uint16_t *src = static_cast<const uint16_t *>(w->w1);
-            for (size_t i = 0; i < static_cast<size_t>(H) * D; ++i)
-                dn[p_w1 + i] = bf16_bits_to_float(src[i]);
-        } else {
-            std::memcpy(&dn[p_w1], w->w1, sizeof(float) * static_cast<size_t>(H) * D);
-        }
-        std::memcpy(&dn[p_wml], w->wmu, sizeof(float) * L * H);
-        std::memcpy(&dn[p_wml + static_cast<size_t>(L) * H], w->wlv, sizeof(float) * L * H);
-        std::memcpy(&dn[p_bml], w->bmu, sizeof(float) * L);
-        std::memcpy(&dn[p_bml + L], w->blv, sizeof(float) * L);
-        std::memcpy(&dn[p_wd1], w->wd1, sizeof(float) * H * L);
-        std::memcpy(&dn[p_wd2], w->wd2, sizeof(float) * static_cast<size_t>(D) * H);
-        std::memcpy(&dn[p_bd2], w->bd2, sizeof(float) * D);
-        st = dev_upload(&d->dense, dn.data(), dn.size() * sizeof(float));
-        if (st != ENOVA_OK) {
-            free_detector(d);
-            return st;
-        }
-        d->d_w1 = d->dense + p_w1;
-        d->d_wml = d->dense + p_wml;
-        d->d_bml = d->dense + p_bml;
-        d->d_wd1 = d->dense + p_wd1;
-        d->d_wd2 = d->dense + p_wd2;
-        d->d_bd2 = d->dense + p_bd2;
-    }
-
-    if (d->kind == 1) {
-        // transposed W1 [D][H] in the storage type
-        const size_t esz = bf ? 2 : 4;
-        std::vector<unsigned char> wt(static_cast<size_t>(D) * H * esz);
-        for (int h = 0; h < H; ++h)
-            for (int j = 0; j < D; ++j) {
-                const size_t dst = (static_cast<size_t>(j) * H + h) * esz;
-                const size_t src = (static_cast<size_t>(h) * D + j) * esz;
-                std::memcpy(&wt[dst], static_cast<const unsigned char *>(w->w1) + src, esz);
-            }
-        st = dev_upload(&d->w1t, wt.data(), wt.size());
-    } else {
-        // A fragments: step i, hidden block hb, lane -> 16 bytes of W1[h][chunk 2i + lane/32]
-        // kPrefetchSteps zero steps follow the last one: the kernel's W1 prefetch runs past it
-        const int steps = g.KC / 2;
-        const size_t frag = static_cast<size_t>(steps + kPrefetchSteps) * g.HB * 64;
-        std::vector<uint32_t> pk(frag * 4, 0u);
-        for (int h = 0; h < H; ++h) {
-            const int64_t row = static_cast<int64_t>(h) * D;
-            uint32_t *dst = pk.data() + (static_cast<size_t>(h >> 5) * 64 + (h & 31)) * 4;
-            for_row(g, g.Mp, g.CPR, g.epc, [&](int j, int kappa, int e) {
-                uint32_t *at = dst + (static_cast<size_t>(kappa >> 1) * g.HB * 64 + (kappa & 1) * 32) * 4;
-                if (bf)
-                    reinterpret_cast<uint16_t *>(at)[e] = static_cast<const uint16_t *>(w->w1)[row + j];
-                else
-                    std::memcpy(at + e, static_cast<const float *>(w->w1) + row + j, 4);
-            });
-        }
-        st = dev_upload(&d->w1p, pk.data(), pk.size() * sizeof(uint32_t));
-        if (st == ENOVA_OK) {
-            hipError_t e = prepare_score_mfma(g);
-            if (e != hipSuccess)
-                st = hip_fail(e, "configure matrix-core kernel");
-        }
-        if (st == ENOVA_OK && g.ring)
-            st = pack_ring(d, w);
-        if (st == ENOVA_OK) {
-            d->sg = plan_split(g);
-            d->sg.ok = d->sg.ok && score_list_lds(g) <= kLdsLimit && split_weights_ok(g, w);
-            if (d->sg.ok)
-                st = pack_split(d, w);
-        }
-        if (st == ENOVA_OK && stream_score_supported(g))
-            st = pack_stream(d, w);
-        if (st == ENOVA_OK && ext_split_supported(g, d->sg) && split_output_ok(g, w))
-            st = pack_ext_split(d, w);
-        if (st == ENOVA_OK && !d->wd2x && ext_fused_supported(g))
-            st = pack_ext_fused(d, w);
-    }
-    if (st != ENOVA_OK) {
-        free_detector(d);
-        return st;
-    }
-    *out = d;
     return ENOVA_OK;
 }
 
@@ -1187,7 +1227,7 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     p.n_windows = n_windows;
     p.mean = ref_mean;
     p.std = ref_std;
-    p.w1p = static_cast<const uint4 *>(det->w1p);
+    p.w1p = det->w1p;
     p.whp = det->whp;
     p.wd1p = det->wd1p;
     p.w1t = det->w1t;
@@ -1380,7 +1420,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         fp.tile_stream = tmap;
         fp.mean = ref_mean;
         fp.std = ref_std;
-        fp.w1p = static_cast<const uint4 *>(det->w1p);
+        fp.w1p = det->w1p;
         fp.cst = det->whp;
         fp.wd2p = det->wd2p;
         fp.bd2 = det->d_bd2;
