@@ -976,14 +976,19 @@ bool ext_split_supported(const Geometry &g, const SplitGeometry &sg)
 
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg) { return padded_d(g, sg); }
 
-// A tile's chain of steps takes about 0.18 us per padded element of a window however few tiles there
-// are (73 to 93 us at Dp = 480, 205 us at 1024), and that is the pass until the tiles fill the chip; the
-// chunked evaluation spreads few windows over its products' tiles, 50 us and 1.1e-5 us per window and
-// element (7 metrics, W = 60, H = 64: 48 us for 1000 windows, 73 for 4000, 142 for 16000). They meet at
-// n D = (0.18 Dp - 50) / 1.1e-5.
+// On few windows the pass takes as long as one tile's chain of steps, some 22 us and 0.06 us + 0.45 ns per
+// (padded) hidden unit for every padded element of a window; the chunked evaluation spreads few windows
+// over its products' tiles, 50 us and 1e-5 us per window and element. Measured, in us, this pass and the
+// chunked one at 500, 4000, 8000, 16000 windows:
+//   7 metrics, W = 60, H = 64, tanh (Dp = 480)     73-76    58  72  88 123
+//   5 metrics, W = 64, H = 128      (Dp = 512)     83-87    56  70  85 119
+//   12 metrics, W = 64, H = 64      (Dp = 1024)   108-113   55  78 108 157
+//   1 metric, W = 60, H = 64        (Dp = 480)     57-59    51  51  54  64
+//   3 metrics, W = 30, H = 24       (Dp = 240)     40-43    50  56  67  90
 bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows)
 {
-    return n_windows * g.D + 4500000 >= 16400LL * padded_d(g, sg);
+    const double chain = 22.0 + padded_d(g, sg) * (0.06 + 0.00045 * g.Hp);
+    return 50.0 + 1e-5 * static_cast<double>(n_windows) * g.D >= chain;
 }
 
 hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg)
