@@ -440,8 +440,10 @@ enova_status enova_detect_flag(enova_detector det, const float *scores, int64_t 
                                float threshold, uint8_t *out_flags, hipStream_t stream);
 
 /*
- * Kernel timing: when enabled, enova_detect_score brackets its scoring kernel (and, when it
- * computes them, the reference-statistics kernel) with HIP events on `stream`;
+ * Kernel timing: when enabled, enova_detect_score brackets its scoring kernels (and, when it
+ * computes them, all launches that form the reference statistics: on the matrix-core path with
+ * the tile scan that shares one, and for few streams with the tile map, which closes sums that
+ * several blocks formed) with HIP events on `stream`;
  * enova_detect_kernel_times waits for the last call's events and reports milliseconds
  * (a kernel that did not run reports 0).
  */

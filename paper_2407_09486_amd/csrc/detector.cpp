@@ -1216,7 +1216,9 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         if (e != hipSuccess)
             return hip_fail(e, "reference statistics kernel");
     }
-    if (timing && own)
+    // chunk sums are closed by the tile map's launch
+    const bool stats_in_map = own && det->kind == 2 && wk.part;
+    if (timing && own && !stats_in_map)
         (void)hipEventRecord(det->ev[1], stream);
     det->ran_stats = timing && own;
     ScoreParams p{};
@@ -1259,6 +1261,8 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
         e = launch_prep_map(g, x, soff, wk.tiles, n, grid, wk.tile_map, p.marks, own_mean, own_std, wk.part, stream);
         if (e != hipSuccess)
             return hip_fail(e, "tile map kernel");
+        if (timing && stats_in_map)
+            (void)hipEventRecord(det->ev[1], stream);
         p.tile_stream = wk.tile_map;
         if (timing)
             (void)hipEventRecord(det->ev[2], stream);
