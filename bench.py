@@ -665,7 +665,7 @@ def variants_main(args, cfg):
 
     def step():
         binding.enova_detect_score_ext(det.handle, x, so, wo, work.n_streams, N, None, None, norm, sc, md, mdm, rec)
-    kernel = "k_ext_split" if det.ext_fused() else "chunked"
+    kernel = {"split": "k_ext_split", "fused": "k_ext_fused", "chunked": "chunked"}[det.ext_route(work.n_streams, N)]
     for _ in range(args.warmup):
         step()
     binding.enova_detect_set_timing(det.handle, True)
@@ -691,9 +691,9 @@ def variants_main(args, cfg):
     km = float(np.mean(k_ms))
     fpw = variants_flops_per_window(cfg)
     achieved = fpw * N / (km / 1e3) / 1e12
-    fused = kernel == "k_ext_split"
-    # the fused pass takes three f16 products for each fp32 one, the chunked evaluation the fp32 units
-    peak = PEAK_TFLOPS["bf16"] / 3.0 if fused else PEAK_TFLOPS["f32"]
+    fused = kernel != "chunked"
+    # the split pass takes three f16 products for each fp32 one, the others the fp32 units
+    peak = PEAK_TFLOPS["bf16"] / 3.0 if kernel == "k_ext_split" else PEAK_TFLOPS["f32"]
     out = {
         "metric": "windows evaluated/sec (KL score, md, per-metric md vector, reconstruction error)",
         "value": round(N / (ms / 1e3), 1), "unit": "windows/s", "n_gpus": 1, "steps": args.steps,

@@ -347,11 +347,11 @@ enova_status enova_train_destroy(enova_trainer t);
  * metric, out_recon_err = mean_j (v_j - m'_j)^2 (device outputs; any may be NULL; with the last
  * three NULL the decoder is not evaluated). ref_mean /
  * ref_std as in enova_detect_score (NULL: computed; ignored for ENOVA_NORM_WINDOW). M <= 4096.
- * enova_detect_ext_mode tells whether a detector's windows take one fused launch or are
- * evaluated in chunks.
- * The products run in fp32 on the matrix cores (x and W1 of a bf16 detector are bf16 values;
- * v is rounded to bf16 as in enova_detect_score). Asynchronous. Errors: EINVAL, EUNSUPPORTED,
- * ENOMEM, EHIP.
+ * enova_detect_ext_route tells which of three evaluations a call takes. The products accumulate in
+ * fp32 on the matrix cores, from fp32 operands or, in the split evaluation, from two f16 parts of
+ * each (22 to 23 bits; windows outside the parts' range from fp32 operands). x and W1 of a bf16
+ * detector are bf16 values; v is rounded to bf16 as in enova_detect_score. Asynchronous. Errors:
+ * EINVAL, EUNSUPPORTED, ENOMEM, EHIP.
  */
 typedef enum { ENOVA_NORM_REFERENCE = 0, ENOVA_NORM_WINDOW = 1 } enova_norm;
 
@@ -364,14 +364,23 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
  * from its first to its last kernel, milliseconds. */
 enova_status enova_detect_ext_time(enova_detector det, double *ms);
 
-/* How enova_detect_score_ext evaluates this detector's windows (fixed at init): *fused = 1 for
- * one pass per call over the raw steps that stages each tile's raw steps once and keeps every window's v, hidden
- * layers and decoder output on chip (fp32 detectors of 4, 8 or 16 metrics, at most 128 hidden
- * units -- 64 with tanh and 16 metrics --, at most 16 latent units, W*M a multiple of 32, and a
- * tile that fits half a compute unit's LDS); 0 for every other shape: other metric counts up to 16
- * with at most 128 hidden units take one pass over padded steps where their tile fits, the rest the
- * chunked evaluation of normalised windows in device memory. Errors: EINVAL. */
+/* *fused = 1 for detectors of the shapes that enova_detect_score_ext always evaluates in one pass over
+ * the raw steps, whatever the call (fixed at init): fp32 detectors of 4, 8 or 16 metrics, at most 128
+ * hidden units -- 64 with tanh and 16 metrics --, at most 16 latent units, W*M a multiple of 32, and
+ * a tile that fits half a compute unit's LDS; else 0. Errors: EINVAL. */
 enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused);
+
+/* How an enova_detect_score_ext call of n_streams and n_windows evaluates its windows:
+ *   ENOVA_EXT_SPLIT    one pass that stages each tile's raw steps once and keeps every window's v, hidden
+ *                      layers and decoder output on chip, products from f16 parts: fp32 detectors of at
+ *                      most 16 metrics, 128 hidden and 16 latent units whose steps pad to 8 or 16 metrics
+ *                      and whose tile fits half a compute unit's LDS, with weights that the parts hold as
+ *                      well as fp32 does; unless *fused is 1 only calls of enough windows
+ *   ENOVA_EXT_FUSED    such a pass in fp32: the other detectors with *fused = 1
+ *   ENOVA_EXT_CHUNKED  normalised windows in device memory, chunk by chunk, in fp32: all others
+ * The evaluations differ in rounding only. Errors: EINVAL. */
+enum { ENOVA_EXT_CHUNKED = 0, ENOVA_EXT_FUSED = 1, ENOVA_EXT_SPLIT = 2 };
+enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t *route);
 
 /*
  * Configuration scans (Section IV-A, Eqs. (4)-(6), Table II) over the same monitoring series.

@@ -1308,6 +1308,27 @@ enova_status enova_detect_score_noalloc(enova_detector det, const void *x, const
                         out_flags, stream, true);
 }
 
+}  // extern "C"
+
+namespace {
+
+// Tiles of a fused pass over n streams, its grid.
+int64_t ext_tiles(int32_t n, int64_t n_windows) { return (n_windows + kExtFusedNb - 1) / kExtFusedNb + n; }
+
+// The evaluation of a variants call (ENOVA_EXT_*). A shape that only the split pass takes goes to the
+// chunked evaluation also where its tiles are more than a launch can have.
+int ext_route(enova_detector d, int32_t n, int64_t n_windows)
+{
+    if (d->wd2x && (ext_fused_supported(d->g) ||
+                    (ext_tiles(n, n_windows) <= 0x7fffffffLL && ext_split_pays(d->g, d->sg, n_windows))))
+        return ENOVA_EXT_SPLIT;
+    return d->wd2p ? ENOVA_EXT_FUSED : ENOVA_EXT_CHUNKED;
+}
+
+}  // namespace
+
+extern "C" {
+
 enova_status enova_detect_score_ext(enova_detector det, const void *x, const int64_t *soff, const int64_t *woff,
                                     int32_t n, int64_t n_windows, const float *ref_mean, const float *ref_std,
                                     int32_t norm, float *out_scores, float *out_md, float *out_md_metric,
@@ -1339,10 +1360,11 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
                 return hip_fail(e, "hipEventCreate");
     }
     const int D = g.D, H = g.H, L = g.L, M = g.M;
-    const bool split = det->wd2x && (ext_fused_supported(g) || ext_split_pays(g, det->sg, n_windows));
-    if (split || det->wd2p) {
+    const int route = ext_route(det, n, n_windows);
+    if (route != ENOVA_EXT_CHUNKED) {
         // fused pass: one block per 256-window tile, every output written directly
-        const int64_t grid = (n_windows + kExtFusedNb - 1) / kExtFusedNb + n;
+        const bool split = route == ENOVA_EXT_SPLIT;
+        const int64_t grid = ext_tiles(n, n_windows);
         if (grid > 0x7fffffffLL)
             return fail(ENOVA_EUNSUPPORTED, "too many tiles (%lld)", static_cast<long long>(grid));
         const bool stats = norm == ENOVA_NORM_REFERENCE && !ref_mean;
@@ -1698,6 +1720,16 @@ enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused)
     if (!det || !fused)
         return fail(ENOVA_EINVAL, "NULL argument");
     *fused = ext_fused_supported(det->g) && det->kind == 2 ? 1 : 0;
+    return ENOVA_OK;
+}
+
+enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t *route)
+{
+    if (!det || !route)
+        return fail(ENOVA_EINVAL, "NULL argument");
+    if (n_streams < 0 || n_windows < 0)
+        return fail(ENOVA_EINVAL, "n_streams and n_windows must be >= 0");
+    *route = ext_route(det, n_streams, n_windows);
     return ENOVA_OK;
 }
 

@@ -1,6 +1,7 @@
 """The output variants on the 16-bit matrix cores: padded metric counts, tile edges, output rows that end
 inside a 32-row block, hidden layers of one to four blocks, and the windows outside the range of the 16-bit
-parts (evaluated one by one in fp32), against the fp64 oracle. Sums of D products in fp32 differ by about
+parts (evaluated in fp32, up to 64 at a time), against the fp64 oracle. Every call asserts the evaluation it
+takes: calls of few windows take the chunked one at some shapes, and the split pass with a long stream added. Sums of D products in fp32 differ by about
 sqrt(D) 2^-24 of their scale; the tests allow 3e-6 in the 2-norm (D <= 1024)."""
 import numpy as np
 import pytest
@@ -12,11 +13,12 @@ from paper_2407_09486_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-def _run(cfg, weights, w, norm):
+def _run(cfg, weights, w, norm, route="split", pairs=None):
     import torch
     det = detector(cfg, weights)
     x, so = upload(w)
     woff = det.window_offsets(w.stream_offsets)
+    assert det.ext_route(len(w.stream_offsets) - 1, int(woff[-1])) == route
     out = det.score_ext(x, so, torch.from_numpy(woff).cuda(), int(woff[-1]), norm=norm)
     torch.cuda.synchronize()
     res = [o.cpu().numpy().astype(np.float64) for o in out]
@@ -24,8 +26,21 @@ def _run(cfg, weights, w, norm):
     ref = ov.score_ext(w.values_f64(), w.stream_offsets, window=cfg.window, stride=cfg.stride,
                        weights={k: np.asarray(getattr(weights, k), np.float64) for k in
                                 ("w1", "b1", "wmu", "bmu", "wlv", "blv", "wd1", "bd1", "wd2", "bd2")},
-                       act=cfg.act, norm=norm, ref_frac=cfg.ref_frac)
+                       act=cfg.act, norm=norm, ref_frac=cfg.ref_frac, pairs=pairs)
+    if pairs is not None:
+        res = [r[[woff[i] + k for i, k in pairs]] for r in res]
     return res, ref
+
+
+def _with_long_stream(lengths, W, S, windows):
+    """The lengths with a stream of so many windows behind the first two, and the windows to check: all of the
+    other streams, and of the long one its first, last and every 97th."""
+    if not windows:
+        return lengths, None
+    lengths = lengths[:2] + [W + (windows - 1) * S] + lengths[2:]
+    n = [max(0, (T - W) // S + 1) if T >= W else 0 for T in lengths]
+    pairs = [(i, k) for i in range(len(n)) for k in range(n[i]) if i != 2 or k % 97 == 0 or k == n[2] - 1]
+    return lengths, pairs
 
 
 def _check(res, ref, sel):
@@ -43,18 +58,22 @@ def _check(res, ref, sel):
 
 
 @pytest.mark.parametrize("norm", ["reference", "window"])
-@pytest.mark.parametrize("M,W,S,H,act", [(7, 9, 1, 64, "tanh"), (5, 33, 8, 32, "relu"), (12, 11, 1, 128, "tanh"),
-                                         (16, 14, 3, 100, "tanh"), (1, 50, 1, 40, "relu"), (8, 6, 9, 128, "relu"),
-                                         (9, 7, 1, 20, "relu"), (16, 64, 1, 128, "relu")])
-def test_tile_and_block_edges(norm, M, W, S, H, act):
+@pytest.mark.parametrize("M,W,S,H,act,more,route", [
+    (7, 9, 1, 64, "tanh", 0, "split"), (5, 33, 8, 32, "relu", 0, "chunked"), (5, 32, 3, 32, "relu", 0, "split"),
+    (12, 11, 1, 128, "tanh", 0, "split"), (16, 14, 3, 100, "tanh", 0, "chunked"), (16, 14, 1, 100, "tanh", 0, "split"),
+    (1, 50, 1, 40, "relu", 0, "chunked"), (1, 50, 1, 40, "relu", 20000, "split"), (8, 6, 9, 128, "relu", 0, "chunked"),
+    (8, 3, 5, 128, "relu", 0, "split"), (9, 7, 1, 20, "relu", 0, "split"), (16, 64, 1, 128, "relu", 0, "split"),
+    (7, 60, 1, 64, "tanh", 0, "chunked"), (7, 60, 1, 64, "tanh", 4000, "split")])
+def test_tile_and_block_edges(norm, M, W, S, H, act, more, route):
     counts = [1, 31, 64, 65, 255, 257, 513]
     lengths = [W + (k - 1) * S for k in counts] + [W - 1, 0, W + 100 * S + S - 1]
+    lengths, pairs = _with_long_stream(lengths, W, S, more)
     cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, act=act, n_streams=len(lengths))
     log(f"[ext split] {norm} M={M} W={W} S={S} H={H} {act}")
     rng = np.random.default_rng(M + W)
     offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
     w = wl.from_arrays(cfg, rng.standard_normal((int(offs[-1]), M)) * np.exp(rng.uniform(-2, 2, M)) + 3, offs)
-    res, ref = _run(cfg, wl.make_weights(cfg, bias_scale=0.1), w, norm)
+    res, ref = _run(cfg, wl.make_weights(cfg, bias_scale=0.1), w, norm, route, pairs)
     _check(res, ref, np.arange(len(ref["score"])))
 
 
@@ -113,22 +132,23 @@ def test_decoder_output_scales(norm, where):
         weights.bd1[:H // 2] *= 1e-6
         weights.wd2[:, :H // 2] *= 1e6
     log(f"[ext split] decoder scales {norm} {where}, largest |Wd2| {np.abs(weights.wd2).max():.3g}")
-    res, ref = _run(cfg, weights, w, norm)
+    res, ref = _run(cfg, weights, w, norm, "fused")      # 8 metrics: the pass in fp32
     err = np.sqrt(np.mean((res[2] - ref["md_metric"])[:, 1:] ** 2))
     log(f"  rms error {err:.2e}")
     assert err <= 1e-7
 
 
 @pytest.mark.parametrize("norm", ["reference", "window"])
-@pytest.mark.parametrize("M,W,S,H,L,act", [(7, 60, 1, 64, 16, "tanh"), (16, 64, 1, 128, 16, "relu"), (3, 9, 1, 96, 3, "relu"),
-                                           (12, 11, 2, 30, 5, "tanh"), (5, 40, 3, 128, 16, "relu"), (1, 100, 1, 64, 2, "relu"),
-                                           (8, 32, 1, 33, 16, "relu")])
-def test_stretches_outside_the_range(norm, M, W, S, H, L, act):
+@pytest.mark.parametrize("M,W,S,H,L,act,more,route", [
+    (7, 60, 1, 64, 16, "tanh", 4000, "split"), (16, 64, 1, 128, 16, "relu", 0, "split"), (3, 9, 1, 96, 3, "relu", 0, "split"),
+    (12, 11, 2, 30, 5, "tanh", 0, "chunked"), (12, 11, 1, 30, 5, "tanh", 0, "split"), (5, 40, 3, 128, 16, "relu", 6000, "split"),
+    (1, 100, 1, 64, 2, "relu", 0, "chunked"), (1, 100, 1, 64, 2, "relu", 46000, "split"), (8, 32, 1, 33, 16, "relu", 0, "split")])
+def test_stretches_outside_the_range(norm, M, W, S, H, L, act, more, route):
     """Windows left to the fp32 kernel in all numbers, from one of a tile's 64 to whole tiles, beside others: a
     metric that was constant over the reference prefix and moves by thousands later (reference normalisation),
     stretches constant but for their last places (window normalisation)."""
     counts = [700, 300, 64, 1]
-    lengths = [W + (k - 1) * S + W * S for k in counts]
+    lengths, pairs = _with_long_stream([W + (k - 1) * S + W * S for k in counts], W, S, more)
     cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, latent=L, act=act, n_streams=len(lengths))
     log(f"[ext split] stretches {norm} M={M} W={W} S={S} H={H} L={L} {act}")
     rng = np.random.default_rng(M + H)
@@ -150,12 +170,15 @@ def test_stretches_outside_the_range(norm, M, W, S, H, L, act):
     weights = wl.make_weights(cfg, bias_scale=0.1)
     if norm == "reference":
         weights.w1 *= 1e-3                               # e^lv stays finite
-    res, ref = _run(cfg, weights, w, norm)
+    res, ref = _run(cfg, weights, w, norm, route, pairs)
     _check(res, ref, np.arange(len(ref["score"])))
     import torch
     det = detector(cfg, weights)
     xd, so = upload(w)
     wo = det.window_offsets(offs)
     only = det.score_ext(xd, so, torch.from_numpy(wo).cuda(), int(wo[-1]), norm=norm, scores_only=True)[0]
-    assert np.array_equal(only.cpu().numpy().astype(np.float64), res[0])
+    only = only.cpu().numpy().astype(np.float64)
+    if pairs is not None:
+        only = only[[wo[i] + k for i, k in pairs]]
+    assert np.array_equal(only, res[0])
     det.close()

@@ -86,12 +86,18 @@ def test_variants_match_oracle(norm, shape):
     ("c4", {}, False),                                           # bf16 detector
 ])
 def test_variant_evaluation_mode(name, over, fused):
-    """Which shapes take the fused single launch (the rest are evaluated in chunks); both kinds are
-    checked against the oracle above."""
+    """Which shapes are always evaluated in one pass, whatever the call: on f16 parts, or in fp32 where the
+    parts do not hold the weights as well. Of the others, calls of enough windows take the split pass where
+    it has the shape, and the rest are evaluated in chunks."""
     cfg = wl.CONFIGS[name].replace(**over)
     det = detector(cfg, wl.make_weights(cfg), "mfma")
     try:
         assert det.ext_fused() == fused
+        # tanh, 128 units, 16 metrics and 5 metrics pad to shapes of the split pass
+        padded = name == "c1" and not fused
+        assert det.ext_route(1, 1000000) == ("split" if fused or padded else "chunked")
+        if padded and cfg.metrics == 5:
+            assert det.ext_route(1000000, 2 ** 62) == "chunked"   # more tiles than a launch has
     finally:
         det.close()
 
