@@ -498,7 +498,7 @@ __device__ __forceinline__ void pot_eval_item(const double *__restrict__ y, cons
 #pragma unroll
         for (int k = 0; k < kPotX; ++k) {
             double ta, tb, r;
-            gpd_terms_fast(x[k] * yi, ta, tb, r);
+            gpd_terms(x[k] * yi, ta, tb, r);
             acc[0][k] += ta;
             acc[1][k] += tb;
             if constexpr (DER) {

@@ -597,7 +597,7 @@ __device__ void fit_eval(FitShared &sh, const double *y, int N, double nw = 0.0)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 double ta, tb;
-                gpd_terms_fast(x[k] * yi, ta, tb);
+                gpd_terms(x[k] * yi, ta, tb);
                 a[k] += ta;
                 b[k] += tb;
             }
@@ -809,7 +809,7 @@ __device__ void spot_fit_stream(FitShared &sh, int s, double q, const SpotState 
                     for (int i = lane; i < N; i += 64) {
                         const double yi = y[i];
                         double ta, tb, r;
-                        gpd_terms_fast(x * yi, ta, tb, r);
+                        gpd_terms(x * yi, ta, tb, r);
                         sa += ta;
                         sb += tb;
                         sdb += yi * r;
