@@ -128,9 +128,8 @@ __global__ __launch_bounds__(kCfgThreads) void k_cfg_scan(CfgParams c, int nb, c
 // window below that (a column constant over the window but not over the block, a perfect line)
 // takes the two passes, so that exact zeros stay exact. A column constant over the whole block
 // has all its sums exactly zero.
-// Measured (1024 services x 16384 steps, W = 64, S = 1): 676 -> 288 us for the scan kernel; blocks of
-// 448 windows give every thread two samples (512: 421 us, 256: 545 us, both with a shuffle scan of
-// all eight quantities in every thread; that one at 448: 388 us).
+// Measured (1024 services x 16384 steps, W = 64, S = 1): 676 -> 288 us for the scan kernel, with blocks of 448
+// windows (a shuffle scan of all eight quantities in every thread: 388 us, and with blocks of 512 421).
 constexpr int kCfgSumsN = 8;
 constexpr double kCfgKeep = 1e-4;
 
@@ -489,7 +488,12 @@ __global__ __launch_bounds__(kCfgThreads) void k_cfg_stream(CfgParams c, const v
 }  // namespace
 
 // The prefix form where windows share at least three quarters of their steps and a block of 64
-// windows or more fits its LDS (at W = 64, S = 1: 448 windows, 511 samples; four blocks a compute unit).
+// windows or more fits its LDS (four blocks a compute unit). A block takes as many windows as leave
+// every thread at most two samples and the 512 prefixes whole, 511 samples: rounds of 2^k windows, as it
+// was for all but W + 447 S < 512, left threads without one (1024 services x 8192 steps, in us: W = 128,
+// S = 1: 199 -> 171, W = 64, S = 2: 185 -> 138, S = 4: 175 -> 123, W = 270, S = 1: 347 -> 211). A few windows
+// over one a thread would cost a second round of them: 257 of W = 256 take 220 us against 205, 281 of 232 211
+// against 205, 297 of 216 200 against 203.
 constexpr size_t kCfgPrefixLds = 39 * 1024;
 
 static size_t prefix_lds_bytes(const CfgParams &c, int nb)
@@ -502,10 +506,11 @@ static int prefix_windows_per_block(const CfgParams &c)
 {
     if (4LL * c.S > c.W)
         return 0;
-    for (int nb = 448; nb >= 64; nb = nb > 256 ? 256 : nb >> 1)
-        if (prefix_lds_bytes(c, nb) <= kCfgPrefixLds)
-            return nb;
-    return 0;
+    constexpr int kSamples = 2 * kCfgThreads - 1, kFewOver = 36;
+    int nb = c.W <= kSamples ? (kSamples - c.W) / c.S + 1 : 0;
+    if (nb > kCfgThreads && nb < kCfgThreads + kFewOver)
+        nb = kCfgThreads;
+    return nb >= 64 ? nb : (prefix_lds_bytes(c, 64) <= kCfgPrefixLds ? 64 : 0);
 }
 
 int cfg_scan_windows_per_block(const CfgParams &c)

@@ -194,7 +194,10 @@ def test_recommend_longest_window():
 
 @pytest.mark.parametrize("W,S,lengths", [(64, 1, [511, 512, 575, 64, 63, 2000]), (16, 4, [1900, 16, 20]),
                                          (5, 1, [5, 6, 452, 900]), (200, 3, [1500, 200, 202, 700]),
-                                         (300, 1, [1400, 301]), (12, 4, [300, 12]), (3, 1, [700]), (40, 11, [900])])
+                                         (300, 1, [1400, 301]), (12, 4, [300, 12]), (3, 1, [700]), (40, 11, [900]),
+                                         # one window short of a block, a whole one and one more
+                                         (64, 2, [1100, 508, 510, 512]), (216, 1, [1300, 510, 511, 512]),
+                                         (225, 1, [1300, 479, 480, 481]), (449, 1, [1500, 511, 512, 513])])
 def test_scan_shapes_and_degenerate_stretches(W, S, lengths):
     """Both forms of the scan at the edges of their blocks, over series with what a difference of running
     sums must not blur: columns constant over a window but not over its block, a perfect line, a drift of
