@@ -145,15 +145,18 @@ enova_status enova_detect_score(enova_detector det, const void *x, const int64_t
 /*
  * enova_detect_score without any allocation, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, hosts that forbid hipMalloc). Arguments,
- * results and errors are those of enova_detect_score, with the same kernels; it calls no
- * hipMalloc, hipFree or allocating routine, and records no timing events (kernel timing reports
- * nothing for it). Its workspace -- the reference statistics when ref_mean/ref_std are NULL
- * (2 * n_streams * M floats), and for the matrix-core kernel the tile offsets
- * ((n_streams + 1) int64) and block-to-stream map ((n_windows + Nb - 1) / Nb + n_streams ints,
- * Nb = windows per tile: 128-512 by shape), each rounded up to 256 bytes -- lives in a fixed
+ * results and errors are those of enova_detect_score, with the same kernels (see below for the one
+ * exception); it calls no hipMalloc, hipFree or allocating routine, and records no timing events
+ * (kernel timing reports nothing for it). Its workspace -- the reference statistics when
+ * ref_mean/ref_std are NULL (2 * n_streams * M floats), and for the matrix-core kernels the tile
+ * offsets ((n_streams + 1) int64) and block-to-stream map ((n_windows + Nb - 1) / Nb + n_streams ints,
+ * Nb = windows per tile: 64-512 by shape and size of the call; for fp32 detectors on the split
+ * kernel as many ints and one more for its marks, at most n_windows + 1), each rounded up to 256 bytes;
+ * chunk sums of the statistics where there is room -- lives in a fixed
  * 16 MiB device array that the library holds on every GPU it runs on until the process ends,
- * shared by all detectors on that GPU. A call that needs more returns ENOVA_ESHAPE before any
- * launch. Every part of that workspace is fully rewritten by each call before it is read, so no
+ * shared by all detectors on that GPU. Where the split kernel's map and marks do not fit it but the fp32
+ * kernel's map does, that kernel scores the call, and the results differ from enova_detect_score's in
+ * rounding. A call that needs more returns ENOVA_ESHAPE before any launch. Every part of that workspace is fully rewritten by each call before it is read, so no
  * clearing is needed between calls; calls that overlap on one GPU (on different streams, or from
  * several threads) race on the array and must be serialised by the caller.
  */

@@ -18,11 +18,12 @@
 // Measured on one MI355X, every output, before (k_ext_fused or the chunked pass) and now: 64 ragged
 // streams of 16 metrics, W = 64, H = 128, per-window normalisation (2.1e6 windows) 9.39 -> 4.60 ms;
 // 32 streams of 7 metrics, W = 60, H = 64, tanh, reference normalisation (3.6e5 windows) 1985 ->
-// 300 us (most of it the chunked pass's trips through memory). The errors against 64 bits are
+// 247 us (most of it the chunked pass's trips through memory). The errors against 64 bits are
 // smaller: scores 4.2e-7 -> 3.0e-7, md 6.1e-6 -> 4.4e-6, reconstruction error 2.3e-7 -> 5.1e-8
 // on the first.
 //
-// Windows out of the parts' range (split.h) are marked and evaluated in fp32 by k_ext_list.
+// Windows out of the parts' range (split.h) are marked and evaluated in fp32 by k_ext_list; detectors whose
+// output weights stand too far apart for one scale take the fp32 passes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -12,18 +12,19 @@
 // than that (D/2 roundings of the partial sum against 3 D / 16 here). Measured against 64 bits,
 // the scores' relative error (2-norm) went from 4.3e-7 to 3.2e-7 at D = 512 and from 5.2e-7 to
 // 3.6e-7 at D = 1024. One MI355X, whole scoring calls before and after: 64 services of 16384 steps x
-// 8 metrics, W = 64, H = 64: 602 -> 245 us; 512 ragged streams x 16 metrics, W = 64, H = 128 (1.6e7
+// 8 metrics, W = 64, H = 64: 602 -> 240 us; 512 ragged streams x 16 metrics, W = 64, H = 128 (1.6e7
 // windows): 31.3 -> 10.7 ms (410 fp32-equivalent TFLOP/s); 96 streams x 7 metrics, W = 60, H = 64,
-// tanh: 1006 -> 362 us.
+// tanh: 1006 -> 349 us.
 //
 // Range. f16 ends at 65504 and its numbers are 2^-24 apart below 2^-14, so V is scaled by 2^4
 // and each row of W1 by a power of two that puts its largest weight into [2^13, 2^14); both come
-// off exactly with the bias (one fused multiply-add). A window whose largest |v| exceeds
-// kSplitMax (or is not finite), or is not zero but below kSplitMin, does not fit that range: it
-// is left to k_score_mfma's list mode, which goes through the marked tiles in fp32. Waves without a
-// window of their own kind skip the products on both sides. The choice depends on the window's own steps alone (a super-row's maximum is
-// kept for all its steps and for those that a window ends with), so scores stay independent of what
-// else a stream or a batch holds.
+// off exactly with the bias (one fused multiply-add). Detectors whose inputs' weights stand so far
+// apart that the parts' fixed 2^-29 of a small input would show take the fp32 kernel (decided at
+// set-up). So do the windows whose largest |v| exceeds kSplitMax (or is not finite), or is not zero but
+// below kSplitMin: they are left to k_score_mfma's list mode, which goes through the marked tiles. Waves
+// without a window of their own kind skip the products on both sides. The choice depends on the
+// window's own steps alone (a super-row's maximum is kept for all its steps and for those that a
+// window ends with), so scores stay independent of what else a stream or a batch holds.
 //
 // The posterior heads and the decoder's hidden layer chain from the accumulators as in the other
 // kernels, on 32x32x16 bf16 ops: activations, mu and weights as three bf16 parts each (24 bits,
