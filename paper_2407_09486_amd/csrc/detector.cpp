@@ -1399,6 +1399,24 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
         if ((e = launch_prep_map(g, x, soff, tiles, n, grid, tmap, marks, own_mean, own_std, part, stream)) != hipSuccess)
             return hip_fail(e, "tile map kernel");
         const int decode = (out_md || out_md_metric || out_recon) ? 1 : 0;
+        ExtFusedParams fp{};
+        fp.x = static_cast<const float *>(x);
+        fp.soff = soff;
+        fp.woff = woff;
+        fp.tile_off = tiles;
+        fp.tile_stream = tmap;
+        fp.mean = ref_mean;
+        fp.std = ref_std;
+        fp.w1p = det->w1p;
+        fp.cst = det->whp;
+        fp.wd2p = det->wd2p;
+        fp.bd2 = det->d_bd2;
+        fp.scores = out_scores;
+        fp.md = out_md;
+        fp.mdm = out_md_metric;
+        fp.rec = out_recon;
+        fp.norm = norm;
+        fp.decode = decode;
         if (split) {
             ExtSplitParams sp{};
             sp.x = static_cast<const float *>(x);
@@ -1431,31 +1449,22 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
             sp.rec = out_recon;
             sp.norm = norm;
             sp.decode = decode;
-            if ((e = launch_ext_split(g, det->sg, sp, det->wd2_unscale, grid, stream)) != hipSuccess)
+            e = launch_ext_split(g, det->sg, sp, det->wd2_unscale, grid, stream);
+            if (e == hipSuccess && ext_fused_list_supported(g)) {
+                fp.marks = marks;
+                fp.masks = masks;
+                fp.wd2 = det->d_wd2;
+                e = launch_ext_fused_list(g, fp, grid, stream);
+            } else if (e == hipSuccess) {
+                e = launch_ext_list(g, det->sg, sp, grid, stream);
+            }
+            if (e != hipSuccess)
                 return hip_fail(e, "split variant kernels");
             if (det->timing)
                 (void)hipEventRecord(det->ext_ev[1], stream);
             det->ran_ext = true;
             return ENOVA_OK;
         }
-        ExtFusedParams fp{};
-        fp.x = static_cast<const float *>(x);
-        fp.soff = soff;
-        fp.woff = woff;
-        fp.tile_off = tiles;
-        fp.tile_stream = tmap;
-        fp.mean = ref_mean;
-        fp.std = ref_std;
-        fp.w1p = det->w1p;
-        fp.cst = det->whp;
-        fp.wd2p = det->wd2p;
-        fp.bd2 = det->d_bd2;
-        fp.scores = out_scores;
-        fp.md = out_md;
-        fp.mdm = out_md_metric;
-        fp.rec = out_recon;
-        fp.norm = norm;
-        fp.decode = decode;
         if ((e = launch_ext_fused(g, fp, grid, stream)) != hipSuccess)
             return hip_fail(e, "fused variant kernel");
         if (det->timing)

@@ -41,6 +41,16 @@ __device__ __forceinline__ float4 fma4(float4 x, float4 a, float4 b)
     return make_float4(fmaf(x.x, a.x, b.x), fmaf(x.y, a.y, b.y), fmaf(x.z, a.z, b.z), fmaf(x.w, a.w, b.w));
 }
 
+// A fragment normalised: x a + b, or (k: a mean in place of b) (x - k) a.
+template <bool K>
+__device__ __forceinline__ float4 norm4(float4 x, float4 a, float4 b)
+{
+    if constexpr (K)
+        return make_float4((x.x - b.x) * a.x, (x.y - b.y) * a.y, (x.z - b.z) * a.z, (x.w - b.w) * a.w);
+    else
+        return fma4(x, a, b);
+}
+
 __device__ __forceinline__ float comp(float4 v, int e)
 {
     return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
@@ -48,8 +58,10 @@ __device__ __forceinline__ float comp(float4 v, int e)
 
 // HB: 32-row hidden blocks (hidden units padded to 32 HB); MC: 16-byte metric chunks per step
 // (M = 4 MC). Every wave owns all hidden rows and two 32-window blocks.
-template <int HB, int MC, int ACT>
-__global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParams p, ExtFusedShape g)
+// LIST: a tile that k_ext_split marked, of which the windows of its masks are evaluated and written. It holds
+// no step behind a window under zero weights (ext_fused_list_supported), whose NaN would be the window's.
+template <int HB, int MC, int ACT, bool LIST>
+__device__ __forceinline__ void ext_fused_tile(const ExtFusedParams &p, const ExtFusedShape &g, int64_t b)
 {
     constexpr int NT = kFusedWaves * 64;
     constexpr int NBW = kFusedNbw;
@@ -67,8 +79,12 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
     const int wave = tid >> 6;
     const int half = lane >> 5;
 
+    const uint4 *w1p = p.w1p;
+    const float4 *wd2 = reinterpret_cast<const float4 *>(LIST ? p.wd2 : reinterpret_cast<const float *>(p.wd2p));
+    if constexpr (LIST)   // or loads of weights move out of the list's loop, into spilled registers
+        asm volatile("" : "+s"(w1p), "+s"(wd2));
+
     // ---- tile -> (stream, first window)
-    const int64_t b = blockIdx.x;
     const int s = p.tile_stream[b];
     if (s < 0)
         return;
@@ -129,7 +145,8 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
     __syncthreads();
 
     const int wn0 = wave * NBW * 32;
-    const bool wave_active = wn0 < nv;
+    const uint64_t mask = LIST ? p.masks[b * kFusedWaves + wave] : ~uint64_t{0};   // the wave's windows to write
+    const bool wave_active = wn0 < nv && mask != 0;
     if (!wave_active)
         return;   // no barrier follows
     int rb[NBW];
@@ -178,7 +195,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                     if (sd <= 1e-6 * fmax(1.0, fabs(mean)))
                         sd = 1.0;   // constant metric inside the window
                     av[e] = static_cast<float>(1.0 / sd);
-                    bv[e] = static_cast<float>(-mean / sd);
+                    bv[e] = static_cast<float>(LIST ? mean : -mean / sd);
                 }
                 ca[nb][j] = make_float4(av[0], av[1], av[2], av[3]);
                 cb[nb][j] = make_float4(bv[0], bv[1], bv[2], bv[3]);
@@ -192,7 +209,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
             for (int e = 0; e < 4; ++e) {
                 const double sd = static_cast<double>(p.std[e0 + e]);
                 av[e] = static_cast<float>(1.0 / sd);
-                bv[e] = static_cast<float>(-static_cast<double>(p.mean[e0 + e]) / sd);
+                bv[e] = LIST ? p.mean[e0 + e] : static_cast<float>(-static_cast<double>(p.mean[e0 + e]) / sd);
             }
 #pragma unroll
             for (int nb = 0; nb < NBW; ++nb) {
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                 acc[hb][nb][r] = 0.0f;
     {
         const int nsteps = g.KC / 2;   // a multiple of PD
-        const uint4 *ap = p.w1p + lane;
+        const uint4 *ap = w1p + lane;
         const int dpitch = CPRP - CPR;
         int cc = half % CPR;
         int koff = (half / CPR) * CPRP + cc;
@@ -249,7 +266,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                 float4 vb[NBW];
 #pragma unroll
                 for (int nb = 0; nb < NBW; ++nb)
-                    vb[nb] = fma4(reinterpret_cast<const float4 &>(bq[j % RB][nb]), ca[nb][cj], cb[nb][cj]);
+                    vb[nb] = norm4<LIST>(reinterpret_cast<const float4 &>(bq[j % RB][nb]), ca[nb][cj], cb[nb][cj]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -321,11 +338,13 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
         // same fragment of block ob + 1 (of block 0 after the last block, for the next window block)
         const int nob = g.D / 32;
         constexpr int PF = HB * 4;
-        const float4 *wa = p.wd2p + lane;
+        // (list: from the dense rows, of HP units: fragment f of row l % 32 is the units 8 f + 4 (l / 32) on)
+        constexpr int FS = LIST ? 2 : 64, OS = LIST ? 8 * HP : PF * 64;   // strides of fragments and blocks
+        const float4 *wa = wd2 + (LIST ? (lane & 31) * (HP / 4) + half : lane);
         float4 ar[PF];
 #pragma unroll
         for (int f = 0; f < PF; ++f)
-            ar[f] = wa[f * 64];
+            ar[f] = wa[f * FS];
 #pragma unroll
         for (int i = 0; i < NBW; ++i) {
             v16f hd[HB];
@@ -343,7 +362,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                     hd[hb][r] = act_fn<ACT>(hd[hb][r] + s_bd1[hb * 32 + crow(r, half)]);
             }
             for (int ob = 0; ob < nob; ++ob) {
-                const float4 *wnext = wa + (ob + 1 == nob ? 0 : (ob + 1) * PF * 64);
+                const float4 *wnext = wa + (ob + 1 == nob ? 0 : (ob + 1) * OS);
                 v16f o;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
@@ -356,7 +375,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                         o = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(ar[f], e), hd[f / 4][4 * (f % 4) + e], o, 0, 0,
                                                                  0);
                     __builtin_amdgcn_sched_barrier(0);
-                    ar[f] = wnext[f * 64];
+                    ar[f] = wnext[f * FS];
                 }
                 // registers 4 gq .. 4 gq + 3 hold the chunk (8 ob + 2 gq + half) of the window,
                 // i.e. step t = chunk / MC, metric chunk = chunk mod MC (constant set gq mod 2
@@ -368,7 +387,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
                     const int off = S == 1 ? t * CPRP + mchunk(cj) : (t / S) * CPRP + (t % S) * MC + mchunk(cj);
                     const float4 bd = reinterpret_cast<const float4 *>(s_bd2)[ob * 8 + 2 * gq + half];
                     const float4 x4 = reinterpret_cast<const float4 &>(seg[rb[i] + off]);
-                    const float4 v4 = fma4(x4, ca[i][cj], cb[i][cj]);
+                    const float4 v4 = norm4<LIST>(x4, ca[i][cj], cb[i][cj]);
                     const float d0 = (v4.x - bd.x) - o[4 * gq + 0];
                     const float d1 = (v4.y - bd.y) - o[4 * gq + 1];
                     const float d2 = (v4.z - bd.z) - o[4 * gq + 2];
@@ -405,7 +424,7 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
             tot += __shfl_xor(tot, 32);
         }
         const float sqt = sq[i] + __shfl_xor(sq[i], 32);
-        if (n >= nv)
+        if (n >= nv || !((mask >> (n - wn0)) & 1u))
             continue;
         const int64_t w = p.woff[s] + k0 + n;
         if (half == 0) {
@@ -429,37 +448,94 @@ __global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParam
     }
 }
 
+template <int HB, int MC, int ACT>
+__global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused(ExtFusedParams p, ExtFusedShape g)
+{
+    ext_fused_tile<HB, MC, ACT, false>(p, g, blockIdx.x);
+}
+
+// The tiles that k_ext_split marked, dealt out over the blocks. Data that leaves the 16-bit range for long
+// leaves it in whole tiles, which take as long here as on k_ext_fused; k_ext_list, with its 64 windows a block,
+// took up to twice that. In us, k_ext_fused over all windows, and the split pass with k_ext_list and
+// with this: 64 streams x 4096 steps x 8 metrics, W = 64, H = 64, half of the windows out 341, 513, 376, all 329, 645,
+// 334; 16 x 16384 x 16, H = 128, half 1190, 1183, 1058, all 1149, 1674, 1124, a NaN every 1024 steps 1169, 998, 1132.
+template <int HB, int MC, int ACT>
+__global__ __launch_bounds__(kFusedWaves * 64, 2) void k_ext_fused_list(ExtFusedParams p, ExtFusedShape g)
+{
+    const int64_t count = p.marks[0];
+    for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
+        ext_fused_tile<HB, MC, ACT, true>(p, g, p.marks[1 + i]);
+        __syncthreads();   // the tile's LDS is written again
+    }
+}
+
 using FusedKernel = void (*)(ExtFusedParams, ExtFusedShape);
 
+template <int HB, int MC, int ACT>
+FusedKernel pick_list(bool list)
+{
+    return list ? k_ext_fused_list<HB, MC, ACT> : k_ext_fused<HB, MC, ACT>;
+}
+
 template <int ACT>
-FusedKernel pick_mc(int hb, int mc)
+FusedKernel pick_mc(int hb, int mc, bool list)
 {
     switch (hb * 8 + mc) {
-    case 1 * 8 + 1: return k_ext_fused<1, 1, ACT>;
-    case 1 * 8 + 2: return k_ext_fused<1, 2, ACT>;
-    case 1 * 8 + 4: return k_ext_fused<1, 4, ACT>;
-    case 2 * 8 + 1: return k_ext_fused<2, 1, ACT>;
-    case 2 * 8 + 2: return k_ext_fused<2, 2, ACT>;
-    case 2 * 8 + 4: return k_ext_fused<2, 4, ACT>;
+    case 1 * 8 + 1: return pick_list<1, 1, ACT>(list);
+    case 1 * 8 + 2: return pick_list<1, 2, ACT>(list);
+    case 1 * 8 + 4: return pick_list<1, 4, ACT>(list);
+    case 2 * 8 + 1: return pick_list<2, 1, ACT>(list);
+    case 2 * 8 + 2: return pick_list<2, 2, ACT>(list);
+    case 2 * 8 + 4: return pick_list<2, 4, ACT>(list);
     default: break;
     }
     switch (hb * 8 + mc) {
-    case 4 * 8 + 1: return k_ext_fused<4, 1, ACT>;
-    case 4 * 8 + 2: return k_ext_fused<4, 2, ACT>;
+    case 4 * 8 + 1: return pick_list<4, 1, ACT>(list);
+    case 4 * 8 + 2: return pick_list<4, 2, ACT>(list);
     default: break;
     }
     if constexpr (ACT == ENOVA_RELU) {   // with tanh, 128 hidden units and 16 metrics exceed the registers
         if (hb == 4 && mc == 4)
-            return k_ext_fused<4, 4, ACT>;
+            return pick_list<4, 4, ACT>(list);
     }
     return nullptr;
 }
 
-FusedKernel pick_fused(const Geometry &g)
+FusedKernel pick_fused(const Geometry &g, bool list)
 {
     if (!ext_fused_supported(g))
         return nullptr;
-    return g.act == ENOVA_RELU ? pick_mc<ENOVA_RELU>(g.HB, g.M / 4) : pick_mc<ENOVA_TANH>(g.HB, g.M / 4);
+    return g.act == ENOVA_RELU ? pick_mc<ENOVA_RELU>(g.HB, g.M / 4, list) : pick_mc<ENOVA_TANH>(g.HB, g.M / 4, list);
+}
+
+hipError_t prepare(FusedKernel k)
+{
+    if (!k)
+        return hipErrorInvalidValue;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(kLdsLimit));
+}
+
+hipError_t launch(FusedKernel k, const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st)
+{
+    if (grid <= 0)
+        return hipSuccess;
+    if (!k)
+        return hipErrorInvalidValue;
+    ExtFusedShape sh;
+    sh.S = g.S;
+    sh.W = g.W;
+    sh.Q = g.Q;
+    sh.CPR = g.CPR;
+    sh.CPRP = g.CPRP;
+    sh.KC = g.KC;
+    sh.spare = g.spare;
+    sh.D = g.D;
+    sh.inv_w = 1.0f / static_cast<float>(g.W);
+    sh.inv_d = 1.0f / static_cast<float>(g.D);
+    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(kFusedWaves * 64), ext_fused_lds_bytes(g), st, p,
+                       sh);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -478,36 +554,22 @@ bool ext_fused_supported(const Geometry &g)
            g.KC % 4 == 0 && ext_fused_lds_bytes(g) <= kLdsLimit / 2;
 }
 
-hipError_t prepare_ext_fused(const Geometry &g)
-{
-    FusedKernel k = pick_fused(g);
-    if (!k)
-        return hipErrorInvalidValue;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               static_cast<int>(kLdsLimit));
-}
+// Strides that divide the window leave no weights of zero in its last super-row, and hidden layers of whole
+// blocks let the list read Wd2's dense rows.
+bool ext_fused_list_supported(const Geometry &g) { return ext_fused_supported(g) && g.W % g.S == 0 && g.H == g.Hp; }
+
+hipError_t prepare_ext_fused(const Geometry &g) { return prepare(pick_fused(g, false)); }
+
+hipError_t prepare_ext_fused_list(const Geometry &g) { return prepare(pick_fused(g, true)); }
 
 hipError_t launch_ext_fused(const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st)
 {
-    if (grid <= 0)
-        return hipSuccess;
-    FusedKernel k = pick_fused(g);
-    if (!k)
-        return hipErrorInvalidValue;
-    ExtFusedShape sh;
-    sh.S = g.S;
-    sh.W = g.W;
-    sh.Q = g.Q;
-    sh.CPR = g.CPR;
-    sh.CPRP = g.CPRP;
-    sh.KC = g.KC;
-    sh.spare = g.spare;
-    sh.D = g.D;
-    sh.inv_w = 1.0f / static_cast<float>(g.W);
-    sh.inv_d = 1.0f / static_cast<float>(g.D);
-    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(kFusedWaves * 64), ext_fused_lds_bytes(g), st, p,
-                       sh);
-    return hipGetLastError();
+    return launch(pick_fused(g, false), g, p, grid, st);
+}
+
+hipError_t launch_ext_fused_list(const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st)
+{
+    return launch(pick_fused(g, true), g, p, grid < 512 ? grid : 512, st);   // two blocks a compute unit
 }
 
 }  // namespace enova

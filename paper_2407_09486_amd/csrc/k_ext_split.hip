@@ -22,8 +22,9 @@
 // smaller: scores 4.2e-7 -> 3.0e-7, md 6.1e-6 -> 4.4e-6, reconstruction error 2.3e-7 -> 5.1e-8
 // on the first.
 //
-// Windows out of the parts' range (split.h) are marked and evaluated in fp32 by k_ext_list; detectors whose
-// output weights stand too far apart for one scale take the fp32 passes.
+// Windows out of the parts' range (split.h) are marked and evaluated in fp32, by k_ext_fused_list or, of shapes
+// that it does not take, by k_ext_list; detectors whose output weights stand too far apart for one scale take
+// the fp32 passes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(256, 2) void k_ext_split(ExtSplitParams p, ExtSplit
     }
     __syncthreads();
 
-    // windows outside the range (a wave holds 64): left to k_ext_list; waves without any other are done
+    // windows outside the range (a wave holds 64) are left to the list; waves without any other are done
     static_assert(kNb == NT && kNbw == 2, "a thread per window, a mask's word per wave");
     const bool out = tid < nv && split_outside(wmx[tid]);
     const uint64_t outside = __ballot(out);
@@ -622,7 +623,7 @@ __device__ __forceinline__ void load_row(const float *w, int k, int K, float (&a
     }
 }
 
-// The windows that k_ext_split left, in fp32: up to 64 of a marked tile (a mask's word) at a time, the
+// The windows that k_ext_split left, in fp32 (of shapes that k_ext_fused_list does not take): up to 64 of a marked tile (a mask's word) at a time, the
 // parts dealt out evenly over the blocks. The windows are the columns of fp32 matrix ops whose other
 // operand is a dense weight matrix read in place; in a run of 2 N reduction indices op t takes index t of
 // the lower lanes' and index N + t of the upper lanes' half, so that a lane reads whole cache lines. The
@@ -631,9 +632,9 @@ __device__ __forceinline__ void load_row(const float *w, int k, int K, float (&a
 // in order). The output's blocks go to the waves in turn, and a lane adds its rows' v - m' per metric in
 // a place of its own in LDS.
 // This is for data that leaves the range for long (a metric constant over the reference prefix that
-// moves later, gaps held as NaN). One window per block and serial dot products, as it was first, took 94.9 ms
-// for 16 streams x 16384 steps x 16 metrics, W = 64, H = 128, half of the windows out; now 1.46 (0.67 in range; all
-// windows on the fp32 pass 1.19). 7 metrics, W = 60, H = 64, tanh: 26.6 -> 0.58 ms (chunked evaluation 2.6).
+// moves later, gaps held as NaN). One window per block and serial dot products, as it was first, took 26.6 ms
+// for 32 streams x 8192 steps x 7 metrics, W = 60, H = 64, tanh, half of the windows out; now 0.55 (0.18 in range;
+// chunked evaluation 1.97).
 constexpr int kExtListWin = 64, kExtListPitch = 65;   // windows, and floats of a row of them in LDS
 constexpr int kExtListRun = 64;                       // reduction indices of a run
 constexpr int kExtListPart = 2 * kExtListRun * kExtListPitch;   // two runs; partial sums later
@@ -1001,18 +1002,14 @@ hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg)
                                              static_cast<int>(lds_bytes(g, sg)));
     if (e != hipSuccess)
         return e;
+    if (ext_fused_list_supported(g))
+        return prepare_ext_fused_list(g);
     return hipFuncSetAttribute(reinterpret_cast<const void *>(pick_list(g.HB)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(kLdsLimit / 2));
 }
 
-hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,
-                            int64_t grid, hipStream_t st)
+static ExtSplitShape shape_of(const Geometry &g, const SplitGeometry &sg)
 {
-    if (grid <= 0)
-        return hipSuccess;
-    SplitKernel k = pick(g, sg);
-    if (!k)
-        return hipErrorInvalidValue;
     ExtSplitShape sh{};
     sh.M = g.M;
     sh.S = g.S;
@@ -1027,15 +1024,32 @@ hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const Ex
     sh.nsteps = sg.nsteps;
     sh.spare = sg.spare;
     sh.Dp = padded_d(g, sg);
-    sh.wd2_unscale = wd2_unscale;
     sh.inv_w = 1.0f / static_cast<float>(g.W);
     sh.inv_d = 1.0f / static_cast<float>(g.D);
+    return sh;
+}
+
+hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,
+                            int64_t grid, hipStream_t st)
+{
+    if (grid <= 0)
+        return hipSuccess;
+    SplitKernel k = pick(g, sg);
+    if (!k)
+        return hipErrorInvalidValue;
+    ExtSplitShape sh = shape_of(g, sg);
+    sh.wd2_unscale = wd2_unscale;
     hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(grid)), dim3(256), lds_bytes(g, sg), st, p, sh);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_ext_list(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, int64_t grid,
+                           hipStream_t st)
+{
+    if (grid <= 0)
+        return hipSuccess;
     hipLaunchKernelGGL(pick_list(g.HB), dim3(static_cast<unsigned>(std::min<int64_t>(4 * grid, 512))), dim3(256),
-                       list_lds_bytes(g), st, p, sh);
+                       list_lds_bytes(g), st, p, shape_of(g, sg));
     return hipGetLastError();
 }
 

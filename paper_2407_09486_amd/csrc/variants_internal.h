@@ -41,6 +41,10 @@ struct ExtFusedParams {
     const float *cst;            // the scoring kernel's block: heads, decoder hidden layer, b1, bd1, u, bh
     const float4 *wd2p;          // [D/32][HB][4][64 lanes]: Wd2[32 ob + l%32][32 hb + crow(4 r4 + e, l/32)], e = 0..3
     const float *bd2;            // [D]
+    // list: the split pass's marks and masks, and Wd2 as it is, [D][H]
+    const unsigned *marks;
+    const uint64_t *masks;
+    const float *wd2;
     float *scores, *md, *mdm, *rec;   // any may be NULL
     int norm;                    // ENOVA_NORM_REFERENCE or ENOVA_NORM_WINDOW
     int decode;                  // 0: scores only (the decoder is skipped)
@@ -53,11 +57,16 @@ bool ext_fused_supported(const Geometry &g);
 size_t ext_fused_lds_bytes(const Geometry &g);
 hipError_t prepare_ext_fused(const Geometry &g);
 hipError_t launch_ext_fused(const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st);
+// The same over the windows that k_ext_split left, of up to `grid` tiles.
+bool ext_fused_list_supported(const Geometry &g);
+hipError_t prepare_ext_fused_list(const Geometry &g);
+hipError_t launch_ext_fused_list(const Geometry &g, const ExtFusedParams &p, int64_t grid, hipStream_t st);
 
 // ---------------------------------------------------------------------------------------------
 // The same on the 16-bit matrix cores (k_ext_split.hip): fp32 detectors that the split scoring kernel
 // takes, with steps padded to 8 or 16 metrics, at most 128 hidden units and a tile within half a
-// compute unit's LDS; windows out of the split's range in fp32, from the dense weights.
+// compute unit's LDS; windows out of the split's range are left to launch_ext_fused_list where that has the
+// shape, else to launch_ext_list (fp32, from the dense weights).
 // ---------------------------------------------------------------------------------------------
 struct ExtSplitParams {
     const float *x;
@@ -87,5 +96,7 @@ hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg);
 // wd2_unscale: the inverse of the power of two that wd2x is scaled by
 hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,
                             int64_t grid, hipStream_t st);
+hipError_t launch_ext_list(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, int64_t grid,
+                           hipStream_t st);
 
 }  // namespace enova

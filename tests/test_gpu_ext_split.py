@@ -142,7 +142,10 @@ def test_decoder_output_scales(norm, where):
 @pytest.mark.parametrize("M,W,S,H,L,act,more,route", [
     (7, 60, 1, 64, 16, "tanh", 4000, "split"), (16, 64, 1, 128, 16, "relu", 0, "split"), (3, 9, 1, 96, 3, "relu", 0, "split"),
     (12, 11, 2, 30, 5, "tanh", 0, "chunked"), (12, 11, 1, 30, 5, "tanh", 0, "split"), (5, 40, 3, 128, 16, "relu", 6000, "split"),
-    (1, 100, 1, 64, 2, "relu", 0, "chunked"), (1, 100, 1, 64, 2, "relu", 46000, "split"), (8, 32, 1, 33, 16, "relu", 0, "split")])
+    (1, 100, 1, 64, 2, "relu", 0, "chunked"), (1, 100, 1, 64, 2, "relu", 46000, "split"), (8, 32, 1, 33, 16, "relu", 0, "split"),
+    # windows left to the fp32 pass of whole tiles (strides that divide the window, whole hidden blocks), or just not
+    (4, 16, 1, 64, 3, "tanh", 0, "split"), (8, 12, 3, 32, 16, "relu", 0, "split"), (8, 12, 5, 64, 16, "relu", 0, "split"),
+    (8, 16, 4, 128, 7, "tanh", 0, "split"), (16, 8, 2, 64, 16, "tanh", 0, "split"), (16, 6, 1, 32, 16, "relu", 0, "split")])
 def test_stretches_outside_the_range(norm, M, W, S, H, L, act, more, route):
     """Windows left to the fp32 kernel in all numbers, from one of a tile's 64 to whole tiles, beside others: a
     metric that was constant over the reference prefix and moves by thousands later (reference normalisation),
