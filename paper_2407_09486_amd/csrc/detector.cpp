@@ -1117,6 +1117,13 @@ size_t noalloc_bytes(const Geometry &g, int kind, int32_t n, int64_t grid, int64
     return o;
 }
 
+// Windows of fewer values than this are scored by the fp32 kernel. Of independent normal values a share of
+// 0.2^D windows has them all below kSplitMin (split.h), which the split kernel leaves to its list: one in
+// five of a single value, and every wave has some up to three. 200 streams x 8000 steps, H = 32, 64, 128,
+// 200, split and fp32 in us: D = 1 274, 435, 882, 1702 and 159, 271, 476, 923; D = 3 212, 327, 639, 1029 and 162,
+// 276, 480, 926; D = 4 158, 238, 401, 650 and 163, 279, 482, 925.
+constexpr int kSplitLeastD = 4;
+
 // Both scoring entry points. noalloc: the workspace is carved from the device's fixed scratch
 // (no allocation, no timing events); otherwise it is the detector's grow-only workspace.
 enova_status score_common(enova_detector det, const void *x, const int64_t *soff, const int64_t *woff, int32_t n,
@@ -1138,7 +1145,7 @@ enova_status score_common(enova_detector det, const void *x, const int64_t *soff
     const Geometry &g = det->g;
     // windows per tile: the split kernel's where it applies, unless its smaller tiles need more
     // blocks or workspace than a call may have
-    bool split = det->kind == 2 && det->sg.ok;
+    bool split = det->kind == 2 && det->sg.ok && g.D >= kSplitLeastD;
     int nb = split ? det->sg.nb(n_windows, n) : g.Nb;
     int64_t grid = det->kind == 2 ? (n_windows + nb - 1) / nb + n : 0;
     size_t o_tiles = 0, o_map = 0, o_part = 0;

@@ -199,6 +199,18 @@ def test_steps_beside_a_window_do_not_count(M, W, S, H):
     valu.close()
 
 
+@pytest.mark.parametrize("M,W,H", [(1, 1, 64), (3, 1, 200), (1, 3, 32), (2, 2, 128), (1, 5, 64)])
+def test_windows_of_few_values(M, W, H):
+    """Below four values a window the fp32 kernel scores; from four on the split kernel leaves the quiet windows to
+    its list."""
+    cfg = _cfg(M, W, 1, H, n=2)
+    rng = np.random.default_rng(M + W)
+    offs = np.array([0, 3000, 4100], np.int64)
+    log(f"[split] few values M={M} W={W} H={H}")
+    w = wl.from_arrays(cfg, rng.standard_normal((4100, M)), offs)
+    _check(cfg, w, wl.make_weights(cfg, bias_scale=0.1), f"M={M} W={W} H={H}")
+
+
 @pytest.mark.parametrize("H", [32, 64, 128, 256])
 def test_marked_parts_of_large_tiles(H):
     """Large tiles whose windows leave the range at the edges of their parts and waves, for one window, for a
