@@ -665,7 +665,8 @@ def variants_main(args, cfg):
 
     def step():
         binding.enova_detect_score_ext(det.handle, x, so, wo, work.n_streams, N, None, None, norm, sc, md, mdm, rec)
-    kernel = {"split": "k_ext_split", "fused": "k_ext_fused", "chunked": "chunked"}[det.ext_route(work.n_streams, N)]
+    route = det.ext_route(work.n_streams, N, args.norm)
+    kernel = {"split": "k_ext_split", "fused": "k_ext_fused", "chunked": "chunked"}[route]
     for _ in range(args.warmup):
         step()
     binding.enova_detect_set_timing(det.handle, True)

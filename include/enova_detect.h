@@ -373,7 +373,7 @@ enova_status enova_detect_ext_time(enova_detector det, double *ms);
  * a tile that fits half a compute unit's LDS; else 0. Errors: EINVAL. */
 enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused);
 
-/* How an enova_detect_score_ext call of n_streams and n_windows evaluates its windows:
+/* How an enova_detect_score_ext call of n_streams and n_windows, normalised as norm says, evaluates them:
  *   ENOVA_EXT_SPLIT    one pass that stages each tile's raw steps once and keeps every window's v, hidden
  *                      layers and decoder output on chip, products from f16 parts: fp32 detectors of at
  *                      most 16 metrics, 128 hidden and 16 latent units whose steps pad to 8 or 16 metrics
@@ -383,7 +383,8 @@ enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused);
  *   ENOVA_EXT_CHUNKED  normalised windows in device memory, chunk by chunk, in fp32: all others
  * The evaluations differ in rounding only. Errors: EINVAL. */
 enum { ENOVA_EXT_CHUNKED = 0, ENOVA_EXT_FUSED = 1, ENOVA_EXT_SPLIT = 2 };
-enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t *route);
+enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t norm,
+                                    int32_t *route);
 
 /*
  * Configuration scans (Section IV-A, Eqs. (4)-(6), Table II) over the same monitoring series.

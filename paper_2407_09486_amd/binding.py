@@ -119,7 +119,7 @@ def lib():
     L.enova_detect_score_ext.argtypes = [P, P, P, P, I32, I64, P, P, I32, P, P, P, P, P]
     L.enova_detect_ext_time.argtypes = [P, P]
     L.enova_detect_ext_mode.argtypes = [P, P]
-    L.enova_detect_ext_route.argtypes = [P, ctypes.c_int32, ctypes.c_int64, P]
+    L.enova_detect_ext_route.argtypes = [P, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, P]
     L.enova_config_t_critical.argtypes = [D, I32, P]
     L.enova_config_init.argtypes = [ctypes.POINTER(enova_config_params), ctypes.POINTER(P)]
     L.enova_config_destroy.argtypes = [P]
@@ -377,10 +377,10 @@ def enova_detect_ext_mode(handle):
     return v.value
 
 
-def enova_detect_ext_route(handle, n_streams, n_windows):
+def enova_detect_ext_route(handle, n_streams, n_windows, norm):
     v = ctypes.c_int32()
-    _check(lib().enova_detect_ext_route(ctypes.c_void_p(handle), int(n_streams), int(n_windows), ctypes.byref(v)),
-           "enova_detect_ext_route")
+    _check(lib().enova_detect_ext_route(ctypes.c_void_p(handle), int(n_streams), int(n_windows), int(norm),
+                                        ctypes.byref(v)), "enova_detect_ext_route")
     return v.value
 
 
@@ -496,9 +496,10 @@ class Detector:
     def ext_fused(self):
         return enova_detect_ext_mode(self.handle) == 1
 
-    def ext_route(self, n_streams, n_windows):
+    def ext_route(self, n_streams, n_windows, norm="reference"):
         """The evaluation that a score_ext call of so many streams and windows takes."""
-        return ("chunked", "fused", "split")[enova_detect_ext_route(self.handle, n_streams, n_windows)]
+        norm = {"reference": ENOVA_NORM_REFERENCE, "window": ENOVA_NORM_WINDOW}[norm]
+        return ("chunked", "fused", "split")[enova_detect_ext_route(self.handle, n_streams, n_windows, norm)]
 
     def window_offsets(self, stream_offsets_host):
         return enova_detect_window_offsets(self.handle, stream_offsets_host)

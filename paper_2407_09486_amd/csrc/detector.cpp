@@ -1324,10 +1324,10 @@ int64_t ext_tiles(int32_t n, int64_t n_windows) { return (n_windows + kExtFusedN
 
 // The evaluation of a variants call (ENOVA_EXT_*). A shape that only the split pass takes goes to the
 // chunked evaluation also where its tiles are more than a launch can have.
-int ext_route(enova_detector d, int32_t n, int64_t n_windows)
+int ext_route(enova_detector d, int32_t n, int64_t n_windows, int norm)
 {
     if (d->wd2x && (ext_fused_supported(d->g) ||
-                    (ext_tiles(n, n_windows) <= 0x7fffffffLL && ext_split_pays(d->g, d->sg, n_windows))))
+                    (ext_tiles(n, n_windows) <= 0x7fffffffLL && ext_split_pays(d->g, d->sg, n_windows, norm))))
         return ENOVA_EXT_SPLIT;
     return d->wd2p ? ENOVA_EXT_FUSED : ENOVA_EXT_CHUNKED;
 }
@@ -1367,7 +1367,7 @@ enova_status enova_detect_score_ext(enova_detector det, const void *x, const int
                 return hip_fail(e, "hipEventCreate");
     }
     const int D = g.D, H = g.H, L = g.L, M = g.M;
-    const int route = ext_route(det, n, n_windows);
+    const int route = ext_route(det, n, n_windows, norm);
     if (route != ENOVA_EXT_CHUNKED) {
         // fused pass: one block per 256-window tile, every output written directly
         const bool split = route == ENOVA_EXT_SPLIT;
@@ -1739,13 +1739,16 @@ enova_status enova_detect_ext_mode(enova_detector det, int32_t *fused)
     return ENOVA_OK;
 }
 
-enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t *route)
+enova_status enova_detect_ext_route(enova_detector det, int32_t n_streams, int64_t n_windows, int32_t norm,
+                                    int32_t *route)
 {
     if (!det || !route)
         return fail(ENOVA_EINVAL, "NULL argument");
     if (n_streams < 0 || n_windows < 0)
         return fail(ENOVA_EINVAL, "n_streams and n_windows must be >= 0");
-    *route = ext_route(det, n_streams, n_windows);
+    if (norm != ENOVA_NORM_REFERENCE && norm != ENOVA_NORM_WINDOW)
+        return fail(ENOVA_EINVAL, "bad normalisation mode");
+    *route = ext_route(det, n_streams, n_windows, norm);
     return ENOVA_OK;
 }
 

@@ -978,19 +978,34 @@ bool ext_split_supported(const Geometry &g, const SplitGeometry &sg)
 
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg) { return padded_d(g, sg); }
 
-// On few windows the pass takes as long as one tile's chain of steps, some 22 us and 0.06 us + 0.45 ns per
-// (padded) hidden unit for every padded element of a window; the chunked evaluation spreads few windows
-// over its products' tiles, 50 us and 1e-5 us per window and element. Measured, in us, this pass and the
+// On few windows the pass takes as long as one tile's chain of steps: some 25 us, 0.06 us + 0.45 ns per
+// (padded) hidden unit for every padded element of a window, tanh's epilogue, and against the window itself
+// 0.038 us for every element's share in its statistics. The chunked evaluation spreads few windows over its
+// products' tiles: 50 us and, a window, 2 to 4 ns and more with its elements and their products. Measured, in us,
+// under reference and window normalisation, this pass (the same from 500 windows to 16000, within 5) and the
 // chunked one at 500, 4000, 8000, 16000 windows:
-//   7 metrics, W = 60, H = 64, tanh (Dp = 480)     73-76    58  72  88 123
-//   5 metrics, W = 64, H = 128      (Dp = 512)     83-87    56  70  85 119
-//   12 metrics, W = 64, H = 64      (Dp = 1024)   108-113   55  78 108 157
-//   1 metric, W = 60, H = 64        (Dp = 480)     57-59    51  51  54  64
-//   3 metrics, W = 30, H = 24       (Dp = 240)     40-43    50  56  67  90
-bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows)
+//   7 metrics, W = 60, H = 64, tanh (Dp = 480)     76  91    61  74  89 123    52  72  92 138
+//   7 metrics, W = 128, S = 5, H = 5, tanh (1024)  109 141   59  75  93 130    52  71  96 148
+//   7 metrics, W = 120, H = 32      (Dp = 960)     90 122    58  71  89 128    51  67  93 145
+//   5 metrics, W = 64, H = 128      (Dp = 512)     86  96    60  73  86 121    55  71  91 137
+//   12 metrics, W = 64, H = 64      (Dp = 1024)   111 140    61  82 110 158    52  75 110 171
+//   12 metrics, W = 128, H = 32     (Dp = 2048)   174 235    61  80 112 160    55  77 116 177
+//   13 metrics, W = 32, H = 128, tanh (Dp = 512)  133 152    62  78  90 125    54  73  89 133
+//   6 metrics, W = 16, S = 3, H = 100, tanh (128)  81  81    61  66  75 102    52  63  78 115
+//   1 metric, W = 60, H = 64        (Dp = 480)     60  60    55  55  56  67    54  76 103 155
+//   1 metric, W = 200, H = 128      (Dp = 1600)   202 210    62  68  78 102    64  90 121 188
+//   3 metrics, W = 30, H = 24       (Dp = 240)     43  41    56  60  69  92    47  61  80 119
+bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows, int norm)
 {
-    const double chain = 22.0 + padded_d(g, sg) * (0.06 + 0.00045 * g.Hp);
-    return 50.0 + 1e-5 * static_cast<double>(n_windows) * g.D >= chain;
+    const bool own = norm == ENOVA_NORM_WINDOW;
+    const double D = g.D, H = g.H;
+    double chain = 25.0 + padded_d(g, sg) * (0.06 + 0.00045 * g.Hp);
+    if (g.act == ENOVA_TANH)
+        chain += g.Hp > 64 ? 42.0 : 11.0;
+    if (own)
+        chain += 0.038 * D;
+    const double each = own ? 4e-3 + 2.3e-6 * D + 1.5e-8 * D * H : 1.9e-3 + 2.4e-6 * D + 2.2e-8 * D * H;
+    return (own ? 50.0 : 56.0) + each * static_cast<double>(n_windows) >= chain;
 }
 
 hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg)

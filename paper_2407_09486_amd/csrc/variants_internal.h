@@ -91,7 +91,7 @@ struct ExtSplitShape {
 bool ext_split_supported(const Geometry &g, const SplitGeometry &sg);
 int ext_split_rows(const Geometry &g, const SplitGeometry &sg);   // Dp
 // Whether n_windows are enough for it, against the chunked evaluation.
-bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows);
+bool ext_split_pays(const Geometry &g, const SplitGeometry &sg, int64_t n_windows, int norm);
 hipError_t prepare_ext_split(const Geometry &g, const SplitGeometry &sg);
 // wd2_unscale: the inverse of the power of two that wd2x is scaled by
 hipError_t launch_ext_split(const Geometry &g, const SplitGeometry &sg, const ExtSplitParams &p, float wd2_unscale,

