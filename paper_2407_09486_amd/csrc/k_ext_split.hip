@@ -750,7 +750,8 @@ __global__ __launch_bounds__(256, 2) void k_ext_list(ExtSplitParams p, ExtSplitS
 #pragma unroll
                 for (int t = 0; t < 16; ++t) {
                     const float2 q = cak[m * C + sc];
-                    dst[t * PITCH] = (v[t] - q.y) * q.x;   // (past the end under weights of zero)
+                    // past the end zero, not the metric's normalised zero: that may be infinite
+                    dst[t * PITCH] = k + t < D ? (v[t] - q.y) * q.x : 0.0f;
                     m = m + 1 == M ? 0 : m + 1;
                 }
             };

@@ -193,3 +193,33 @@ def test_stretches_outside_the_range(norm, M, W, S, H, L, act, more, route):
         only = only[[wo[i] + k for i, k in pairs]]
     assert np.array_equal(only, res[0])
     det.close()
+
+
+@pytest.mark.parametrize("M,W,S,H", [(6, 1, 1, 64), (7, 9, 1, 50), (8, 6, 5, 33)])
+def test_infinite_reference_mean(M, W, S, H):
+    """A metric whose reference mean is infinite makes v infinite at every step; tanh's hidden layer is then all ones
+    in size and the scores are finite, as the chunked evaluation has them: the padding of the list's runs
+    may not turn them into NaN."""
+    import torch
+    cfg = wl.CONFIGS["c1"].replace(metrics=M, window=W, stride=S, hidden=H, act="tanh", n_streams=2)
+    rng = np.random.default_rng(M * W)
+    offs = np.array([0, 400, 700], np.int64)
+    w = wl.from_arrays(cfg, rng.standard_normal((700, M)), offs)
+    # one sign for every step's weight, or infinities of both would meet
+    weights = wl.make_weights(cfg, bias_scale=0.1)
+    weights.w1.reshape(H, W, M)[:, :, 0] = np.sign(weights.w1.reshape(H, W, M)[:, :1, 0])
+    log(f"[ext split] infinite mean M={M} W={W} S={S} H={H}")
+    mean, std = np.zeros((2, M)), np.ones((2, M))
+    mean[1, 0] = np.inf
+    det = detector(cfg, weights)
+    x, so = upload(w)
+    wo = det.window_offsets(offs)
+    assert det.ext_route(2, int(wo[-1])) == "split"
+    out = det.score_ext(x, so, torch.from_numpy(wo).cuda(), int(wo[-1]), ref_mean=torch.from_numpy(mean).float().cuda(),
+                        ref_std=torch.from_numpy(std).float().cuda())[0].cpu().numpy().astype(np.float64)
+    det.close()
+    ref = ov.score_ext(w.values_f64(), offs, window=W, stride=S, weights={k: np.asarray(getattr(weights, k), np.float64) for k in
+                       ("w1", "b1", "wmu", "bmu", "wlv", "blv", "wd1", "bd1", "wd2", "bd2")},
+                       act="tanh", ref_mean=mean, ref_std=std)["score"]
+    out, ref = out[wo[1]:], ref[wo[1]:]                  # the second stream's: sums of H exact products, 16 squares
+    assert np.all(np.isfinite(ref)) and np.all(np.abs(out - ref) <= 1e-5 * np.abs(ref))
